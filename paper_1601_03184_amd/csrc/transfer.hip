@@ -43,15 +43,6 @@ struct TransArgs {
     float *yco;
 };
 
-// native element offset (without the vector part) of row r of half h of an aggregate, the
-// aggregate's site offsets staged in sbase
-__device__ inline uint32_t trow_off(const uint32_t *sbase, int h, uint32_t cstr, int r)
-{
-    const int sl = r / 6, q = r - 6 * sl;
-    const int sp = q >= 3 ? 1 : 0, c = q - 3 * sp;
-    return sbase[sl] + (uint32_t)(2 * (3 * (2 * h + sp) + c)) * cstr;
-}
-
 // vector k of a native set: group and lane part of the element offset
 __device__ inline size_t tcol_off(const KGeo &g, int k)
 {
@@ -69,78 +60,139 @@ __device__ inline void stage_agg_sites(const TransArgs &a, int i, uint32_t *sbas
     __syncthreads();
 }
 
+// The 6Va rows of an aggregate half are taken component by component, the sites innermost
+// (the contraction over rows and the order of the output rows are free): consecutive rows are
+// consecutive sites of one component plane, so that a load covers runs of S elements of
+// several sites side by side.  16-row block B holds sites s0 .. s0 + 15 of component q, the last
+// block of a component padded with rows that read as zero.
+struct RowBlock {
+    uint32_t co;  // element offset of the component's real plane
+    int s0;       // first site
+};
+
+__device__ inline RowBlock row_block(int B, int nbq, int h, uint32_t cstr)
+{
+    const int q = B / nbq;
+    return {(uint32_t)(2 * (6 * h + q)) * cstr, 16 * (B - q * nbq)};
+}
+
 // ---------------------------------------------------------------------------------------
 // restriction: one workgroup per (aggregate i, half h).  Output tiles: rows j (test
-// vectors), columns k (right-hand sides), at most 2 x 2.  The wavefronts split the 6Va rows
-// (K) and their partial tiles are summed in LDS in a fixed order.
+// vectors), columns k (right-hand sides), NJ x NK of 16.  The wavefronts split the 16-row blocks
+// (K) and their partial tiles are summed in LDS in a fixed order.  Bound by the reads of Q and
+// y: a block's operands (K step j: sites s0 + 4j .. + 3, whose S elements per group form one
+// run) are loaded while the previous block is on the matrix cores.  24^3 x 48, 32 vectors in
+// FP32, restriction and prolongation together (8.2 GB): 3.59-3.91 ms with the rows site by site
+// (16-byte runs, one K step's loads at a time), 1.83 ms so, the rate of a device copy.
 // ---------------------------------------------------------------------------------------
-template <typename Tq, typename Ty>
+template <typename Tq, typename Ty, int NJ, int NK> struct RestrictRaw {
+    Tq q[4][NJ][2];
+    Ty y[4][NK][2];
+    uint32_t ok;  // bit j: the site of K step j is in range
+};
+
+template <typename Tq, typename Ty, int NJ, int NK>
 __global__ void __launch_bounds__(TTHR) k_restrict(TransArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *sbase = reinterpret_cast<uint32_t *>(smem);          // [Va]
     float *part = reinterpret_cast<float *>(sbase + a.Va);          // [2 (re/im)][32][32]
     const int i = blockIdx.x >> 1, h = blockIdx.x & 1;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const Tq *Q = static_cast<const Tq *>(a.Q);
-    const Ty *y = static_cast<const Ty *>(a.y);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t cstr = (uint32_t)a.g.Vb * (uint32_t)a.g.S;
-    const int TJ = (a.N + 15) / 16, TK = (a.n + 15) / 16;
     stage_agg_sites(a, i, sbase);
 
-    f4 ar[2][2], ai[2][2];
+    f4 ar[NJ][NK], ai[NJ][NK];
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < NJ; ++x)
 #pragma unroll
-        for (int z = 0; z < 2; ++z) ar[x][z] = ai[x][z] = f4{0.f, 0.f, 0.f, 0.f};
-    // per lane: test vector j = 16 tj + l%16 (A operand column), rhs k = 16 tk + l%16
-    size_t qo[2], yo[2];
-    bool qok[2], yok[2];
+        for (int z = 0; z < NK; ++z) ar[x][z] = ai[x][z] = f4{0.f, 0.f, 0.f, 0.f};
+    // per lane: test vector j = 16 tj + l%16 (A operand column), rhs k = 16 tk + l%16; a vector out
+    // of range reads vector 0 and only reaches outputs that are not stored
+    const Tq *qp[NJ];
+    const Ty *yp[NK];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < NJ; ++t) {
         const int j = 16 * t + (lane & 15);
-        qok[t] = t < TJ && j < a.N;
-        qo[t] = qok[t] ? tcol_off(a.g, j) : 0;
-        yok[t] = t < TK && j < a.n;
-        yo[t] = yok[t] ? tcol_off(a.g, j) : 0;
+        qp[t] = static_cast<const Tq *>(a.Q) + (j < a.N ? tcol_off(a.g, j) : 0);
     }
-    const int rows = 6 * a.Va;
-    for (int r0 = 4 * wave; r0 < rows; r0 += 4 * TNW) {
-        const int r = r0 + (lane >> 4);
-        const bool rok = r < rows;
-        const uint32_t ro = rok ? trow_off(sbase, h, cstr, r) : 0;
-        float qr[2], qi[2], yr[2], yi[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const bool okq = rok && qok[t], oky = rok && yok[t];
-            const size_t iq = okq ? ro + qo[t] : 0, iy = oky ? ro + yo[t] : 0;
-            const float a0 = to_f32(Q[iq]), a1 = to_f32(Q[okq ? iq + cstr : 0]);
-            const float b0 = to_f32(y[iy]), b1 = to_f32(y[oky ? iy + cstr : 0]);
-            qr[t] = okq ? a0 : 0.f;
-            qi[t] = okq ? a1 : 0.f;
-            yr[t] = oky ? b0 : 0.f;
-            yi[t] = oky ? b1 : 0.f;
-        }
-        // conj(q) y = (qr yr + qi yi) + i (qr yi - qi yr)
+    for (int t = 0; t < NK; ++t) {
+        const int k = 16 * t + (lane & 15);
+        yp[t] = static_cast<const Ty *>(a.y) + (k < a.n ? tcol_off(a.g, k) : 0);
+    }
+    const int nbq = (a.Va + 15) / 16, nblocks = 6 * nbq;
+    using Raw = RestrictRaw<Tq, Ty, NJ, NK>;
+    auto load = [&](int B, Raw &o) {
+        const RowBlock rb = row_block(B, nbq, h, cstr);
+        o.ok = 0;
 #pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
+        for (int j = 0; j < 4; ++j) {
+            const int n = rb.s0 + 4 * j + (lane >> 4);
+            const bool ok = n < a.Va;
+            const uint32_t ro = sbase[ok ? n : 0] + rb.co;
+            o.ok |= (uint32_t)ok << j;
 #pragma unroll
-            for (int tk = 0; tk < 2; ++tk) {
-                if (tj >= TJ || tk >= TK) continue;
-                ar[tj][tk] = mfma32(qr[tj], yr[tk], ar[tj][tk]);
-                ar[tj][tk] = mfma32(qi[tj], yi[tk], ar[tj][tk]);
-                ai[tj][tk] = mfma32(qr[tj], yi[tk], ai[tj][tk]);
-                ai[tj][tk] = mfma32(-qi[tj], yr[tk], ai[tj][tk]);
+            for (int t = 0; t < NJ; ++t) {
+                o.q[j][t][0] = qp[t][ro];
+                o.q[j][t][1] = qp[t][ro + cstr];
             }
+#pragma unroll
+            for (int t = 0; t < NK; ++t) {
+                o.y[j][t][0] = yp[t][ro];
+                o.y[j][t][1] = yp[t][ro + cstr];
+            }
+        }
+    };
+    auto products = [&](const Raw &o) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool ok = (o.ok >> j) & 1u;
+            float qr[NJ], qi[NJ], yr[NK], yi[NK];
+#pragma unroll
+            for (int t = 0; t < NJ; ++t) {
+                qr[t] = ok ? to_f32(o.q[j][t][0]) : 0.f;
+                qi[t] = ok ? to_f32(o.q[j][t][1]) : 0.f;
+            }
+#pragma unroll
+            for (int t = 0; t < NK; ++t) {
+                yr[t] = ok ? to_f32(o.y[j][t][0]) : 0.f;
+                yi[t] = ok ? to_f32(o.y[j][t][1]) : 0.f;
+            }
+            // conj(q) y = (qr yr + qi yi) + i (qr yi - qi yr)
+#pragma unroll
+            for (int tj = 0; tj < NJ; ++tj)
+#pragma unroll
+                for (int tk = 0; tk < NK; ++tk) {
+                    ar[tj][tk] = mfma32(qr[tj], yr[tk], ar[tj][tk]);
+                    ai[tj][tk] = mfma32(qr[tj], yi[tk], ai[tj][tk]);
+                    ar[tj][tk] = mfma32(qi[tj], yi[tk], ar[tj][tk]);
+                    ai[tj][tk] = mfma32(-qi[tj], yr[tk], ai[tj][tk]);
+                }
+        }
+    };
+    // two operand sets take turns, so that no register copy waits for loads in flight
+    {
+        Raw ra, rb;
+        int B = wave;
+        if (B < nblocks) load(B, ra);
+        while (B < nblocks) {
+            if (B + TNW < nblocks) load(B + TNW, rb);
+            products(ra);
+            B += TNW;
+            if (B >= nblocks) break;
+            if (B + TNW < nblocks) load(B + TNW, ra);
+            products(rb);
+            B += TNW;
+        }
     }
     // partial tiles of the wavefronts summed in order
     for (int w = 0; w < TNW; ++w) {
         if (wave == w) {
 #pragma unroll
-            for (int tj = 0; tj < 2; ++tj)
+            for (int tj = 0; tj < NJ; ++tj)
 #pragma unroll
-                for (int tk = 0; tk < 2; ++tk) {
-                    if (tj >= TJ || tk >= TK) continue;
+                for (int tk = 0; tk < NK; ++tk) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int j = 16 * tj + 4 * (lane >> 4) + q, k = 16 * tk + (lane & 15);
@@ -165,20 +217,21 @@ __global__ void __launch_bounds__(TTHR) k_restrict(TransArgs a)
 // ---------------------------------------------------------------------------------------
 // prolongation: PSPLIT workgroups per (aggregate i, half h), each taking every PSPLIT-th
 // group of 16-row blocks (the output rows are independent).  (y_c)^h_i is staged in LDS;
-// each wavefront forms 16-row blocks of Q^h_i (y_c)^h_i, K = the test vectors.
+// each wavefront forms 16-row blocks of Q^h_i (y_c)^h_i, K = the test vectors.  Operand row
+// 4g + q of a block is site s0 + 4q + g, so that accumulator register q of the four lane
+// groups g = l/16 holds four neighbouring sites and a store covers their runs side by side.
 // ---------------------------------------------------------------------------------------
-template <typename Tq, typename Ty>
+template <typename Tq, typename Ty, int NK>
 __global__ void __launch_bounds__(TTHR) k_prolong(TransArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *sbase = reinterpret_cast<uint32_t *>(smem);  // [Va]
     float *ycs = reinterpret_cast<float *>(sbase + a.Va);   // [2 (re/im)][32 (j)][32 (k)]
     const int i = blockIdx.x >> 1, h = blockIdx.x & 1;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Tq *Q = static_cast<const Tq *>(a.Q);
     Ty *yo = static_cast<Ty *>(a.yo);
     const uint32_t cstr = (uint32_t)a.g.Vb * (uint32_t)a.g.S;
-    const int TK = (a.n + 15) / 16, KS = (a.N + 3) / 4;
     for (int e = threadIdx.x; e < 2048; e += blockDim.x) {
         const int p = e >> 10, j = (e >> 5) & 31, k = e & 31;
         float v = 0.f;
@@ -188,48 +241,65 @@ __global__ void __launch_bounds__(TTHR) k_prolong(TransArgs a)
     stage_agg_sites(a, i, sbase);
     // output lanes: the n right-hand sides and the padding lanes of the last group (zero)
     const int nw = (a.n + a.g.S - 1) / a.g.S * a.g.S;
-    size_t yoff[2];
-    bool kok[2], kin[2];
+    size_t yoff[NK];
+    bool kok[NK], kin[NK];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < NK; ++t) {
         const int k = 16 * t + (lane & 15);
-        kok[t] = t < TK && k < nw;
+        kok[t] = k < nw;
         kin[t] = k < a.n;
         yoff[t] = kok[t] ? tcol_off(a.g, k) : 0;
     }
-    const int rows = 6 * a.Va;
-    for (int b0 = 16 * (wave + TNW * (int)blockIdx.y); b0 < rows; b0 += 16 * TNW * (int)gridDim.y) {
-        const int ra = b0 + (lane & 15);  // A operand row
-        const bool raok = ra < rows;
-        const uint32_t roa = raok ? trow_off(sbase, h, cstr, ra) : 0;
-        f4 dr[2], di[2];
+    const int nbq = (a.Va + 15) / 16, nblocks = 6 * nbq;
+    const int r16 = lane & 15, asite = 4 * (r16 & 3) + (r16 >> 2);  // A operand row -> site of the block
+    // this lane's columns j = 4 ks + l/16: vectors out of range read vector 0 and meet zero rows
+    // of (y_c)^h_i
+    size_t qoff[8];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) dr[t] = di[t] = f4{0.f, 0.f, 0.f, 0.f};
-        for (int ks = 0; ks < KS; ++ks) {
-            const int j = 4 * ks + (lane >> 4);  // K index: test vector
-            const bool ok = raok && j < a.N;
-            const size_t iq = ok ? roa + tcol_off(a.g, j) : 0;
-            const float q0 = to_f32(Q[iq]), q1 = to_f32(Q[ok ? iq + cstr : 0]);
-            const float qr = ok ? q0 : 0.f, qi = ok ? q1 : 0.f;
+    for (int ks = 0; ks < 8; ++ks) {
+        const int j = 4 * ks + (lane >> 4);
+        qoff[ks] = j < a.N ? tcol_off(a.g, j) : 0;
+    }
+    const int KS = (a.N + 3) / 4;
+    for (int B = wave + TNW * (int)blockIdx.y; B < nblocks; B += TNW * (int)gridDim.y) {
+        const RowBlock rb = row_block(B, nbq, h, cstr);
+        const int n = rb.s0 + asite;
+        const Tq *qr0 = Q + (sbase[n < a.Va ? n : 0] + rb.co);
+        Tq q0[8], q1[8];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                if (t >= TK) continue;
-                const int k = 16 * t + (lane & 15);
+        for (int ks = 0; ks < 8; ++ks) {
+            if (ks < KS) {
+                q0[ks] = qr0[qoff[ks]];
+                q1[ks] = qr0[qoff[ks] + cstr];
+            }
+        }
+        f4 dr[NK], di[NK];
+#pragma unroll
+        for (int t = 0; t < NK; ++t) dr[t] = di[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            if (ks >= KS) break;
+            const int j = 4 * ks + (lane >> 4);
+            const bool ok = j < a.N;
+            const float qr = ok ? to_f32(q0[ks]) : 0.f, qi = ok ? to_f32(q1[ks]) : 0.f;
+#pragma unroll
+            for (int t = 0; t < NK; ++t) {
+                const int k = 16 * t + r16;
                 const float br = ycs[j * 32 + k], bi = ycs[1024 + j * 32 + k];  // j < 32 always
                 // q y_c = (qr br - qi bi) + i (qr bi + qi br)
                 dr[t] = mfma32(qr, br, dr[t]);
-                dr[t] = mfma32(-qi, bi, dr[t]);
                 di[t] = mfma32(qr, bi, di[t]);
+                dr[t] = mfma32(-qi, bi, dr[t]);
                 di[t] = mfma32(qi, br, di[t]);
             }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int r = b0 + 4 * (lane >> 4) + q;
-            if (r >= rows) continue;
-            const uint32_t ro = trow_off(sbase, h, cstr, r);
+            const int ns = rb.s0 + 4 * q + (lane >> 4);
+            if (ns >= a.Va) continue;
+            const uint32_t ro = sbase[ns] + rb.co;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < NK; ++t) {
                 if (!kok[t]) continue;
                 const size_t idx = ro + yoff[t];
                 yo[idx] = store_as<Ty>(kin[t] ? dr[t][q] : 0.f);
@@ -651,14 +721,20 @@ TransArgs trans_args(const mrhs_op *op, int n_tv, int n)
 template <typename Tq, typename Ty> int restrict_typed(const TransArgs &a, hipStream_t st)
 {
     const size_t lds = sizeof(uint32_t) * a.Va + sizeof(float) * 2048;
-    hipLaunchKernelGGL((k_restrict<Tq, Ty>), dim3(2 * a.n_agg), dim3(TTHR), lds, st, a);
+    const dim3 grid(2 * a.n_agg), block(TTHR);
+    if (a.N > 16 && a.n > 16) hipLaunchKernelGGL((k_restrict<Tq, Ty, 2, 2>), grid, block, lds, st, a);
+    else if (a.N > 16) hipLaunchKernelGGL((k_restrict<Tq, Ty, 2, 1>), grid, block, lds, st, a);
+    else if (a.n > 16) hipLaunchKernelGGL((k_restrict<Tq, Ty, 1, 2>), grid, block, lds, st, a);
+    else hipLaunchKernelGGL((k_restrict<Tq, Ty, 1, 1>), grid, block, lds, st, a);
     return hip_check(hipGetLastError(), "k_restrict launch");
 }
 
 template <typename Tq, typename Ty> int prolong_typed(const TransArgs &a, hipStream_t st)
 {
     const size_t lds = sizeof(uint32_t) * a.Va + sizeof(float) * 2048;
-    hipLaunchKernelGGL((k_prolong<Tq, Ty>), dim3(2 * a.n_agg, PSPLIT), dim3(TTHR), lds, st, a);
+    const dim3 grid(2 * a.n_agg, PSPLIT);
+    if (a.n > 16) hipLaunchKernelGGL((k_prolong<Tq, Ty, 2>), grid, dim3(TTHR), lds, st, a);
+    else hipLaunchKernelGGL((k_prolong<Tq, Ty, 1>), grid, dim3(TTHR), lds, st, a);
     return hip_check(hipGetLastError(), "k_prolong launch");
 }
 
