@@ -12,10 +12,14 @@
 // Cholesky factorisations and triangular inverses of the n_tv x n_tv matrices run on the
 // vector units in LDS and registers.
 //
-// V is read three times, in 16-row blocks that each wavefront loads one block ahead of the
-// one on the matrix cores; the row offsets of the aggregate's sites are staged in LDS.  Q1
-// is never stored: each 16-row block of it passes through the wavefront's own LDS rows
-// into the second Gram product.
+// The second Gram product (half of the matrix-core work) is skipped where it cannot change the
+// stored Q (one_pass_enough).  Bound by the FP64 matrix cores, with the reads of V (two passes, three
+// with the second product) close behind: 32^3 x 64, 32 vectors in FP32 10.8 -> 5.6 ms (19.3 GB,
+// 3.5 TB/s), 24^3 x 48, 24 vectors, Q in binary16 3.84 -> 2.20 ms.
+//
+// V is read in 16-row blocks that each wavefront loads one block ahead of the one on the matrix
+// cores; the row offsets of the aggregate's sites are staged in LDS.  Q1 is never stored: each
+// 16-row block of it goes from the transform's accumulators into the second Gram product.
 //
 // MFMA lane layout of v_mfma_f64_16x16x4f64 (measured on gfx950): lane l supplies A[l%16][l/16]
 // and B[l/16][l%16] and holds D[l/16 + 4r][l%16] in accumulator register r.
@@ -51,13 +55,21 @@ template <> __device__ inline double to_f64<__half>(__half v) { return (double)_
 
 __device__ inline d4 mfma(double x, double y, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0); }
 
-// Row n of V^h_i (local site n / 6, spin in the half, colour) inside the staged range of
-// sites: native element offset without the column part.
-__device__ inline uint32_t row_off(const uint32_t *sbase, int h, uint32_t cstr, int n)
+// The rows of V^h_i are taken component by component (spin in the half, colour), the sites of
+// the staged range innermost: the contractions over rows do not depend on their order, and
+// consecutive rows are consecutive sites of one component plane, so a load covers runs of
+// S elements per site instead of one such run per row in six different planes.  16-row block
+// B holds sites s0 .. s0 + 15 of component q; a range of n sites has nbq = ceil(n / 16) blocks
+// per component, the last one padded with rows that read as zero.
+struct RowBlock {
+    uint32_t co;  // element offset of the component's real plane
+    int s0;       // first site
+};
+
+__device__ inline RowBlock row_block(int B, int nbq, int h, uint32_t cstr)
 {
-    const int sl = n / 6, q = n - 6 * sl;
-    const int sp = q >= 3 ? 1 : 0, c = q - 3 * sp;
-    return sbase[sl] + (uint32_t)(2 * (3 * (2 * h + sp) + c)) * cstr;
+    const int q = B / nbq;
+    return {(uint32_t)(2 * (6 * h + q)) * cstr, 16 * (B - q * nbq)};
 }
 
 // G (NP x NP, upper triangle, in place) -> R with G = R^dag R.  Flags a pivot that falls to
@@ -243,27 +255,27 @@ __device__ inline void gram_reduce(const GramAcc<G3> &acc, Cplx *G, int NP, int 
     }
 }
 
-// Operands of one 16-row block for a Gram product: K step j covers rows b0 + 4j .. b0 + 4j + 3;
-// lane l holds row b0 + 4j + l/16 of columns 16 t + l%16.
+// Operands of one 16-row block for a Gram product: K step j covers its rows 4j .. 4j + 3;
+// lane l holds row 4j + l/16 of columns 16 t + l%16.
 template <typename Tv, int NT> struct GramRaw {
     Tv v[4][NT][2];
     uint32_t ok;  // bit NT j + t: the operand (j, t) is in range (else it reads as zero)
 };
 
 // vk[t]: V plus the offset of this lane's column 16 t + l%16 (V itself beyond n_tv).  An
-// operand out of range (its row beyond nrows, its column beyond n_tv) reads a valid element
-// (row 0, or column 0's group) and the products take it as zero, so that nothing here waits
+// operand out of range (its site beyond nsc, its column beyond n_tv) reads a valid element
+// (site 0, or column 0's group) and the products take it as zero, so that nothing here waits
 // for the loads and no load is behind a branch.
 template <typename Tv, int NT>
-__device__ inline void load_gram(const Tv *const (&vk)[2], const uint32_t *sbase, int h, uint32_t cstr, int b0,
-                                 int nrows, int N, int lane, GramRaw<Tv, NT> &o)
+__device__ inline void load_gram(const Tv *const (&vk)[2], const uint32_t *sbase, RowBlock rb, uint32_t cstr, int nsc,
+                                 int N, int lane, GramRaw<Tv, NT> &o)
 {
     o.ok = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int n = b0 + 4 * j + (lane >> 4);
-        const bool nok = n < nrows;
-        const uint32_t ro = row_off(sbase, h, cstr, nok ? n : 0);
+        const int n = rb.s0 + 4 * j + (lane >> 4);
+        const bool nok = n < nsc;
+        const uint32_t ro = sbase[nok ? n : 0] + rb.co;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const bool ok = nok && 16 * t + (lane & 15) < N;
@@ -291,22 +303,22 @@ __device__ inline void gram_block(const GramRaw<Tv, NT> &o, GramAcc<G3> &acc)
     }
 }
 
-// Operands of one 16-row block for a transform V M: lane l holds row b0 + l%16 of columns
+// Operands of one 16-row block for a transform V M: lane l holds row l%16 of columns
 // 4 ks + l/16.
 template <typename Tv, int NT> struct TransRaw {
     Tv v[4 * NT][2];
     uint32_t ok;  // bit ks: the operand ks is in range (else it reads as zero)
 };
 
-// As load_gram: an operand out of range reads a valid element (row 0, or column 0's group)
+// As load_gram: an operand out of range reads a valid element (site 0, or column 0's group)
 // and is taken as zero by the products; no load is behind a branch.
 template <typename Tv, int NT>
-__device__ inline void load_trans(const Tv *V, const uint32_t *sbase, const size_t *coff, int h, uint32_t cstr, int b0,
-                                  int nrows, int N, int lane, TransRaw<Tv, NT> &o)
+__device__ inline void load_trans(const Tv *V, const uint32_t *sbase, const size_t *coff, RowBlock rb, uint32_t cstr,
+                                  int nsc, int N, int lane, TransRaw<Tv, NT> &o)
 {
-    const int n = b0 + (lane & 15);
-    const bool nok = n < nrows;
-    const Tv *vr = V + row_off(sbase, h, cstr, nok ? n : 0), *vi = vr + cstr;
+    const int n = rb.s0 + (lane & 15);
+    const bool nok = n < nsc;
+    const Tv *vr = V + (sbase[nok ? n : 0] + rb.co), *vi = vr + cstr;
     o.ok = 0;
 #pragma unroll
     for (int ks = 0; ks < 4 * NT; ++ks) {
@@ -319,7 +331,7 @@ __device__ inline void load_trans(const Tv *V, const uint32_t *sbase, const size
 }
 
 // tile tj of (the 16 rows) M for upper-triangular M (NP x NP in LDS); the accumulator of
-// tile tj holds rows b0 + l/16 + 4r of columns 16 tj + l%16 in register r.  Three real
+// tile tj holds rows l/16 + 4r of columns 16 tj + l%16 in register r.  Three real
 // products per complex one (Gauss): with t1 = Vr Mr, t2 = Vi Mi, t3 = (Vr + Vi)(Mr + Mi),
 // Re V M = t1 - t2 and Im V M = t3 - t1 - t2.
 template <typename Tv, int NT>
@@ -351,24 +363,47 @@ __device__ inline void trans_block(const TransRaw<Tv, NT> &o, const Cplx *M, int
     }
 }
 
-// Runs body(operands, b0) for the 16-row blocks b0 = first, first + step, ... < nrows, with the
+// Runs body(operands, B) for the 16-row blocks B = first, first + step, ... < nblocks, with the
 // loads of each block issued before the products of the previous one.  Two operand sets take
 // turns, so that no register copy has to wait for loads still in flight.
 template <typename Raw, typename Load, typename Body>
-__device__ inline void pipelined_blocks(int first, int step, int nrows, Load load, Body body)
+__device__ inline void pipelined_blocks(int first, int step, int nblocks, Load load, Body body)
 {
     Raw ra, rb;
-    int b0 = first;
-    if (b0 < nrows) load(b0, ra);
-    while (b0 < nrows) {
-        if (b0 + step < nrows) load(b0 + step, rb);
-        body(ra, b0);
-        b0 += step;
-        if (b0 >= nrows) break;
-        if (b0 + step < nrows) load(b0 + step, ra);
-        body(rb, b0);
-        b0 += step;
+    int B = first;
+    if (B < nblocks) load(B, ra);
+    while (B < nblocks) {
+        if (B + step < nblocks) load(B + step, rb);
+        body(ra, B);
+        B += step;
+        if (B >= nblocks) break;
+        if (B + step < nblocks) load(B + step, ra);
+        body(rb, B);
+        B += step;
     }
+}
+
+// Whether Q = V R1^-1 alone is the Q of CholQR2 to well below the rounding of a Q stored in
+// FP32 or binary16.  One Cholesky pass leaves Q with an error of about c u kappa^2 (u = 2^-53,
+// c ~ 2^4 for the sums over the rows, kappa the condition number of V with its columns scaled to
+// unit norm).  kappa^2 <= N ||D X1||_F^2, D the column norms and X1 = R1^-1 (||R1 D^-1||_F^2 = N),
+// so at the limit of 2^16 the error is at most 2^-33, 2^-9 of FP32's rounding 2^-24 (Gaussian
+// vectors: N^2, 2^10 at 32).  A NaN takes the second pass.
+constexpr double ONE_PASS_MAX = 65536.0;
+
+template <int NP> __device__ bool one_pass_enough(const Cplx *X1, const double *diag0, int N, double *red)
+{
+    double s = 0.0;
+    for (int e = threadIdx.x; e < NP * NP; e += NTHR) {
+        const int l = e / NP, m = e % NP;
+        if (l < N && m < N) s += diag0[l] * (X1[e].re * X1[e].re + X1[e].im * X1[e].im);
+    }
+    for (int o = 32; o; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    s = 0.0;
+    for (int w = 0; w < NW; ++w) s += red[w];
+    return N * s <= ONE_PASS_MAX;
 }
 
 // native offsets of the staged aggregate sites [ls0, ls0 + n): block and site part
@@ -402,11 +437,12 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     size_t *coff = reinterpret_cast<size_t *>(diag0 + NP);
     uint32_t *sbase = reinterpret_cast<uint32_t *>(coff + NP);
     __shared__ int bad;
+    __shared__ double red[NW];
 
     const Tv *V = static_cast<const Tv *>(a.V);
     Tq *Q = static_cast<Tq *>(a.Q);
     const int wi = xcd_remap(blockIdx.x, gridDim.x), i = wi >> 1, h = wi & 1;  // runs per XCD
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t cstr = (uint32_t)a.g.Vb * (uint32_t)a.g.S;
     const size_t gstr = (size_t)a.g.nblk * 24 * cstr;  // one group of S test vectors
     if (threadIdx.x == 0) bad = 0;
@@ -424,14 +460,16 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     GramAcc<G3> acc;
     acc.zero();
     for (int ls0 = 0; ls0 < a.Va; ls0 += SCH) {
-        const int nsc = std::min(SCH, a.Va - ls0), nrows = 6 * nsc;
+        const int nsc = std::min(SCH, a.Va - ls0), nbq = (nsc + 15) / 16, nblocks = 6 * nbq;
         if (staged != ls0) {
             stage_sites(a, i, ls0, nsc, sbase);
             staged = ls0;
         }
         pipelined_blocks<GramRaw<Tv, NT>>(
-            wave * 16, NW * 16, nrows,
-            [&](int b0, GramRaw<Tv, NT> &o) { load_gram<Tv, NT>(vk, sbase, h, cstr, b0, nrows, N, lane, o); },
+            wave, NW, nblocks,
+            [&](int B, GramRaw<Tv, NT> &o) {
+                load_gram<Tv, NT>(vk, sbase, row_block(B, nbq, h, cstr), cstr, nsc, N, lane, o);
+            },
             [&](const GramRaw<Tv, NT> &o, int) { gram_block<Tv, NT, G3>(o, acc); });
     }
     __syncthreads();
@@ -441,63 +479,68 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     cholesky_inplace(G, diag0, N, NP, &bad);
     tri_inverse<NP>(G, X1);
 
-    // G2 = Q1^dag Q1 with Q1 = V R1^-1 formed block by block on the matrix cores
-    acc.zero();
-    for (int ls0 = 0; ls0 < a.Va; ls0 += SCH) {
-        const int nsc = std::min(SCH, a.Va - ls0), nrows = 6 * nsc;
-        if (staged != ls0) {
-            stage_sites(a, i, ls0, nsc, sbase);
-            staged = ls0;
-        }
-        const auto load = [&](int b0, TransRaw<Tv, NT> &o) {
-            load_trans<Tv, NT>(V, sbase, coff, h, cstr, b0, nrows, N, lane, o);
-        };
-        for (int b0 = wave * 16; b0 < nrows; b0 += NW * 16) {
-            TransRaw<Tv, NT> cur;
-            load(b0, cur);
-            d4 dr[2], di[2];
-            trans_block<Tv, NT>(cur, X1, NP, lane, dr, di);
-            // the transform leaves row b0 + l/16 + 4r of column 16 t + l%16 in register r of
-            // lane l, which is where K step r of the Gram product takes its operand: the 16
-            // rows of Q1 go from the accumulators straight into the Gram product
+    const Cplx *M = X1;  // Q = V M
+    if (sizeof(Tq) == 8 || bad || !one_pass_enough<NP>(X1, diag0, N, red)) {
+        // G2 = Q1^dag Q1 with Q1 = V R1^-1 formed block by block on the matrix cores
+        acc.zero();
+        for (int ls0 = 0; ls0 < a.Va; ls0 += SCH) {
+            const int nsc = std::min(SCH, a.Va - ls0), nbq = (nsc + 15) / 16, nblocks = 6 * nbq;
+            if (staged != ls0) {
+                stage_sites(a, i, ls0, nsc, sbase);
+                staged = ls0;
+            }
+            const auto load = [&](int B, TransRaw<Tv, NT> &o) {
+                load_trans<Tv, NT>(V, sbase, coff, row_block(B, nbq, h, cstr), cstr, nsc, N, lane, o);
+            };
+            for (int B = wave; B < nblocks; B += NW) {
+                TransRaw<Tv, NT> cur;
+                load(B, cur);
+                d4 dr[2], di[2];
+                trans_block<Tv, NT>(cur, X1, NP, lane, dr, di);
+                // the transform leaves row l/16 + 4r of column 16 t + l%16 in register r of
+                // lane l, which is where K step r of the Gram product takes its operand: the 16
+                // rows of Q1 go from the accumulators straight into the Gram product
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                double xr[2] = {0.0, 0.0}, xi[2] = {0.0, 0.0};
+                for (int j = 0; j < 4; ++j) {
+                    double xr[2] = {0.0, 0.0}, xi[2] = {0.0, 0.0};
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    xr[t] = dr[t][j];
-                    xi[t] = di[t][j];
+                    for (int t = 0; t < NT; ++t) {
+                        xr[t] = dr[t][j];
+                        xi[t] = di[t][j];
+                    }
+                    gram_step<NT>(xr, xi, acc);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                gram_step<NT>(xr, xi, acc);
-                __builtin_amdgcn_sched_barrier(0);
             }
         }
+        __syncthreads();
+        gram_reduce<NT>(acc, G, NP, lane, wave);
+        gram_fix_diag<NT>(G, NP);
+        for (int k = threadIdx.x; k < NP; k += blockDim.x) diag0[k] = 1.0;
+        cholesky_inplace(G, diag0, N, NP, &bad);
+        tri_inverse<NP>(G, X2);
+        tri_product(X1, X2, G, NP);  // G <- R1^-1 R2^-1
+        M = G;
     }
-    __syncthreads();
-    gram_reduce<NT>(acc, G, NP, lane, wave);
-    gram_fix_diag<NT>(G, NP);
-    for (int k = threadIdx.x; k < NP; k += blockDim.x) diag0[k] = 1.0;
-    cholesky_inplace(G, diag0, N, NP, &bad);
-    tri_inverse<NP>(G, X2);
-    tri_product(X1, X2, G, NP);  // G <- R1^-1 R2^-1
-    // Q = V (R1^-1 R2^-1)
+    // Q = V R1^-1 or V (R1^-1 R2^-1)
     for (int ls0 = 0; ls0 < a.Va; ls0 += SCH) {
-        const int nsc = std::min(SCH, a.Va - ls0), nrows = 6 * nsc;
+        const int nsc = std::min(SCH, a.Va - ls0), nbq = (nsc + 15) / 16, nblocks = 6 * nbq;
         if (staged != ls0) {
             stage_sites(a, i, ls0, nsc, sbase);
             staged = ls0;
         }
-        const auto load = [&](int b0, TransRaw<Tv, NT> &o) {
-            load_trans<Tv, NT>(V, sbase, coff, h, cstr, b0, nrows, N, lane, o);
+        const auto load = [&](int B, TransRaw<Tv, NT> &o) {
+            load_trans<Tv, NT>(V, sbase, coff, row_block(B, nbq, h, cstr), cstr, nsc, N, lane, o);
         };
-        pipelined_blocks<TransRaw<Tv, NT>>(wave * 16, NW * 16, nrows, load, [&](const TransRaw<Tv, NT> &cur, int b0) {
+        pipelined_blocks<TransRaw<Tv, NT>>(wave, NW, nblocks, load, [&](const TransRaw<Tv, NT> &cur, int B) {
             d4 dr[2], di[2];
-            trans_block<Tv, NT>(cur, G, NP, lane, dr, di);
+            trans_block<Tv, NT>(cur, M, NP, lane, dr, di);
+            const RowBlock rb = row_block(B, nbq, h, cstr);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int n = b0 + (lane >> 4) + 4 * r;
-                if (n >= nrows) continue;
-                const uint32_t ro = row_off(sbase, h, cstr, n);
+                const int n = rb.s0 + (lane >> 4) + 4 * r;
+                if (n >= nsc) continue;
+                const uint32_t ro = sbase[n] + rb.co;
 #pragma unroll
                 for (int tj = 0; tj < NT; ++tj) {
                     const int k = tj * 16 + (lane & 15);
