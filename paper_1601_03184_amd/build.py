@@ -22,6 +22,9 @@ FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-I" + INCLUDE,
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",
+    # a kernel argument structure with many uses (the SAP batch) is read in place from the kernel
+    # arguments; above the default limit of uses the compiler copies it to scratch first
+    "-mllvm", "-instcombine-max-copied-from-constant-users=4000",
 ]
 
 

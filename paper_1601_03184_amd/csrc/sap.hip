@@ -4,13 +4,19 @@
 // uneven size, each with its own right-hand sides).  Workgroup = one SAP block of that
 // colour x a tile of T right-hand sides; thread (off, t) owns one site of the block and
 // one right-hand side.  The workgroup
-//   1. forms the residual r = b - D x on its block (full stencil, neighbours from global
-//      memory; skipped where x is known to be zero),
+//   1. forms the residual r = b - D x on its block: the full stencil on a first visit from a
+//      guess, afterwards the block's kept residual minus the hops across its faces, which the
+//      neighbours left, spin-projected and multiplied by the link, in face buffers (read once and
+//      in order, a quarter of the loads of reading the neighbours' spinors across the faces; all
+//      of them in flight at once),
 //   2. runs n_mr minimal-residual steps on the block operator D_j = I_j^T D I_j with the
 //      block residual rho kept in LDS ([24][Vb][T], conflict-free for the thread order),
 //      the two inner products per step reduced across the block with wavefront shuffles
 //      and one LDS exchange, and the correction e kept in registers,
-//   3. writes x|_j (+)= e.
+//   3. writes x|_j (+)= e, its residual and its own faces.
+// 32^3 x 64, 32 right-hand sides in FP32, 3 x 4: 49.5 -> 46.5 ms per call with the face buffers (of the
+// 30 vector sets that a call must move at 4.4 TB/s, 22 ms); the even-odd solver, which formed the
+// full residual at every visit, 3.59 -> 2.84 ms at 16^3 x 32 with 24.
 // The links and clover of a site are loaded once per stencil for all T lanes of the site.
 // With the even-odd block solver (k_sap_batched_eo) step 2 runs on the block's Schur
 // complement over its even sites instead (sap_block_eo).
@@ -22,6 +28,48 @@
 #include <type_traits>
 
 namespace {
+
+// Faces of a block: for every direction mu with more than one block, the +mu face and then the
+// -mu face, each [12 / n][face sites][S] component vectors of n numbers (16 bytes).
+struct FaceGeo {
+    int base[4];   // first vector of direction mu's faces, in units of S
+    int vf[4];     // face sites
+    int fs[4][4];  // strides of the other coordinates in the face-site index
+    int per_blk;   // vectors of one block, in units of S
+};
+
+// 16-byte component vectors
+template <typename Tc> struct V16;
+template <> struct V16<float> {
+    typedef float type __attribute__((ext_vector_type(4)));
+    static constexpr int n = 4;
+};
+template <> struct V16<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+    static constexpr int n = 2;
+};
+
+template <typename Tc> FaceGeo face_geo(const KGeo &g)
+{
+    FaceGeo f{};
+    int base = 0;
+    for (int mu = 0; mu < 4; ++mu) {
+        f.vf[mu] = g.Vb / g.b[mu];
+        f.base[mu] = base;
+        if (g.nb[mu] > 1) base += 2 * (12 / V16<Tc>::n) * f.vf[mu];
+        for (int nu = 0; nu < 4; ++nu)
+            f.fs[mu][nu] = nu < mu ? g.ostr[nu] : nu > mu ? g.ostr[nu] / g.b[mu] : 0;
+    }
+    f.per_blk = base;
+    return f;
+}
+
+// numbers of the face buffer for n_rhs right-hand sides
+template <typename Tc> size_t face_elems(const mrhs_op *op, int n_rhs)
+{
+    const size_t ngrp = (n_rhs + op->k.S - 1) / op->k.S;
+    return ngrp * op->k.nblk * face_geo<Tc>(op->k).per_blk * op->k.S * V16<Tc>::n;
+}
 
 template <typename Ts, typename Tc> struct SapArgs {
     KGeo g;
@@ -36,18 +84,20 @@ template <typename Ts, typename Tc> struct SapArgs {
     const Ts *b;
     const Ts *xr;           // where neighbours' x is read (x itself, or a snapshot)
     Ts *x;
-    // sigma = b - D_j x_j per block, kept between the visits of a colour (arithmetic type):
-    // the residual of a later visit is sigma - (hops across the block's faces)
+    // kept per block between the visits of a colour (arithmetic type, component vectors of 16
+    // bytes: SigIndex).  inc (no block has a neighbour of its own colour): the block residual rho
+    // after the last visit; a later visit's residual is rho minus the face hops of the change the
+    // other colour made in between, which the other colour left in `face`.  Otherwise
+    // sigma = b - D_j x_j, a later visit's residual being sigma - (face hops of x).
     Tc *sig;
-    int sig_in;             // this colour's sigma is valid (read it instead of forming b - D x)
-    int sig_out;            // write sigma for the next visit of this colour
-    // incremental residual (no block has a neighbour of its own colour): sig holds the block's
-    // residual rho after its last visit, ecor each block's last change of x; a later visit's
-    // residual is rho - (face hops of the neighbours' changes since then), the change the
-    // other colour made in between
+    int sig_in;             // this colour's rho or sigma is valid (read it instead of forming b - D x)
+    int sig_out;            // write it for the next visit of this colour
     int inc;
-    Tc *ecor;
-    int e_out;              // write this visit's change of x (a later visit reads it)
+    // inc: every block's outgoing hops across its faces, of its last change of x: per face site the
+    // two spin rows (1 -+ g_mu) U_mu applied to the change, which the neighbour adds to its residual
+    Tc *face;
+    FaceGeo fg;
+    int f_out;              // write this visit's faces (a later visit reads them)
     // even-odd block solver: A^-1 per site (clover layout), block offsets in parity order,
     // number of even sites of a block
     const Tc *cloverinv;
@@ -174,13 +224,348 @@ __device__ inline void block_hops(const KGeo &g, const Tc *__restrict__ links, c
     }
 }
 
+// a site's entry of a block set in component vectors of 16 bytes, [group][block][24 / n][Vb][S]:
+// what is kept between visits is read and written by this kernel alone, so it takes a layout of
+// its own with a quarter of the load and store instructions of the native one
+template <typename Tc>
+__device__ __forceinline__ typename V16<Tc>::type *sig_ptr(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt)
+{
+    using V = typename V16<Tc>::type;
+    V *base = reinterpret_cast<V *>(sig) + ((size_t)grp * g.nblk + blk) * (24 / V16<Tc>::n) * (size_t)(g.Vb * g.S);
+    return base + (uint32_t)(off * g.S + tt);
+}
+
+template <typename Tc>
+__device__ __forceinline__ void sig_load(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt, Spinor<Tc> &s)
+{
+    constexpr int n = V16<Tc>::n;
+    const typename V16<Tc>::type *p = sig_ptr(g, sig, grp, blk, off, tt);
+    const uint32_t str = (uint32_t)(g.Vb * g.S);
+#pragma unroll
+    for (int v = 0; v < 24 / n; ++v) {
+        const auto q = p[v * str];
+#pragma unroll
+        for (int c = 0; c < n; c += 2) {
+            s.re[(v * n + c) / 2] = q[c];
+            s.im[(v * n + c) / 2] = q[c + 1];
+        }
+    }
+}
+
+template <typename Tc>
+__device__ __forceinline__ void sig_store(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt, const Spinor<Tc> &s)
+{
+    constexpr int n = V16<Tc>::n;
+    typename V16<Tc>::type *p = sig_ptr(g, sig, grp, blk, off, tt);
+    const uint32_t str = (uint32_t)(g.Vb * g.S);
+#pragma unroll
+    for (int v = 0; v < 24 / n; ++v) {
+        typename V16<Tc>::type q;
+#pragma unroll
+        for (int c = 0; c < n; c += 2) {
+            q[c] = s.re[(v * n + c) / 2];
+            q[c + 1] = s.im[(v * n + c) / 2];
+        }
+        p[v * str] = q;
+    }
+}
+
+// two spin rows of three colours, complex
+template <typename Tc> struct HalfSpinor {
+    Tc re[2][3], im[2][3];
+};
+
+// first component vector of a site's entry on face `minus` of direction MU of block blk
+template <int MU, typename Ts, typename Tc>
+__device__ __forceinline__ typename V16<Tc>::type *face_ptr(const SapArgs<Ts, Tc> &a, int grp, int blk, bool minus, int f, int tt)
+{
+    using V = typename V16<Tc>::type;
+    const KGeo &g = a.g;
+    V *base = reinterpret_cast<V *>(a.face) + ((size_t)grp * g.nblk + blk) * (size_t)(a.fg.per_blk * g.S);
+    return base + (uint32_t)((a.fg.base[MU] + (minus ? (12 / V16<Tc>::n) * a.fg.vf[MU] : 0) + f) * g.S + tt);
+}
+
+template <int MU, typename Ts, typename Tc>
+__device__ __forceinline__ int face_index(const SapArgs<Ts, Tc> &a, uint32_t lcp)
+{
+    int f = 0;
+#pragma unroll
+    for (int nu = 0; nu < 4; ++nu)
+        if (nu != MU) f += unpack_coord(lcp, nu) * a.fg.fs[MU][nu];
+    return f;
+}
+
+// block across the +MU (minus: -MU) face of a block with block coordinate bc in direction MU
+template <int MU> __device__ __forceinline__ int face_nbr(const KGeo &g, int blk, int bc, bool minus)
+{
+    const int wrap = (g.nb[MU] - 1) * g.bstr[MU];
+    return minus ? blk + (bc > 0 ? -g.bstr[MU] : wrap) : blk + (bc + 1 < g.nb[MU] ? g.bstr[MU] : -wrap);
+}
+
+// What the neighbour across the +MU face (fwd) or the -MU face left for this site
+template <int MU, typename Ts, typename Tc>
+__device__ __forceinline__ void face_load(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp, int tt, bool fwd,
+                                 HalfSpinor<Tc> &w)
+{
+    constexpr int n = V16<Tc>::n;
+    const int bc = unpack_coord(bcp, MU);
+    // both neighbours are uniform over the workgroup, the choice is the lane's
+    const int nf = face_nbr<MU>(a.g, blk, bc, false), nb = face_nbr<MU>(a.g, blk, bc, true);
+    const typename V16<Tc>::type *p = face_ptr<MU>(a, grp, fwd ? nf : nb, fwd, face_index<MU>(a, lcp), tt);
+    const uint32_t str = (uint32_t)(a.fg.vf[MU] * a.g.S);
+#pragma unroll
+    for (int v = 0; v < 12 / n; ++v) {
+        const auto q = p[v * str];
+#pragma unroll
+        for (int c = 0; c < n; c += 2) {
+            const int k = (v * n + c) / 2;
+            w.re[k / 3][k % 3] = q[c];
+            w.im[k / 3][k % 3] = q[c + 1];
+        }
+    }
+}
+
+// r += the hop whose two upper spin rows are w: rows 2, 3 are sg g_MU's rows of it, sg = -1 for
+// the forward hop (1 - g_MU), +1 for the backward one
+template <int MU, typename Tc> __device__ __forceinline__ void face_add(const HalfSpinor<Tc> &w, Tc sg, Spinor<Tc> &r)
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        Tc t2r, t2i, t3r, t3i;
+        mul_ipow<gphase(MU, 2)>(w.re[gperm(MU, 2)][c], w.im[gperm(MU, 2)][c], t2r, t2i);
+        mul_ipow<gphase(MU, 3)>(w.re[gperm(MU, 3)][c], w.im[gperm(MU, 3)][c], t3r, t3i);
+        r.re[c] += w.re[0][c];
+        r.im[c] += w.im[0][c];
+        r.re[3 + c] += w.re[1][c];
+        r.im[3 + c] += w.im[1][c];
+        r.re[6 + c] += sg * t2r;
+        r.im[6 + c] += sg * t2i;
+        r.re[9 + c] += sg * t3r;
+        r.im[9 + c] += sg * t3i;
+    }
+}
+
+// r += the hops across the block's faces, from the neighbours' face entries.  A site lies on at
+// most one of the two faces of a direction unless its block is one site thick there (then the
+// backward face follows); the loads of ND directions are issued before their arithmetic.
+template <int MU0, int ND, typename Ts, typename Tc>
+__device__ __forceinline__ void face_round(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp, int tt,
+                                  Spinor<Tc> &r)
+{
+    const KGeo &g = a.g;
+    HalfSpinor<Tc> w[ND];
+    auto fwd = [&](int mu) __attribute__((always_inline)) { return unpack_coord(lcp, mu) + 1 == g.b[mu] && g.nb[mu] > 1; };
+    auto bwd = [&](int mu) __attribute__((always_inline)) { return unpack_coord(lcp, mu) == 0 && g.nb[mu] > 1; };
+    auto load = [&](auto m) __attribute__((always_inline)) {
+        constexpr int MU = MU0 + decltype(m)::value;
+        const bool ff = fwd(MU);
+        if (ff || bwd(MU)) face_load<MU>(a, grp, blk, bcp, lcp, tt, ff, w[MU - MU0]);
+    };
+    auto add = [&](auto m) __attribute__((always_inline)) {
+        constexpr int MU = MU0 + decltype(m)::value;
+        const bool ff = fwd(MU);
+        if (ff || bwd(MU)) face_add<MU>(w[MU - MU0], ff ? Tc(-1) : Tc(1), r);
+        if (g.b[MU] == 1 && g.nb[MU] > 1) {  // uniform: the site is on the backward face as well
+            HalfSpinor<Tc> v;
+            face_load<MU>(a, grp, blk, bcp, lcp, tt, false, v);
+            face_add<MU>(v, Tc(1), r);
+        }
+    };
+    load(std::integral_constant<int, 0>{});
+    load(std::integral_constant<int, 1>{});
+    if constexpr (ND == 4) {
+        load(std::integral_constant<int, 2>{});
+        load(std::integral_constant<int, 3>{});
+    }
+    sched_fence();
+    add(std::integral_constant<int, 0>{});
+    add(std::integral_constant<int, 1>{});
+    if constexpr (ND == 4) {
+        add(std::integral_constant<int, 2>{});
+        add(std::integral_constant<int, 3>{});
+    }
+}
+
+// residual of a visit that reads faces: r (the kept rho, or b) minus the face hops, which are summed
+// in the order of the full stencil
+template <typename Ts, typename Tc>
+__device__ __forceinline__ void face_residual(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp, int tt,
+                                     Spinor<Tc> &r)
+{
+    Spinor<Tc> f;
+    spinor_zero(f);
+    if constexpr (sizeof(Tc) == 4) {
+        face_round<0, 4>(a, grp, blk, bcp, lcp, tt, f);
+    } else {
+        face_round<0, 2>(a, grp, blk, bcp, lcp, tt, f);
+        face_round<2, 2>(a, grp, blk, bcp, lcp, tt, f);
+    }
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        r.re[c] -= f.re[c];
+        r.im[c] -= f.im[c];
+    }
+}
+
+// A site's outgoing hops across its faces, for the neighbours' next visits: on the +MU face the
+// neighbour's backward hop U^dag (1 + g_MU) e with the site's own link, on the -MU face the
+// neighbour's forward hop U (1 - g_MU) e with the neighbour's link.  The lane's face (fwd) selects
+// the element order and the sign of the link's imaginary part, so that lanes of both faces share
+// one pass.
+template <typename Tc> struct FaceLink {
+    typename Vec2<Tc>::type u[9];
+};
+
+template <int MU, typename Ts, typename Tc>
+__device__ __forceinline__ void face_link(const SapArgs<Ts, Tc> &a, int blk, int off, uint32_t bcp, bool fwd,
+                                          FaceLink<Tc> &l)
+{
+    using V2 = typename Vec2<Tc>::type;
+    const KGeo &g = a.g;
+    const int nb = face_nbr<MU>(g, blk, unpack_coord(bcp, MU), true);
+    const int ls = fwd ? blk * g.Vb + off : nb * g.Vb + off + (g.b[MU] - 1) * g.ostr[MU];
+    const V2 *U = reinterpret_cast<const V2 *>(a.links + ((size_t)(uint32_t)ls * 4 + MU) * 18);
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) l.u[3 * r + c] = U[r == c ? 4 * r : fwd ? 3 * c + r : 3 * r + c];
+}
+
+template <int MU, typename Tc>
+__device__ __forceinline__ void face_hop(const FaceLink<Tc> &l, bool fwd, const Spinor<Tc> &e, HalfSpinor<Tc> &w)
+{
+    const Tc sg = fwd ? Tc(1) : Tc(-1);
+    Tc hr[2][3], hi[2][3];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            Tc tr, ti;
+            if (r == 0) mul_ipow<gphase(MU, 0)>(e.re[3 * gperm(MU, 0) + c], e.im[3 * gperm(MU, 0) + c], tr, ti);
+            else mul_ipow<gphase(MU, 1)>(e.re[3 * gperm(MU, 1) + c], e.im[3 * gperm(MU, 1) + c], tr, ti);
+            hr[r][c] = e.re[3 * r + c] + sg * tr;
+            hi[r][c] = e.im[3 * r + c] + sg * ti;
+        }
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            Tc sr = 0, si = 0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const Tc ur = l.u[3 * x + c].x, ui = -sg * l.u[3 * x + c].y;
+                sr += ur * hr[r][c];
+                sr -= ui * hi[r][c];
+                si += ur * hi[r][c];
+                si += ui * hr[r][c];
+            }
+            w.re[r][x] = sr;
+            w.im[r][x] = si;
+        }
+}
+
+template <int MU, typename Ts, typename Tc>
+__device__ __forceinline__ void face_store(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t lcp, int tt, bool fwd,
+                                           const HalfSpinor<Tc> &w)
+{
+    constexpr int n = V16<Tc>::n;
+    typename V16<Tc>::type *p = face_ptr<MU>(a, grp, blk, !fwd, face_index<MU>(a, lcp), tt);
+    const uint32_t str = (uint32_t)(a.fg.vf[MU] * a.g.S);
+#pragma unroll
+    for (int v = 0; v < 12 / n; ++v) {
+        typename V16<Tc>::type q;
+#pragma unroll
+        for (int c = 0; c < n; c += 2) {
+            const int k = (v * n + c) / 2;
+            q[c] = w.re[k / 3][k % 3];
+            q[c + 1] = w.im[k / 3][k % 3];
+        }
+        p[v * str] = q;
+    }
+}
+
+// The end of a visit on one site: x (+)= e, and with the incremental residual the faces of the
+// change of the stored x (the correction as rounded to the storage type) and, kept, rho for later
+// visits (keep(): stores it).  A load waits for every store issued before it, so the loads come
+// first, in two rounds (the old x and the links of directions 0, 1; the links of 2, 3), and the
+// stores after the last of them.
+template <typename Ts, typename Tc, typename Keep>
+__device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, int blk, int off, uint32_t bcp,
+                                            uint32_t lcp, int tt, Spinor<Tc> &e, Keep keep)
+{
+    const KGeo &g = a.g;
+    sched_fence();
+    bool ff[4], on[4];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        const int l = unpack_coord(lcp, mu);
+        ff[mu] = l + 1 == g.b[mu];
+        on[mu] = a.f_out && g.nb[mu] > 1 && (ff[mu] || l == 0);
+    }
+    FaceLink<Tc> l0, l1;
+    HalfSpinor<Tc> w[2];
+    if (on[0]) face_link<0>(a, blk, off, bcp, ff[0], l0);
+    if (on[1]) face_link<1>(a, blk, off, bcp, ff[1], l1);
+    Spinor<Tc> xn;
+    if (a.mode == 2) {
+        Spinor<Tc> xo;
+        load_spinor<Tc>(g, a.x, grp, blk, off, tt, xo);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            xn.re[c] = xo.re[c] + e.re[c];
+            xn.im[c] = xo.im[c] + e.im[c];
+            Ts sr = store_as<Ts>(xn.re[c]), si = store_as<Ts>(xn.im[c]);
+            e.re[c] = load_as<Tc>(&sr) - xo.re[c];
+            e.im[c] = load_as<Tc>(&si) - xo.im[c];
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            xn.re[c] = e.re[c];
+            xn.im[c] = e.im[c];
+            Ts sr = store_as<Ts>(e.re[c]), si = store_as<Ts>(e.im[c]);
+            e.re[c] = load_as<Tc>(&sr);
+            e.im[c] = load_as<Tc>(&si);
+        }
+    }
+    sched_fence();
+    if (on[0]) face_hop<0>(l0, ff[0], e, w[0]);
+    if (on[1]) face_hop<1>(l1, ff[1], e, w[1]);
+    sched_fence();
+    if (on[2]) face_link<2>(a, blk, off, bcp, ff[2], l0);
+    if (on[3]) face_link<3>(a, blk, off, bcp, ff[3], l1);
+    sched_fence();
+    store_spinor(g, a.x, grp, blk, off, tt, xn);
+    if (a.sig_out && a.inc) keep();
+    if (on[0]) face_store<0>(a, grp, blk, lcp, tt, ff[0], w[0]);
+    if (on[1]) face_store<1>(a, grp, blk, lcp, tt, ff[1], w[1]);
+    sched_fence();
+    if (on[2]) face_hop<2>(l0, ff[2], e, w[0]);
+    if (on[2]) face_store<2>(a, grp, blk, lcp, tt, ff[2], w[0]);
+    if (on[3]) face_hop<3>(l1, ff[3], e, w[1]);
+    if (on[3]) face_store<3>(a, grp, blk, lcp, tt, ff[3], w[1]);
+    // a block one site thick: every site is on the -MU face as well
+    auto thin = [&](auto m) __attribute__((always_inline)) {
+        constexpr int MU = decltype(m)::value;
+        if (g.b[MU] == 1 && on[MU]) {
+            face_link<MU>(a, blk, off, bcp, false, l0);
+            face_hop<MU>(l0, false, e, w[0]);
+            face_store<MU>(a, grp, blk, lcp, tt, false, w[0]);
+        }
+    };
+    thin(std::integral_constant<int, 0>{});
+    thin(std::integral_constant<int, 1>{});
+    thin(std::integral_constant<int, 2>{});
+    thin(std::integral_constant<int, 3>{});
+}
+
 // words of LDS for the reduction scratch of a workgroup: [waves][T][3], rounded to 4
 __host__ __device__ inline int red_words(int threads, int T) { return ((threads / 64) * T * 3 + 3) / 4 * 4; }
 
 // One workgroup's share of a half-sweep: block blk, right-hand-side tile `tile`.  LL: the
 // block's links are staged in LDS (after rho and the reduction scratch) for the MR steps.
 template <typename Ts, typename Tc, int T, bool LL>
-__device__ inline void sap_block(const SapArgs<Ts, Tc> &a, int blk, int tile, unsigned char *smem)
+__device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int tile, unsigned char *smem)
 {
     using P2 = typename LdsPair<Tc>::type;
     const KGeo &g = a.g;
@@ -219,48 +604,42 @@ __device__ inline void sap_block(const SapArgs<Ts, Tc> &a, int blk, int tile, un
         }
     }
 
-    // 1. residual on the block: b - D x, or sigma - (face hops) once sigma is known
+    // 1. residual on the block: b - D x, or the kept rho or sigma minus the face hops
     const int colour = a.colour, mode = a.mode;
     const uint32_t *bcs = a.blk_coords;
+    const uint32_t bcp = bcs[blk];
     auto skip = [=](int nblk) { return mode == 1 && block_colour(g, bcs, nblk) == colour; };
-    // The face hops F of this visit (what the other blocks' x contribute) are what sigma for the
-    // next visit needs as well (sigma' = rho + F, step 4): where step 1 forms them on their own
-    // (a sigma visit, or the first visit of the second colour, where x vanishes on the block so
-    // that D x is F), they are kept in this site's sigma slot until step 4.
-    const bool keep_f = !a.inc && a.sig_out && (a.sig_in || a.mode == 1);
+    // Without inc, the face hops F of this visit (what the other blocks' x contribute) are what
+    // sigma for the next visit needs as well (sigma' = rho + F, step 4): where step 1 forms them on
+    // their own they are kept in this site's sigma slot until step 4.
+    const bool keep_f = !a.inc && a.sig_out && a.sig_in;
     if (active) {
         Spinor<Tc> r;
-        if (a.mode != 0) {
+        if (a.mode == 0) {
+            load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
+        } else if (a.inc && (a.sig_in || a.mode == 1)) {
+            // rho minus the other colour's change across the faces; the first visit of the second
+            // colour from zero (x vanishes on the block and the other colour's change is its x)
+            // likewise with b for rho
+            if (a.sig_in) sig_load(g, a.sig, grp, blk, off, tt, r);
+            else load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
+            face_residual(a, grp, blk, bcp, lcp, tt, r);
+        } else {
             Spinor<Tc> bb;
-            if constexpr (std::is_same<Ts, Tc>::value) {
-                // a visit that knows sigma, and the first visit of the second colour (x vanishes on
-                // the block, so D x is its face hops), through one call of the face hops
-                if (a.sig_in || a.mode == 1) {
-                    spinor_zero(r);
-                    const Tc *src = a.sig_in && a.inc ? (const Tc *)a.ecor : a.xr;
-                    face_hops_global<Tc>(g, a.links, src, grp, tt, blk, off, bc, lc, r, skip);
-                    load_spinor<Tc>(g, a.sig_in ? (const Tc *)a.sig : a.b, grp, blk, off, tt, bb);
-                } else {
-                    dirac_site_global<Tc>(g, a.links, a.clover, a.xr, grp, tt, blk, off, bc, lc, r, skip);
-                    load_spinor<Tc>(g, a.b, grp, blk, off, tt, bb);
-                }
-            } else if (a.sig_in) {
+            if (a.sig_in) {
                 spinor_zero(r);
-                if (a.inc) face_hops_global<Tc>(g, a.links, (const Tc *)a.ecor, grp, tt, blk, off, bc, lc, r, skip);
-                else face_hops_global<Tc>(g, a.links, a.xr, grp, tt, blk, off, bc, lc, r, skip);
-                load_spinor<Tc>(g, a.sig, grp, blk, off, tt, bb);
+                face_hops_global<Tc>(g, a.links, a.xr, grp, tt, blk, off, bc, lc, r, skip);
+                sig_load(g, a.sig, grp, blk, off, tt, bb);
+                if (keep_f) sig_store(g, a.sig, grp, blk, off, tt, r);
             } else {
                 dirac_site_global<Tc>(g, a.links, a.clover, a.xr, grp, tt, blk, off, bc, lc, r, skip);
                 load_spinor<Tc>(g, a.b, grp, blk, off, tt, bb);
             }
-            if (keep_f) store_spinor(g, a.sig, grp, blk, off, tt, r);
 #pragma unroll
             for (int c = 0; c < 12; ++c) {
                 r.re[c] = bb.re[c] - r.re[c];
                 r.im[c] = bb.im[c] - r.im[c];
             }
-        } else {
-            load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
         }
         lds_store<Tc>(rho, str, me, r);
     }
@@ -370,45 +749,20 @@ __device__ inline void sap_block(const SapArgs<Ts, Tc> &a, int blk, int tile, un
         }
     }
 
-    // 3. x|_j (+)= e; with the incremental residual also the change of the stored x (the
-    //    correction as rounded to the storage type)
-    if (active) {
-        Spinor<Tc> xo;
-        if (a.mode == 2) {
-            load_spinor<Tc>(g, a.x, grp, blk, off, tt, xo);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                e.re[c] += xo.re[c];
-                e.im[c] += xo.im[c];
-            }
-        }
-        store_spinor(g, a.x, grp, blk, off, tt, e);
-        if (a.e_out) {
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                Ts sr = store_as<Ts>(e.re[c]), si = store_as<Ts>(e.im[c]);
-                e.re[c] = load_as<Tc>(&sr);
-                e.im[c] = load_as<Tc>(&si);
-                if (a.mode == 2) {
-                    e.re[c] -= xo.re[c];
-                    e.im[c] -= xo.im[c];
-                }
-            }
-            store_spinor(g, a.ecor, grp, blk, off, tt, e);
-        }
-    }
+    // 3. x|_j (+)= e, and with the incremental residual rho and the faces for later visits
+    if (active)
+        finish_site(a, grp, blk, off, bcp, (uint32_t)opaque_index((int)lcp), tt, e, [&]() __attribute__((always_inline)) {
+            Spinor<Tc> rr;
+            lds_load<Tc>(rho, str, me, rr);
+            sig_store(g, a.sig, grp, blk, off, tt, rr);
+        });
     // 4. sigma for the next visit: b - D_j x_j(new) = rho (the block residual after the MR
     //    steps, this lane's own LDS slot) + the face hops, which this half-sweep leaves unchanged
     //    (kept from step 1, or formed again after a full residual)
-    if (active && a.sig_out && a.inc) {
-        // the incremental residual keeps rho itself
-        Spinor<Tc> rr;
-        lds_load<Tc>(rho, str, me, rr);
-        store_spinor(g, a.sig, grp, blk, off, tt, rr);
-    } else if (active && a.sig_out) {
+    if (active && a.sig_out && !a.inc) {
         Spinor<Tc> sg;
         if (keep_f) {
-            load_spinor<Tc>(g, a.sig, grp, blk, off, tt, sg);
+            sig_load(g, a.sig, grp, blk, off, tt, sg);
         } else if (a.mode != 0) {
             // the coordinates are decoded again rather than kept live through the MR steps
             int bc2[4], lc2[4];
@@ -427,7 +781,7 @@ __device__ inline void sap_block(const SapArgs<Ts, Tc> &a, int blk, int tile, un
                 sg.im[c] = o.y;
             }
         }
-        store_spinor(g, a.sig, grp, blk, off, tt, sg);
+        sig_store(g, a.sig, grp, blk, off, tt, sg);
     }
 }
 
@@ -455,15 +809,27 @@ __device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const typename LdsPair<
     hop_fence(h);
 }
 
+// The residual of one site, to LDS.  With inc a later visit starts from what the last one left:
+// the Schur residual rho on the even sites (kept in sig) and zero on the odd ones, whose
+// equations that visit's reconstruction solved.
 template <typename Ts, typename Tc, int T>
-__device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, typename LdsPair<Tc>::type *rho, int blk, int off, int grp,
+__device__ __forceinline__ void eo_residual(const SapArgs<Ts, Tc> &a, typename LdsPair<Tc>::type *rho, int blk, int off, int grp,
                                    int tt, int t)
 {
     const KGeo &g = a.g;
-    int bc[4], lc[4];
-    decode_site(g, a.blk_coords, a.loc_coords, blk, off, bc, lc);
     Spinor<Tc> r;
-    if (a.mode != 0) {
+    if (a.mode == 0) {
+        load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
+    } else if (a.inc && (a.sig_in || a.mode == 1)) {
+        const uint32_t bcp = a.blk_coords[blk], lcp = a.loc_coords[off];
+        const int odd = (unpack_coord(lcp, 0) + unpack_coord(lcp, 1) + unpack_coord(lcp, 2) + unpack_coord(lcp, 3)) & 1;
+        if (!a.sig_in) load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
+        else if (odd) spinor_zero(r);
+        else sig_load(g, a.sig, grp, blk, off, tt, r);
+        face_residual(a, grp, blk, bcp, lcp, tt, r);
+    } else {
+        int bc[4], lc[4];
+        decode_site(g, a.blk_coords, a.loc_coords, blk, off, bc, lc);
         const int colour = a.colour, mode = a.mode;
         const uint32_t *bcs = a.blk_coords;
         auto skip = [=](int nblk) { return mode == 1 && block_colour(g, bcs, nblk) == colour; };
@@ -475,29 +841,18 @@ __device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, typename LdsPair<Tc
             r.re[c] = bb.re[c] - r.re[c];
             r.im[c] = bb.im[c] - r.im[c];
         }
-    } else {
-        load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
     }
     lds_store<Tc>(rho, g.Vb * T, off * T + t, r);
 }
 
 template <typename Ts, typename Tc, int T>
-__device__ inline void eo_update_x(const SapArgs<Ts, Tc> &a, const typename LdsPair<Tc>::type *rho, int blk, int off,
+__device__ __forceinline__ void eo_update_x(const SapArgs<Ts, Tc> &a, const typename LdsPair<Tc>::type *rho, int blk, int off,
                                    int grp, int tt, int t)
 {
-    const KGeo &g = a.g;
     Spinor<Tc> e;
-    lds_load<Tc>(rho, g.Vb * T, off * T + t, e);
-    if (a.mode == 2) {
-        Spinor<Tc> xo;
-        load_spinor<Tc>(g, a.x, grp, blk, off, tt, xo);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            e.re[c] += xo.re[c];
-            e.im[c] += xo.im[c];
-        }
-    }
-    store_spinor(g, a.x, grp, blk, off, tt, e);
+    lds_load<Tc>(rho, a.g.Vb * T, off * T + t, e);
+    // (the Schur residual is kept in step 4)
+    finish_site(a, grp, blk, off, a.blk_coords[blk], a.loc_coords[off], tt, e, []() {});
 }
 
 // The even-odd block solver (DD-alpha-AMG's): with a block's sites split by the parity of
@@ -511,7 +866,7 @@ __device__ inline void eo_update_x(const SapArgs<Ts, Tc> &a, const typename LdsP
 // sites and -A_oo^-1 H_oe rho on the odd sites; the residual and the x update run in site
 // order (sites u and u + Vb / 2) for coalesced vector access and go through LDS.
 template <typename Ts, typename Tc, int T>
-__device__ inline void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile, unsigned char *smem)
+__device__ __forceinline__ void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile, unsigned char *smem)
 {
     using P2 = typename LdsPair<Tc>::type;
     const KGeo &g = a.g;
@@ -646,10 +1001,14 @@ __device__ inline void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile,
         }
     }
 
-    // 4. odd: e_o = A_oo^-1 r_o + A_oo^-1 H_oe (-e_e)
+    // 4. odd: e_o = A_oo^-1 r_o + A_oo^-1 H_oe (-e_e); with inc the Schur residual is kept first
     __syncthreads();
     if (active) {
         Spinor<Tc> m;
+        if (a.sig_out && a.inc) {
+            lds_load<Tc>(rho, str, me, m);
+            sig_store(g, a.sig, grp, blk, se, tt, m);
+        }
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             m.re[c] = -ee.re[c];
@@ -697,7 +1056,7 @@ template <typename Ts, typename Tc> struct SapBatch {
 };
 
 template <typename Ts, typename Tc, int T, bool LL>
-__global__ void __launch_bounds__(256 * T) k_sap_batched(SapBatch<Ts, Tc> B)
+__global__ void __launch_bounds__(256 * T, sizeof(Tc) == 4 ? 4 : 1) k_sap_batched(SapBatch<Ts, Tc> B)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int w = xcd_remap(blockIdx.x, B.first[B.n_inst]);
@@ -838,10 +1197,11 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
         }
         a.sig = (Tc *)wp;
         wp += align256(native_elems(op, n_rhs[k]) * sizeof(Tc));
-        a.ecor = nullptr;
+        a.face = nullptr;
+        a.fg = face_geo<Tc>(op->k);
         if (!op->odd_blocks) {
-            a.ecor = (Tc *)wp;
-            wp += align256(native_elems(op, n_rhs[k]) * sizeof(Tc));
+            a.face = (Tc *)wp;
+            wp += align256(face_elems<Tc>(op, n_rhs[k]) * sizeof(Tc));
         }
     }
     for (int s = 0; s < n_sap; ++s)
@@ -855,13 +1215,14 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
                 a.blocks = op->colour_blocks + (c == 0 ? 0 : op->n_colour[0]);
                 a.nblocks = op->n_colour[c];
                 a.mode = s == 0 && !guess ? c : 2;  // from zero, x vanishes on blocks not yet visited
-                // sigma carries a colour's residual from one visit to the next (plain MR only)
-                a.sig_in = !eo && s > 0;
-                a.sig_out = !eo && s + 1 < n_sap;
                 // the incremental residual where no block neighbours one of its own colour: every
-                // visit but the call's last one leaves its change of x for the other colour
-                a.inc = !eo && !op->odd_blocks;
-                a.e_out = a.inc && !(s + 1 == n_sap && c == 1);
+                // visit but the call's last one leaves the hops of its change of x for the other colour
+                a.inc = !op->odd_blocks;
+                a.f_out = a.inc && !(s + 1 == n_sap && c == 1);
+                // rho or sigma carries a colour's residual from one visit to the next (sigma with plain
+                // MR only)
+                a.sig_in = (a.inc || !eo) && s > 0;
+                a.sig_out = (a.inc || !eo) && s + 1 < n_sap;
                 a.xr = a.x;
                 if (a.mode == 2 && op->odd_blocks) {
                     C.src[C.n_inst] = a.x;
@@ -910,7 +1271,8 @@ size_t ws_bytes_sap_batched(const mrhs_op *const *ops, int n, const int32_t *n_r
         const size_t ne = native_elems(ops[k], n_rhs[k]);
         const size_t tc = ops[k]->prec == MRHS_PREC_F64 ? sizeof(double) : sizeof(float);
         if (ops[k]->odd_blocks) w += align256(ne * dtype_size(ops[k]->dtype));  // snapshot of x
-        else w += align256(ne * tc);                                             // changes of x
+        else if (tc == 8) w += align256(face_elems<double>(ops[k], n_rhs[k]) * tc);
+        else w += align256(face_elems<float>(ops[k], n_rhs[k]) * tc);
         w += align256(ne * tc);                                                  // sigma / rho
     }
     return w;
