@@ -64,7 +64,7 @@ size_t sap_lds_bytes(const mrhs_op *op, int T)
 {
     const size_t esz = op->prec == MRHS_PREC_F64 ? 8 : 4;
     const size_t threads = (op->k.Vb * T + 63) / 64 * 64;
-    return esz * (24 * (size_t)op->k.Vb * T + threads / 64 * T * 3);
+    return esz * (24 * (size_t)op->k.Vb * T + threads / 64 * T * 4);
 }
 
 // SAP and stencil tiles with FP64 arithmetic above 2 right-hand sides per site need more

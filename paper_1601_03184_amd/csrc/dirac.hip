@@ -103,8 +103,8 @@ __global__ void __launch_bounds__(RES_SITES * T) k_residual(KGeo g, const double
             den += bb.re[c] * bb.re[c] + bb.im[c] * bb.im[c];
         }
     }
-    num = wave_sum_stride(num, T);
-    den = wave_sum_stride(den, T);
+    num = wave_sum_mod<T>(num);
+    den = wave_sum_mod<T>(den);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane < T) {
         red[wave][lane][0] = num;

@@ -105,40 +105,123 @@ template <typename Ts, typename Tc> struct SapArgs {
     int Ve;
 };
 
-// The block residual rho lives in LDS as (re, im) pairs, [12][Vb][T]: lane (off, t)
-// reads component c at (c * Vb + off) * T + t, consecutive lanes consecutive pairs.
-template <typename Tc> struct LdsPair;
-template <> struct LdsPair<float> { using type = float2; };
-template <> struct LdsPair<double> { using type = double2; };
+// The block residual rho lives in LDS in component vectors of n numbers, [24 / n][Vb][T]: lane
+// (off, t) reads vector v at (v * Vb + off) * T + t, consecutive lanes consecutive vectors.  Plain
+// MR takes 16-byte vectors (half the LDS instructions and addresses of (re, im) pairs: 7.85 ->
+// 7.35 ms per half-sweep at 32^3 x 64, 32 right-hand sides, with the reduction of mr_alpha); the
+// even-odd kernel pairs, whose smaller load groups keep it within its registers.
+template <typename Tc> using LdsVec = typename V16<Tc>::type;
+template <typename Tc> using LdsPair = typename Vec2<Tc>::type;
 
-template <typename Tc>
-__device__ inline void lds_load(const typename LdsPair<Tc>::type *rho, int str, int idx, Spinor<Tc> &s)
+// complex component k of a vector
+template <typename LV, typename Tc> __device__ inline void vec_get(const LV &q, int k, Tc &re, Tc &im)
 {
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        const auto v = rho[c * str + idx];
-        s.re[c] = v.x;
-        s.im[c] = v.y;
+    if constexpr (std::is_same<LV, LdsPair<Tc>>::value) {
+        re = q.x;
+        im = q.y;
+    } else {
+        re = q[2 * k];
+        im = q[2 * k + 1];
     }
+}
+template <typename LV, typename Tc> __device__ inline void vec_set(LV &q, int k, Tc re, Tc im)
+{
+    if constexpr (std::is_same<LV, LdsPair<Tc>>::value) {
+        q = {re, im};
+    } else {
+        q[2 * k] = re;
+        q[2 * k + 1] = im;
+    }
+}
+
+// the components of s in the vectors [V0, V1)
+template <int V0, int V1, typename Tc, typename LV>
+__device__ inline void lds_load_range(const LV *rho, int str, int idx, Spinor<Tc> &s)
+{
+    constexpr int n = int(sizeof(LV) / sizeof(Tc)) / 2;  // complex components of a vector
+#pragma unroll
+    for (int v = V0; v < V1; ++v) {
+        const LV q = rho[v * str + idx];
+#pragma unroll
+        for (int c = 0; c < n; ++c) vec_get(q, c, s.re[v * n + c], s.im[v * n + c]);
+    }
+}
+
+template <typename Tc, typename LV> __device__ inline void lds_load(const LV *rho, int str, int idx, Spinor<Tc> &s)
+{
+    lds_load_range<0, 24 / int(sizeof(LV) / sizeof(Tc))>(rho, str, idx, s);
 }
 
 // components 6 HF .. 6 HF + 5 (one chiral half) only
-template <int HF, typename Tc>
-__device__ inline void lds_load_half(const typename LdsPair<Tc>::type *rho, int str, int idx, Spinor<Tc> &s)
+template <int HF, typename Tc, typename LV>
+__device__ inline void lds_load_half(const LV *rho, int str, int idx, Spinor<Tc> &s)
 {
+    constexpr int h = 12 / int(sizeof(LV) / sizeof(Tc));
+    lds_load_range<HF * h, (HF + 1) * h>(rho, str, idx, s);
+}
+
+template <typename Tc, typename LV> __device__ inline void lds_store(LV *rho, int str, int idx, const Spinor<Tc> &s)
+{
+    constexpr int n = int(sizeof(LV) / sizeof(Tc)) / 2;  // complex components of a vector
 #pragma unroll
-    for (int c = 6 * HF; c < 6 * HF + 6; ++c) {
-        const auto v = rho[c * str + idx];
-        s.re[c] = v.x;
-        s.im[c] = v.y;
+    for (int v = 0; v < 12 / n; ++v) {
+        LV q;
+#pragma unroll
+        for (int c = 0; c < n; ++c) vec_set(q, c, s.re[v * n + c], s.im[v * n + c]);
+        rho[v * str + idx] = q;
     }
 }
 
-template <typename Tc>
-__device__ inline void lds_store(typename LdsPair<Tc>::type *rho, int str, int idx, const Spinor<Tc> &s)
+// one MR update on this lane's slot: e += alpha rho, rho -= alpha q
+template <typename Tc, typename LV>
+__device__ inline void mr_update(LV *rho, int str, int idx, Tc ar, Tc ai, const Spinor<Tc> &q, Spinor<Tc> &e)
 {
+    constexpr int n = int(sizeof(LV) / sizeof(Tc)) / 2;  // complex components of a vector
 #pragma unroll
-    for (int c = 0; c < 12; ++c) rho[c * str + idx] = {s.re[c], s.im[c]};
+    for (int v = 0; v < 12 / n; ++v) {
+        const LV o = rho[v * str + idx];
+        LV w;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const int c = v * n + k;
+            Tc nr, ni;
+            vec_get(o, k, nr, ni);
+            e.re[c] += ar * nr;
+            e.re[c] -= ai * ni;
+            e.im[c] += ar * ni;
+            e.im[c] += ai * nr;
+            nr -= ar * q.re[c];
+            nr += ai * q.im[c];
+            ni -= ar * q.im[c];
+            ni -= ai * q.re[c];
+            vec_set(w, k, nr, ni);
+        }
+        rho[v * str + idx] = w;
+    }
+}
+
+// this lane's share of <q,q> and <q,rho>
+template <typename Tc, typename LV>
+__device__ inline void mr_products(const LV *rho, int str, int idx, const Spinor<Tc> &q, Tc &qq, Tc &qrr,
+                                            Tc &qri)
+{
+    constexpr int n = int(sizeof(LV) / sizeof(Tc)) / 2;  // complex components of a vector
+#pragma unroll
+    for (int v = 0; v < 12 / n; ++v) {
+        const LV o = rho[v * str + idx];
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const int c = v * n + k;
+            Tc pr, pi;
+            vec_get(o, k, pr, pi);
+            qq += q.re[c] * q.re[c];
+            qq += q.im[c] * q.im[c];
+            qrr += q.re[c] * pr;
+            qrr += q.im[c] * pi;
+            qri += q.re[c] * pi;
+            qri -= q.im[c] * pr;
+        }
+    }
 }
 
 // The links a block operator uses, staged in LDS once per workgroup (the "links in LDS"
@@ -186,8 +269,8 @@ template <typename Tf, typename T> __device__ inline void lds_link(const Tf *ul,
 // ns is the site's native index (opaque to the compiler, so the link loads stay inside
 // the MR loop).  With ul (links in LDS) the links come from there: cf is the site's index
 // in direction MU's box, sb the box's stride in MU.
-template <int MU, typename Tc, bool LL = false>
-__device__ inline void block_hops(const KGeo &g, const Tc *__restrict__ links, const typename LdsPair<Tc>::type *rho,
+template <int MU, typename Tc, bool LL = false, typename LV>
+__device__ inline void block_hops(const KGeo &g, const Tc *__restrict__ links, const LV *rho,
                                   int T, int ns, int off, int t, uint32_t lcp, Spinor<Tc> &q,
                                   const Tc *ul = nullptr, int cf = 0, int sb = 0)
 {
@@ -559,19 +642,44 @@ __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, i
     thin(std::integral_constant<int, 3>{});
 }
 
-// words of LDS for the reduction scratch of a workgroup: [waves][T][3], rounded to 4
-__host__ __device__ inline int red_words(int threads, int T) { return ((threads / 64) * T * 3 + 3) / 4 * 4; }
+// numbers of LDS for the reduction scratch of a workgroup: [waves][T][4]
+__host__ __device__ inline int red_words(int threads, int T) { return threads / 64 * T * 4; }
+
+// alpha = <q,rho> / <q,q> (0 where q vanishes) per right-hand side lane of the workgroup, from every
+// lane's partial sums: each wavefront's sums go to LDS, and after the barrier every wavefront
+// reads all of them at once, one (wavefront, right-hand side) entry per lane (at most
+// 256 T / 64 x T <= 64 entries), and sums them across its lanes.
+template <int T, typename Tc>
+__device__ __forceinline__ void mr_alpha(Tc qq, Tc qrr, Tc qri, Tc *red, Tc &ar, Tc &ai)
+{
+    struct alignas(16) Entry {
+        Tc v[4];
+    };
+    Entry *r = reinterpret_cast<Entry *>(red);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = blockDim.x / 64 * T;
+    qq = wave_sum_mod<T>(qq);
+    qrr = wave_sum_mod<T>(qrr);
+    qri = wave_sum_mod<T>(qri);
+    if (lane < T) r[wave * T + lane] = {{qq, qrr, qri, Tc(0)}};
+    __syncthreads();
+    const Entry x = r[lane < n ? lane : 0];
+    const Tc sqq = wave_sum_mod<T>(lane < n ? x.v[0] : Tc(0));
+    const Tc sr = wave_sum_mod<T>(lane < n ? x.v[1] : Tc(0));
+    const Tc si = wave_sum_mod<T>(lane < n ? x.v[2] : Tc(0));
+    ar = sqq > Tc(0) ? sr / sqq : Tc(0);
+    ai = sqq > Tc(0) ? si / sqq : Tc(0);
+}
 
 // One workgroup's share of a half-sweep: block blk, right-hand-side tile `tile`.  LL: the
 // block's links are staged in LDS (after rho and the reduction scratch) for the MR steps.
 template <typename Ts, typename Tc, int T, bool LL>
 __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int tile, unsigned char *smem)
 {
-    using P2 = typename LdsPair<Tc>::type;
+    using LV = LdsVec<Tc>;
     const KGeo &g = a.g;
-    P2 *rho = reinterpret_cast<P2 *>(smem);
+    LV *rho = reinterpret_cast<LV *>(smem);
     const int str = g.Vb * T;
-    Tc *red_s = reinterpret_cast<Tc *>(rho + 12 * str);  // [waves][T][3]
+    Tc *red_s = reinterpret_cast<Tc *>(rho + 24 / V16<Tc>::n * str);  // [waves][T][4]
     Tc *ul = red_s + red_words(blockDim.x, T);  // used only with LL
 
     const int off = threadIdx.x / T, t = threadIdx.x % T;
@@ -647,7 +755,7 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
     // 2. minimal residual on the block operator
     Spinor<Tc> e;
     spinor_zero(e);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+    const int wave = threadIdx.x >> 6;
     for (int it = 0; it < a.n_mr; ++it) {
         __syncthreads();
         Spinor<Tc> q;
@@ -701,52 +809,13 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
                 clover_term(std::false_type{});
                 hops();
             }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const P2 o = rho[c * str + me];
-                qq += q.re[c] * q.re[c];
-                qq += q.im[c] * q.im[c];
-                qrr += q.re[c] * o.x;
-                qrr += q.im[c] * o.y;
-                qri += q.re[c] * o.y;
-                qri -= q.im[c] * o.x;
-            }
+            mr_products(rho, str, me, q, qq, qrr, qri);
         } else {
             spinor_zero(q);
         }
-        qq = wave_sum_stride(qq, T);
-        qrr = wave_sum_stride(qrr, T);
-        qri = wave_sum_stride(qri, T);
-        if (lane < T) {
-            red_s[(wave * T + lane) * 3 + 0] = qq;
-            red_s[(wave * T + lane) * 3 + 1] = qrr;
-            red_s[(wave * T + lane) * 3 + 2] = qri;
-        }
-        __syncthreads();
-        Tc sqq = 0, sr = 0, si = 0;
-        for (int w = 0; w < nwaves; ++w) {
-            sqq += red_s[(w * T + t) * 3 + 0];
-            sr += red_s[(w * T + t) * 3 + 1];
-            si += red_s[(w * T + t) * 3 + 2];
-        }
-        const Tc ar = sqq > Tc(0) ? sr / sqq : Tc(0);
-        const Tc ai = sqq > Tc(0) ? si / sqq : Tc(0);
-        if (active) {
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const P2 o = rho[c * str + me];
-                e.re[c] += ar * o.x;
-                e.re[c] -= ai * o.y;
-                e.im[c] += ar * o.y;
-                e.im[c] += ai * o.x;
-                Tc nr = o.x, ni = o.y;
-                nr -= ar * q.re[c];
-                nr += ai * q.im[c];
-                ni -= ar * q.im[c];
-                ni -= ai * q.re[c];
-                rho[c * str + me] = {nr, ni};
-            }
-        }
+        Tc ar, ai;
+        mr_alpha<T>(qq, qrr, qri, red_s, ar, ai);
+        if (active) mr_update(rho, str, me, ar, ai, q, e);
     }
 
     // 3. x|_j (+)= e, and with the incremental residual rho and the faces for later visits
@@ -770,16 +839,12 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
             spinor_zero(sg);
             face_hops_global<Tc>(g, a.links, a.xr, grp, tt, blk, off, bc2, lc2, sg, skip);
         }
+        Spinor<Tc> rr;
+        lds_load<Tc>(rho, str, me, rr);
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            const P2 o = rho[c * str + me];
-            if (a.mode != 0) {
-                sg.re[c] += o.x;
-                sg.im[c] += o.y;
-            } else {
-                sg.re[c] = o.x;
-                sg.im[c] = o.y;
-            }
+            sg.re[c] = a.mode != 0 ? sg.re[c] + rr.re[c] : rr.re[c];
+            sg.im[c] = a.mode != 0 ? sg.im[c] + rr.im[c] : rr.im[c];
         }
         sig_store(g, a.sig, grp, blk, off, tt, sg);
     }
@@ -795,11 +860,11 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
 // holds -A_oo^-1 H_oe rho for the step in progress, so that the even sites' hops add
 // -H_eo A_oo^-1 H_oe rho to A_ee rho directly.
 template <typename Ts, typename Tc, int T>
-__device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const typename LdsPair<Tc>::type *rho, int ns, int off, int t,
+__device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int ns, int off, int t,
                                uint32_t lc, Spinor<Tc> &h)
 {
     const KGeo &g = a.g;
-    block_hops<0>(g, a.links, rho, T, ns, off, t, lc, h);
+    block_hops<0, Tc>(g, a.links, rho, T, ns, off, t, lc, h);
     hop_fence(h);
     block_hops<1>(g, a.links, rho, T, ns, off, t, lc, h);
     hop_fence(h);
@@ -813,7 +878,7 @@ __device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const typename LdsPair<
 // the Schur residual rho on the even sites (kept in sig) and zero on the odd ones, whose
 // equations that visit's reconstruction solved.
 template <typename Ts, typename Tc, int T>
-__device__ __forceinline__ void eo_residual(const SapArgs<Ts, Tc> &a, typename LdsPair<Tc>::type *rho, int blk, int off, int grp,
+__device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, LdsPair<Tc> *rho, int blk, int off, int grp,
                                    int tt, int t)
 {
     const KGeo &g = a.g;
@@ -823,9 +888,12 @@ __device__ __forceinline__ void eo_residual(const SapArgs<Ts, Tc> &a, typename L
     } else if (a.inc && (a.sig_in || a.mode == 1)) {
         const uint32_t bcp = a.blk_coords[blk], lcp = a.loc_coords[off];
         const int odd = (unpack_coord(lcp, 0) + unpack_coord(lcp, 1) + unpack_coord(lcp, 2) + unpack_coord(lcp, 3)) & 1;
-        if (!a.sig_in) load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
-        else if (odd) spinor_zero(r);
-        else sig_load(g, a.sig, grp, blk, off, tt, r);
+        if (a.sig_in) {
+            spinor_zero(r);
+            if (!odd) sig_load(g, a.sig, grp, blk, off, tt, r);
+        } else {
+            load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
+        }
         face_residual(a, grp, blk, bcp, lcp, tt, r);
     } else {
         int bc[4], lc[4];
@@ -846,7 +914,7 @@ __device__ __forceinline__ void eo_residual(const SapArgs<Ts, Tc> &a, typename L
 }
 
 template <typename Ts, typename Tc, int T>
-__device__ __forceinline__ void eo_update_x(const SapArgs<Ts, Tc> &a, const typename LdsPair<Tc>::type *rho, int blk, int off,
+__device__ inline void eo_update_x(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int blk, int off,
                                    int grp, int tt, int t)
 {
     Spinor<Tc> e;
@@ -866,13 +934,13 @@ __device__ __forceinline__ void eo_update_x(const SapArgs<Ts, Tc> &a, const type
 // sites and -A_oo^-1 H_oe rho on the odd sites; the residual and the x update run in site
 // order (sites u and u + Vb / 2) for coalesced vector access and go through LDS.
 template <typename Ts, typename Tc, int T>
-__device__ __forceinline__ void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile, unsigned char *smem)
+__device__ inline void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile, unsigned char *smem)
 {
-    using P2 = typename LdsPair<Tc>::type;
+    using LV = LdsPair<Tc>;
     const KGeo &g = a.g;
-    P2 *rho = reinterpret_cast<P2 *>(smem);
+    LV *rho = reinterpret_cast<LV *>(smem);
     const int str = g.Vb * T;
-    Tc *red_s = reinterpret_cast<Tc *>(rho + 12 * str);  // [waves][T][3]
+    Tc *red_s = reinterpret_cast<Tc *>(rho + 12 * str);  // [waves][T][4]
 
     const int u = threadIdx.x / T, t = threadIdx.x % T, Ve = a.Ve;
     const bool active = u < Ve;
@@ -914,7 +982,6 @@ __device__ __forceinline__ void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, 
     }
 
     // 3. minimal residual on S over the even sites
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
     for (int it = 0; it < a.n_mr; ++it) {
         __syncthreads();
         if (active) {
@@ -953,40 +1020,16 @@ __device__ __forceinline__ void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, 
             }
             hop_fence(q);
             eo_hops<Ts, Tc, T>(a, rho, ns, se, t, lce, q);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const P2 o = rho[c * str + me];
-                qq += q.re[c] * q.re[c];
-                qq += q.im[c] * q.im[c];
-                qrr += q.re[c] * o.x;
-                qrr += q.im[c] * o.y;
-                qri += q.re[c] * o.y;
-                qri -= q.im[c] * o.x;
-            }
+            mr_products(rho, str, me, q, qq, qrr, qri);
         } else {
             spinor_zero(q);
         }
-        qq = wave_sum_stride(qq, T);
-        qrr = wave_sum_stride(qrr, T);
-        qri = wave_sum_stride(qri, T);
-        if (lane < T) {
-            red_s[(wave * T + lane) * 3 + 0] = qq;
-            red_s[(wave * T + lane) * 3 + 1] = qrr;
-            red_s[(wave * T + lane) * 3 + 2] = qri;
-        }
-        __syncthreads();
-        Tc sqq = 0, sr = 0, si = 0;
-        for (int w = 0; w < nwaves; ++w) {
-            sqq += red_s[(w * T + t) * 3 + 0];
-            sr += red_s[(w * T + t) * 3 + 1];
-            si += red_s[(w * T + t) * 3 + 2];
-        }
-        const Tc ar = sqq > Tc(0) ? sr / sqq : Tc(0);
-        const Tc ai = sqq > Tc(0) ? si / sqq : Tc(0);
+        Tc ar, ai;
+        mr_alpha<T>(qq, qrr, qri, red_s, ar, ai);
         if (active) {
 #pragma unroll
             for (int c = 0; c < 12; ++c) {
-                const P2 o = rho[c * str + me];
+                const auto o = rho[c * str + me];
                 ee.re[c] += ar * o.x;
                 ee.re[c] -= ai * o.y;
                 ee.im[c] += ar * o.y;

@@ -226,9 +226,59 @@ struct NoSkip {
     __device__ bool operator()(int) const { return false; }
 };
 
-template <typename T> __device__ inline T wave_sum_stride(T v, int T_)
+// One 32-bit word of v from the lane whose index differs in bit log2(O) (O = 1, 2, 4, 8; with 4 and 8 a
+// rotation of the row of 16 lanes, which is that exchange once v is the same in lanes 8 apart)
+template <int O> __device__ inline int dpp_xor(int v)
 {
-    // sum over the lanes of a wave that agree modulo T_ (T_ a power of two <= 32)
-    for (int o = 32; o >= T_; o >>= 1) v += __shfl_xor(v, o, 64);
+    constexpr int ctrl = O == 1 ? 0xB1 : O == 2 ? 0x4E : 0x120 + O;  // quad_perm, row_ror
+    return __builtin_amdgcn_mov_dpp(v, ctrl, 0xf, 0xf, false);
+}
+
+template <int O> __device__ inline float lane_xor_sum(float v)
+{
+    if constexpr (O >= 16) {
+        // both halves of the exchange in one instruction: r[0] holds the lower lanes' values in
+        // every lane, r[1] the upper lanes'
+        const unsigned u = __float_as_uint(v);
+        if constexpr (O == 32) {
+            const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+            return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        } else {
+            const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+            return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+    } else {
+        return v + __int_as_float(dpp_xor<O>(__float_as_int(v)));
+    }
+}
+
+template <int O> __device__ inline double lane_xor_sum(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    if constexpr (O >= 16) {
+        if constexpr (O == 32) {
+            const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+            return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+        } else {
+            const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+            return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+        }
+    } else {
+        return v + __hiloint2double(dpp_xor<O>((int)hi), dpp_xor<O>((int)lo));
+    }
+}
+
+// sum over the lanes of a wave that agree modulo T (a power of two <= 8), the same value in all of
+// them; every lane must be active.  Lane exchanges on the vector unit instead of through LDS.
+template <int T, typename Tv> __device__ inline Tv wave_sum_mod(Tv v)
+{
+    v = lane_xor_sum<32>(v);
+    v = lane_xor_sum<16>(v);
+    if constexpr (T <= 8) v = lane_xor_sum<8>(v);
+    if constexpr (T <= 4) v = lane_xor_sum<4>(v);
+    if constexpr (T <= 2) v = lane_xor_sum<2>(v);
+    if constexpr (T <= 1) v = lane_xor_sum<1>(v);
     return v;
 }
