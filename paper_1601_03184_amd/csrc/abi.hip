@@ -234,7 +234,17 @@ int mrhs_op_create(const mrhs_geom *geom, const double *links, double m0, double
     if (!rc) rc = hip_check(hipMemcpyAsync(op->agg_sites, asites.data(), sizeof(int32_t) * asites.size(), hipMemcpyHostToDevice, st), "copy");
     if (!rc) rc = launch_build_fields(op, links, m0, csw, st);
     if (!rc) rc = hip_check(hipStreamSynchronize(st), "hipStreamSynchronize(op_create)");
-    op->sap_tile = pick_tile(op, prec == MRHS_PREC_F64 ? 1 : 2, true);
+    // SAP tile until mrhs_set_tiles or the autotuner choose one.  A larger tile shares the field loads
+    // and fills the wavefronts of small blocks, a smaller one gives short lattices more
+    // workgroups; it depends on the lattice alone, so that a right-hand side's result does not
+    // depend on how many others share the call.  Measured (3 x 4, us, tiles 1 / 2 / 4): FP32
+    // 24^3 x 48 n 24 18392 / 12351 / 9966, 16^4 n 20 1587 / 1093 / 1036 but n 3 333 / 254 / 293, 8^4 n 8
+    // 210 / 215 / 264; blocks of 16 sites 16^4 n 24 3470 / 1924 / 1024, 4^4 n 8 182 / 184 / 168;
+    // FP64 12^3 x 24 n 10 1349 / 1024, 8^4 n 8 278 / 322.  The even-odd solver is fastest at 2
+    // (24^3 x 48 n 24: 21573 / 14125 / 15246) and takes no more unless asked to.
+    op->sap_tile_auto = true;
+    if (prec == MRHS_PREC_F64) op->sap_tile = pick_tile(op, k.nblk >= 128 || k.Vb <= 64 ? 2 : 1, true);
+    else op->sap_tile = pick_tile(op, k.nblk >= 512 || k.Vb <= 64 ? 4 : 2, true);
     op->dirac_tile = pick_tile(op, prec == MRHS_PREC_F64 ? 1 : 4, false);
     if (rc) {
         free_op(op);
@@ -629,6 +639,7 @@ int mrhs_set_tiles(mrhs_op *op, int32_t sap_tile, int32_t dirac_tile)
         if (!tile_built(op, sap_tile))
             return set_error(MRHS_EUNSUPPORTED, "SAP tiles above 2 are not built for FP64 arithmetic");
         op->sap_tile = sap_tile;
+        op->sap_tile_auto = false;
     }
     if (dirac_tile) {
         if (!ok(dirac_tile) || op->k.S % dirac_tile || op->k.Vb * dirac_tile > 1024)

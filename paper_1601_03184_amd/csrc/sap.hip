@@ -1190,7 +1190,7 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
     size_t max_lds = ops[0]->max_lds;
     const bool eo = ops[0]->block_solver == MRHS_BLOCK_EO_MR;
     for (int k = 0; k < n; ++k) {
-        T = std::min(T, ops[k]->sap_tile);
+        T = std::min(T, eo && ops[k]->sap_tile_auto ? std::min(2, ops[k]->sap_tile) : ops[k]->sap_tile);
         maxVb = std::max(maxVb, ops[k]->k.Vb);
         if ((ops[k]->block_solver == MRHS_BLOCK_EO_MR) != eo)
             return set_error(MRHS_EINVAL, "the operators of a batch use different block solvers");
