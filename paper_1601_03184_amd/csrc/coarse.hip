@@ -30,7 +30,12 @@ constexpr int MAXVA = 256;
 constexpr int MAXFACE = 64;  // face sites of an aggregate whose neighbours the table holds
 constexpr int MAXN = 32;     // test vectors
 constexpr int QST = MAXN + 1, WST = 2 * MAXN + 1;  // LDS row strides (pairs) of rows and columns
-constexpr int RMAX = (CHS * 12 + NTHR / MAXN - 1) / (NTHR / MAXN);  // rows per thread and chunk
+// The threads of a chunk come in units of 32 lanes: 4 neighbouring test vectors (one group of the
+// layout at S = 4) x CHS sites, so that a load of one component covers 16 CHS bytes in one run.  Unit u
+// has group u % 8; with u / 8 it takes one spin half of the columns and every other component
+// of the rows.
+constexpr int RMAX = 12 * (MAXN / 4) / (NTHR / 32);  // rows per thread and chunk
+static_assert(CHS == 8 && NTHR == 16 * 32 && MAXN == 32, "units of 4 vectors x 8 sites");
 
 template <typename Tq> struct CoarseArgs {
     KGeo g;
@@ -72,37 +77,61 @@ __device__ inline SiteRef site_ref(const CoarseArgs<Tq> &a, int i, int ls)
     return r;
 }
 
-// spin half HP of column k' of P at a site: q_k' masked to that half (the half is a template
+// Spin half HP of column k' of P at a site (six complex components of q_k'; the half is a template
 // parameter so that the masked spinor stays in registers); qk points at q_k's group and lane
+template <typename Tc> struct Half {
+    Tc re[6], im[6];
+};
+
 template <int HP, typename Tc, typename Tq>
-__device__ inline void load_half(const Tq *__restrict__ qk, uint32_t vo, uint32_t cs, Spinor<Tc> &s)
+__device__ inline void load_half6(const Tq *__restrict__ qk, uint32_t vo, uint32_t cs, Half<Tc> &s)
 {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        if (c / 6 == HP) {
-            s.re[c] = load_as<Tc>(qk + vo + (2 * c) * cs);
-            s.im[c] = load_as<Tc>(qk + vo + (2 * c + 1) * cs);
-        } else {
-            s.re[c] = s.im[c] = Tc(0);
-        }
+    for (int c = 0; c < 6; ++c) {
+        s.re[c] = load_as<Tc>(qk + vo + (2 * (6 * HP + c)) * cs);
+        s.im[c] = load_as<Tc>(qk + vo + (2 * (6 * HP + c) + 1) * cs);
     }
 }
 
-// w += the forward hop in direction MU when the neighbour x + mu lies in the same aggregate
-template <int MU, int HP, typename Tc, typename Tq>
-__device__ inline void inside_fwd_hop(const CoarseArgs<Tq> &a, const Tc *__restrict__ links, const SiteRef *tab,
-                                      const SiteRef &me, int ls, const Tq *qk, uint32_t cs, Spinor<Tc> &w)
+template <int HP, typename Tc> __device__ inline void expand_half(const Half<Tc> &h, Spinor<Tc> &s)
 {
-    const int l = unpack_coord(me.lc, MU);
-    if (l + 1 < a.a[MU]) {
-        const SiteRef n = tab[ls + a.astr[MU]];
-        Spinor<Tc> chi;
-        load_half<HP, Tc>(qk, n.vo, cs, chi);
-        Tc U[18];
-        load_link(links, a.g.V, MU, me.ns, U);
-        hop_accumulate<MU, -1, false>(U, chi, w);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        s.re[c] = c / 6 == HP ? h.re[c % 6] : Tc(0);
+        s.im[c] = c / 6 == HP ? h.im[c % 6] : Tc(0);
     }
-    hop_fence(w);
+}
+
+// the neighbour x + mu inside the aggregate (the site itself where it lies outside)
+template <int MU, typename Tq>
+__device__ inline bool inside_nbr(const CoarseArgs<Tq> &a, const SiteRef *tab, uint32_t lc, int ls, uint32_t &vo)
+{
+    const bool in = unpack_coord(lc, MU) + 1 < a.a[MU];
+    vo = tab[in ? ls + a.astr[MU] : ls].vo;
+    return in;
+}
+
+// w += the forward hop in direction MU from the neighbour's half chi; the link from LDS (ul: the
+// links of the chunk's site) or from the operator's field
+template <int MU, int HP, typename Tc>
+__device__ inline void inside_fwd_hop(const Tc *__restrict__ links, const Tc *ul, int ns, const Half<Tc> &chi,
+                                      Spinor<Tc> &w)
+{
+    Tc U[18];
+    if constexpr (sizeof(Tc) == 4) {
+        const float2 *p = reinterpret_cast<const float2 *>(ul + 18 * MU);
+#pragma unroll
+        for (int c = 0; c < 9; ++c) {
+            const float2 v = p[c];
+            U[2 * c] = v.x;
+            U[2 * c + 1] = v.y;
+        }
+    } else {
+        load_link(links, 0L, MU, ns, U);
+    }
+    Spinor<Tc> s;
+    expand_half<HP>(chi, s);
+    hop_accumulate<MU, -1, false>(U, s, w);
 }
 
 // local site of the f-th site on the +mu face of an aggregate (local coordinate mu = a_mu - 1)
@@ -118,17 +147,25 @@ __device__ inline int face_site(const int (&a)[4], const int (&astr)[4], int mu,
 // block is G + sigma3 G^dag sigma3 (g5 P = P sigma3).
 template <int HP, typename Tc, typename Tq>
 __device__ inline void self_column(const CoarseArgs<Tq> &a, const Tc *__restrict__ links, const Tc *__restrict__ clover,
-                                   const SiteRef *tab, int ls, const Tq *qk, uint32_t cs, Spinor<Tc> &w)
+                                   const Tc *ul, const SiteRef *tab, int ls, const Tq *qk, uint32_t cs, Spinor<Tc> &w)
 {
     const SiteRef me = tab[ls];
-    Spinor<Tc> p;
-    load_half<HP, Tc>(qk, me.vo, cs, p);
+    uint32_t v0, v1, v2, v3;
+    const bool in0 = inside_nbr<0>(a, tab, me.lc, ls, v0), in1 = inside_nbr<1>(a, tab, me.lc, ls, v1);
+    const bool in2 = inside_nbr<2>(a, tab, me.lc, ls, v2), in3 = inside_nbr<3>(a, tab, me.lc, ls, v3);
+    // the loads of the next hop are issued before the arithmetic of the current one
+    Half<Tc> p, c0, c1;
+    Tc A[36];
+    load_half6<HP>(qk, me.vo, cs, p);
+    load_clover_half<HP>(clover, a.g.V, me.ns, A);
+    load_half6<HP>(qk, v0, cs, c0);
+    sched_fence();
     // the site term is block-diagonal in the spin halves: only half HP is non-zero
     spinor_zero(w);
     {
-        Tc A[36];
-        load_clover_half<HP>(clover, a.g.V, me.ns, A);
-        clover_half<HP>(A, p, w);
+        Spinor<Tc> s;
+        expand_half<HP>(p, s);
+        clover_half<HP>(A, s, w);
     }
 #pragma unroll
     for (int c = 6 * HP; c < 6 * HP + 6; ++c) {
@@ -136,10 +173,20 @@ __device__ inline void self_column(const CoarseArgs<Tq> &a, const Tc *__restrict
         w.im[c] *= Tc(0.5);
     }
     hop_fence(w);
-    inside_fwd_hop<0, HP>(a, links, tab, me, ls, qk, cs, w);
-    inside_fwd_hop<1, HP>(a, links, tab, me, ls, qk, cs, w);
-    inside_fwd_hop<2, HP>(a, links, tab, me, ls, qk, cs, w);
-    inside_fwd_hop<3, HP>(a, links, tab, me, ls, qk, cs, w);
+    load_half6<HP>(qk, v1, cs, c1);
+    sched_fence();
+    if (in0) inside_fwd_hop<0, HP>(links, ul, me.ns, c0, w);
+    hop_fence(w);
+    load_half6<HP>(qk, v2, cs, c0);
+    sched_fence();
+    if (in1) inside_fwd_hop<1, HP>(links, ul, me.ns, c1, w);
+    hop_fence(w);
+    load_half6<HP>(qk, v3, cs, c1);
+    sched_fence();
+    if (in2) inside_fwd_hop<2, HP>(links, ul, me.ns, c0, w);
+    hop_fence(w);
+    if (in3) inside_fwd_hop<3, HP>(links, ul, me.ns, c1, w);
+    hop_fence(w);
 }
 
 // column (HP, k') of the +MU face part at face site f: (1 - g_mu) W_mu P_c(x + mu), the
@@ -148,20 +195,23 @@ template <int MU, int HP, typename Tc, typename Tq>
 __device__ inline void face_column(const CoarseArgs<Tq> &a, const Tc *__restrict__ links, const SiteRef &me,
                                    const SiteRef &nb, const Tq *qk, uint32_t cs, Spinor<Tc> &w)
 {
-    Spinor<Tc> chi;
-    load_half<HP, Tc>(qk, nb.vo, cs, chi);
+    Half<Tc> h;
+    load_half6<HP>(qk, nb.vo, cs, h);
     Tc U[18];
     load_link(links, a.g.V, MU, me.ns, U);
+    Spinor<Tc> chi;
+    expand_half<HP>(h, chi);
     spinor_zero(w);
     hop_accumulate<MU, -1, false>(U, chi, w);
 }
 
 template <int HP, typename Tc, typename Tq>
 __device__ inline void part_column(const CoarseArgs<Tq> &a, const Tc *__restrict__ links, const Tc *__restrict__ clover,
-                                   int d, const SiteRef *tab, int sidx, int ls, const Tq *qk, uint32_t cs, Spinor<Tc> &w)
+                                   const Tc *ul, int d, const SiteRef *tab, int sidx, int ls, const Tq *qk, uint32_t cs,
+                                   Spinor<Tc> &w)
 {
     switch (d) {
-    case 0: self_column<HP>(a, links, clover, tab, ls, qk, cs, w); break;
+    case 0: self_column<HP>(a, links, clover, ul, tab, ls, qk, cs, w); break;
     case 1: face_column<0, HP>(a, links, tab[sidx], tab[MAXVA + sidx], qk, cs, w); break;
     case 2: face_column<1, HP>(a, links, tab[sidx], tab[MAXVA + sidx], qk, cs, w); break;
     case 3: face_column<2, HP>(a, links, tab[sidx], tab[MAXVA + sidx], qk, cs, w); break;
@@ -179,8 +229,12 @@ __device__ inline void part_column(const CoarseArgs<Tq> &a, const Tc *__restrict
 // A[l%16][l/16] = conj(q)[row][kk] and B[l/16][l%16] = w[kk][col], holds D[4(l/16)+r][l%16].
 // The sites the workgroup touches are looked up once into an LDS table (native index,
 // vector offset, local coordinates), so the per-item work has no integer division.  The
-// rows of the next chunk are loaded during the products of the current one, and the
-// (aggregate, part) items are taken in contiguous runs per XCD, so that concurrent
+// rows of the next chunk, and in the self part the links of its sites (staged in LDS), are loaded
+// during the products of the current one; the columns load a hop's operands during the
+// previous hop's arithmetic; lanes cover 4 vectors x 8 sites, 128-byte runs (vectors across the
+// lanes had made every load 16-byte pieces of sixteen lines): 32^3 x 64, 32 vectors in FP32 14.6 ->
+// 11.5 ms, 16^4 with 20 408 -> 328 us, against 5.3 ms of matrix-core work.  The (aggregate, part)
+// items are taken in contiguous runs per XCD, so that concurrent
 // workgroups of one XCD read neighbouring aggregates (the face parts' neighbours) through
 // the same L2, and the vector-unit-heavy self parts share CUs with the latency-bound faces.
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -208,7 +262,7 @@ __device__ inline void tile_products(const float2 *const (&qb)[2], const float2 
 }
 
 template <typename Tc, typename Tq>
-__global__ void __launch_bounds__(NTHR) k_coarse(CoarseArgs<Tq> a, const Tc *__restrict__ links,
+__global__ void __launch_bounds__(NTHR, sizeof(Tc) == 4 && sizeof(Tq) <= 4 ? 4 : 1) k_coarse(CoarseArgs<Tq> a, const Tc *__restrict__ links,
                                                  const Tc *__restrict__ clover)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -221,6 +275,7 @@ __global__ void __launch_bounds__(NTHR) k_coarse(CoarseArgs<Tq> a, const Tc *__r
     SiteRef *tab = reinterpret_cast<SiteRef *>(smem);  // [MAXVA] own sites, [MAXFACE] face neighbours
     float2 *Qs = reinterpret_cast<float2 *>(tab + MAXVA + MAXFACE);  // [2][CHS][6][QST]
     float2 *Ws = Qs + CHS * 12 * QST;                               // [2][CHS][6][WST]
+    Tc *Us = reinterpret_cast<Tc *>(Ws + CHS * 12 * WST);           // [CHS][72] links of the chunk (FP32, self)
     // work item li = 5 i + d: aggregate i, part d (0: the self block; 1 + mu: the +mu face
     // block), so that the five parts of an aggregate are consecutive and a CU runs self and
     // face workgroups side by side; items in contiguous runs per XCD.  A grid of a few waves of
@@ -266,26 +321,36 @@ __global__ void __launch_bounds__(NTHR) k_coarse(CoarseArgs<Tq> a, const Tc *__r
             tab[MAXVA + f] = site_ref(a, j, ls - (a.a[mu] - 1) * a.astr[mu]);
         }
     }
-    // this thread's test vector k (fixed) and its slot among the rows it serves
-    const int kt = threadIdx.x % N, rows_per_pass = NTHR / N, prow = threadIdx.x / N;
-    const Tq *qk = a.Q + (size_t)(kt >> a.sshift) * a.gsz + (kt & ((1 << a.sshift) - 1));
+    // this thread's test vector k and site of the chunk (fixed), its unit's part of rows and columns
+    const int kt = 4 * ((threadIdx.x >> 5) & 7) + (threadIdx.x & 3), st = (threadIdx.x >> 2) & (CHS - 1);
+    const int up = threadIdx.x >> 8;
+    const bool kok = kt < N;
+    const int kq = kok ? kt : 0;
+    const Tq *qk = a.Q + (size_t)(kq >> a.sshift) * a.gsz + (kq & ((1 << a.sshift) - 1));
     const uint32_t cs = (uint32_t)(a.g.Vb * a.g.S);
 
     // rows: q_k at (site, component) of a chunk, one (site, component) row per thread and pass.
     // The next chunk's rows are loaded into registers before the products of the current one
     // and stored to LDS after them; a row outside the set reads site 0 and is stored as zero.
+    // With them, in the self part, the links of the next chunk's sites (16 bytes per thread).
     float2 rv[RMAX];
-    uint32_t rok = 0;
+    bool rok = false;
+    constexpr bool STAGE = sizeof(Tc) == 4;
+    typedef float f4v __attribute__((ext_vector_type(4)));
+    f4v lv = {0.f, 0.f, 0.f, 0.f};
     const auto load_rows = [&](int s0) {
-        rok = 0;
+        const int sidx = s0 + st;
+        rok = sidx < nsites;
+        const uint32_t vo = tab[rok ? sidx : 0].vo;
 #pragma unroll
         for (int it = 0; it < RMAX; ++it) {
-            const int rw = prow + it * rows_per_pass, sl = rw / 12, comp = rw - sl * 12, sidx = s0 + sl;
-            const bool ok = prow < rows_per_pass && rw < CHS * 12 && sidx < nsites;
-            const uint32_t vo = tab[ok ? sidx : 0].vo;
-            const int cc = ok ? comp : 0;
-            rv[it] = make_float2(load_as<float>(qk + vo + (2 * cc) * cs), load_as<float>(qk + vo + (2 * cc + 1) * cs));
-            rok |= (uint32_t)ok << it;
+            const Tq *p = qk + (size_t)(vo + (uint32_t)(2 * up) * cs) + (size_t)(4 * it) * cs;  // component 2 it + up
+            rv[it] = make_float2(load_as<float>(p), load_as<float>(p + cs));
+        }
+        if (STAGE && self && threadIdx.x < CHS * 18) {
+            const int sl = threadIdx.x / 18, q = threadIdx.x - sl * 18;
+            const int ns = tab[s0 + sl < nsites ? s0 + sl : 0].ns;
+            lv = reinterpret_cast<const f4v *>(links)[(size_t)(uint32_t)ns * 18 + q];
         }
     };
     __syncthreads();  // the site table
@@ -293,32 +358,32 @@ __global__ void __launch_bounds__(NTHR) k_coarse(CoarseArgs<Tq> a, const Tc *__r
 
     for (int s0 = 0; s0 < nsites; s0 += CHS) {
         __syncthreads();
+        if (kok) {
+            float2 *qst = Qs + opaque_index((st * 6 + up) * QST + kt);
 #pragma unroll
-        for (int it = 0; it < RMAX; ++it) {
-            const int rw = prow + it * rows_per_pass, sl = rw / 12, comp = rw - sl * 12;
-            if (prow < rows_per_pass && rw < CHS * 12)
-                Qs[((comp >= 6 ? CHS * 6 : 0) + sl * 6 + comp % 6) * QST + kt] =
-                    (rok >> it) & 1u ? rv[it] : make_float2(0.f, 0.f);
+            for (int it = 0; it < RMAX; ++it)  // component 2 it + up: of half 0 for it < 3
+                qst[((it >= 3 ? CHS * 6 : 0) + (2 * it) % 6) * QST] = rok ? rv[it] : make_float2(0.f, 0.f);
         }
-        if (prow < rows_per_pass) {
-            // columns: (h', site) pairs, k' = kt; h' outermost, so that a wavefront mostly
-            // shares one spin half
-            for (int pr = prow; pr < 2 * CHS; pr += rows_per_pass) {
-                const int hp = pr / CHS, sl = pr - hp * CHS, sidx = s0 + sl;
-                Spinor<Tc> w;
-                if (sidx < nsites) {
-                    const int ls = self ? sidx : 0;
-                    if (hp == 0) part_column<0>(a, links, clover, d, tab, sidx, ls, qk, cs, w);
-                    else part_column<1>(a, links, clover, d, tab, sidx, ls, qk, cs, w);
-                } else {
-                    spinor_zero(w);
-                }
-                const int c = hp * N + kt;
-#pragma unroll
-                for (int comp = 0; comp < 12; ++comp)
-                    Ws[((comp / 6) * CHS * 6 + sl * 6 + comp % 6) * WST + c] =
-                        make_float2((float)w.re[comp], (float)w.im[comp]);
+        if (STAGE && self) {
+            if (threadIdx.x < CHS * 18) reinterpret_cast<f4v *>(Us)[threadIdx.x] = lv;
+            __syncthreads();
+        }
+        if (kok) {
+            // column (h', k') = (up, kt) at site st of the chunk
+            const int sidx = s0 + st;
+            Spinor<Tc> w;
+            if (sidx < nsites) {
+                const int ls = self ? sidx : 0;
+                const Tc *ul = Us + 72 * st;
+                if (up == 0) part_column<0>(a, links, clover, ul, d, tab, sidx, ls, qk, cs, w);
+                else part_column<1>(a, links, clover, ul, d, tab, sidx, ls, qk, cs, w);
+            } else {
+                spinor_zero(w);
             }
+            float2 *wst = Ws + opaque_index(st * 6 * WST + up * N + kt);
+#pragma unroll
+            for (int comp = 0; comp < 12; ++comp)
+                wst[((comp / 6) * CHS * 6 + comp % 6) * WST] = make_float2((float)w.re[comp], (float)w.im[comp]);
         }
         __syncthreads();
         if (s0 + CHS < nsites) load_rows(s0 + CHS);
@@ -429,7 +494,8 @@ int coarse_dispatch(const mrhs_op *op, const Tc *links, const Tc *clover, const 
     for (int mu = 0; mu < 4; ++mu)
         if (op->Va / op->g.agg[mu] > MAXFACE)
             return set_error(MRHS_EUNSUPPORTED, "coarse_op_build: aggregate face above 64 sites");
-    const size_t lds = sizeof(SiteRef) * (MAXVA + MAXFACE) + sizeof(float2) * (size_t)CHS * 12 * (QST + WST);
+    const size_t lds = sizeof(SiteRef) * (MAXVA + MAXFACE) + sizeof(float2) * (size_t)CHS * 12 * (QST + WST) +
+                       (sizeof(Tc) == 4 ? sizeof(float) * CHS * 72 : 0);
     hipLaunchKernelGGL((k_coarse<Tc, Tq>), dim3(op->n_agg * 5), dim3(NTHR), lds, st, a, links, clover);
     return hip_check(hipGetLastError(), "k_coarse launch");
 }
