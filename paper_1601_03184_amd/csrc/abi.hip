@@ -359,8 +359,8 @@ int mrhs_residual_norms(const mrhs_op *op, const void *b, const void *x, int32_t
     if (int rc = check_op(op)) return rc;
     if (int rc = check_nrhs(n_rhs)) return rc;
     if (!b || !x || !out || !ws) return set_error(MRHS_EINVAL, "null argument");
-    if (ws_bytes < ws_bytes_residual(op, n_rhs)) return set_error(MRHS_EINVAL, "workspace too small");
-    return launch_residual(op, b, x, n_rhs, out, ws, (hipStream_t)stream);
+    if (ws_bytes < ws_bytes_residual_least(op, n_rhs)) return set_error(MRHS_EINVAL, "workspace too small");
+    return launch_residual(op, b, x, n_rhs, out, ws, ws_bytes, (hipStream_t)stream);
 }
 
 int mrhs_residual_norms_noalloc(const mrhs_op *op, const void *b, const void *x, int32_t n_rhs, double *out,

@@ -6,6 +6,7 @@
 // so the operator is fetched once per site for the whole tile (the mat-vec -> mat-mat
 // argument of Sec. 6); tiles of one block share an XCD's L2 through xcd_remap.
 #include <mutex>
+#include <type_traits>
 
 #include "launch.h"
 #include "stencil.h"
@@ -39,68 +40,231 @@ __global__ void __launch_bounds__(256 * T) k_dirac(KGeo g, const Tc *__restrict_
     store_spinor(g, y, grp, blk, off, tt, out);
 }
 
-// The stencil at tile 4 on a short length of 4 (FP32): a workgroup takes two consecutive
-// groups of the native layout, 8 lanes per site (lanes t < 4 the first group, t >= 4 the
-// second), and walks the block in passes of 128 sites, so that a site's links and clover are
-// loaded once for 8 right-hand sides; lanes of a group beyond the last one do nothing.
-template <typename Ts, typename Tc>
-__global__ void __launch_bounds__(1024) k_dirac_2g(KGeo g, const Tc *__restrict__ links, const Tc *__restrict__ clover,
-                                                   const uint32_t *__restrict__ blk_coords,
-                                                   const uint32_t *__restrict__ loc_coords, const Ts *__restrict__ x,
-                                                   Ts *__restrict__ y, int ntiles, int ngrp)
+// The stencil with the workgroup's own sites in LDS.  A workgroup takes a chunk of consecutive sites
+// of a block for TL right-hand sides (TL lanes per site; TL = 2 S: two groups of the layout): every
+// spinor of the chunk is read once from global memory instead of once per neighbour, and a
+// hop reads LDS where the neighbour lies in the chunk, global memory where it does not (the
+// lanes of either kind share the hop's arithmetic).  With AHEAD the global operands of a hop are
+// loaded two hops ahead.
+//
+// Spinors are held as stored (Elem) and converted where they are used.  LDS: component vectors of
+// 16 bytes, [24 / n][threads].
+template <typename Ts> struct Elem {
+    using type = Ts;
+};
+template <> struct Elem<__half> {
+    using type = _Float16;  // the same bits
+};
+
+template <typename Tx> struct ChunkVec {
+    static constexpr int n = 16 / sizeof(Tx);
+    typedef Tx type __attribute__((ext_vector_type(16 / sizeof(Tx))));
+};
+
+template <typename Tx> __device__ __forceinline__ void chunk_store(typename ChunkVec<Tx>::type *lds, int me, const Spinor<Tx> &s)
 {
-    const int li = xcd_remap(blockIdx.x, g.nblk * ntiles);
-    const int blk = li / ntiles, tile = li - blk * ntiles;
-    const int lt = tile * 8 + threadIdx.x % 8, grp = lt / g.S, tt = lt % g.S;
-    const int nsite = g.Vb < 128 ? g.Vb : 128;
-#pragma unroll 1
-    for (int o = threadIdx.x / 8; o < g.Vb && grp < ngrp; o += nsite) {
-        const int off = opaque_index(o);
-        int bc[4], lc[4];
-        decode_site(g, blk_coords, loc_coords, blk, off, bc, lc);
-        Spinor<Tc> out;
-        dirac_site_global<Tc>(g, links, clover, x, grp, tt, blk, off, bc, lc, out, NoSkip{});
-        store_spinor(g, y, grp, blk, off, tt, out);
+    constexpr int n = ChunkVec<Tx>::n;
+#pragma unroll
+    for (int v = 0; v < 24 / n; ++v) {
+        typename ChunkVec<Tx>::type q;
+#pragma unroll
+        for (int c = 0; c < n; c += 2) {
+            q[c] = s.re[(v * n + c) / 2];
+            q[c + 1] = s.im[(v * n + c) / 2];
+        }
+        lds[v * (int)blockDim.x + me] = q;
     }
 }
 
-// Per (block, tile of T right-hand sides): partial sums of |b - D x|^2 and |b|^2 per
-// right-hand side, FP64.  A workgroup of (up to 64 sites) x T lanes walks the block in
-// passes of 64 sites, so that a workgroup is small while the FP64 stencil takes ~130
-// registers.  The T lanes of a site share its FP64 field loads; with T = 2S a tile spans two
+template <typename Tx>
+__device__ __forceinline__ void chunk_load(const typename ChunkVec<Tx>::type *lds, int me, Spinor<Tx> &s)
+{
+    constexpr int n = ChunkVec<Tx>::n;
+#pragma unroll
+    for (int v = 0; v < 24 / n; ++v) {
+        const auto q = lds[v * (int)blockDim.x + me];
+#pragma unroll
+        for (int c = 0; c < n; c += 2) {
+            s.re[(v * n + c) / 2] = q[c];
+            s.im[(v * n + c) / 2] = q[c + 1];
+        }
+    }
+}
+
+// Operand of one hop: where it comes from and, for a lane whose neighbour is outside the chunk, the
+// neighbour's spinor
+template <typename Tx> struct HopIn {
+    Spinor<Tx> chi;
+    int lds;   // LDS site of the neighbour, or -1
+    int site;  // native site of the neighbour
+};
+
+template <int MU, bool FWD, typename Tx, typename Ts>
+__device__ __forceinline__ void hop_fetch(const KGeo &g, const Ts *__restrict__ x, int grp, int tt, int blk, int off, int o0,
+                                          int ns, const int (&bc)[4], const int (&lc)[4], HopIn<Tx> &h)
+{
+    const NbrSite n = FWD ? nbr_fwd(g, MU, blk, off, bc, lc) : nbr_bwd(g, MU, blk, off, bc, lc);
+    const int l = n.off - o0;
+    h.lds = n.blk == blk && l >= 0 && l < ns ? l : -1;
+    h.site = n.blk * g.Vb + n.off;
+    if (h.lds < 0) load_spinor<Tx>(g, x, grp, n.blk, n.off, tt, h.chi);
+}
+
+template <int MU, bool FWD, int TL, typename Tc, typename Tx, typename Tf>
+__device__ __forceinline__ void hop_apply(const Tf *__restrict__ links, const typename ChunkVec<Tx>::type *lds, int t,
+                                          int own, HopIn<Tx> &h, Spinor<Tc> &out)
+{
+    Tc U[18];
+    load_link(links, 0L, MU, FWD ? own : h.site, U);
+    if (h.lds >= 0) chunk_load<Tx>(lds, h.lds * TL + t, h.chi);
+    hop_accumulate<MU, FWD ? -1 : 1, !FWD>(U, h.chi, out);
+    hop_fence(out);
+}
+
+template <int TL, bool AHEAD, typename Tc, typename Tx, typename Tf>
+__device__ __forceinline__ void dirac_chunk(const KGeo &g, const Tf *__restrict__ links, const Tf *__restrict__ clover,
+                                            const uint32_t *__restrict__ blk_coords,
+                                            const uint32_t *__restrict__ loc_coords, const Tx *__restrict__ x, int grp,
+                                            int tt, int blk, int o0, int ns, bool ok, unsigned char *smem, Spinor<Tc> &out)
+{
+    using V = typename ChunkVec<Tx>::type;
+    V *lds = reinterpret_cast<V *>(smem);
+    const int t = threadIdx.x % TL, off = o0 + (ok ? (int)threadIdx.x / TL : 0);
+    const int own = blk * g.Vb + off;
+    int bc[4], lc[4];
+    decode_site(g, blk_coords, loc_coords, blk, off, bc, lc);
+    HopIn<Tx> f, b;
+    auto fetch = [&](auto mu, auto fwd, HopIn<Tx> &h) __attribute__((always_inline)) {
+        hop_fetch<decltype(mu)::value, decltype(fwd)::value>(g, x, grp, tt, blk, off, o0, ns, bc, lc, h);
+    };
+    std::integral_constant<int, 0> m0;
+    std::true_type fw;
+    std::false_type bw;
+    if (ok) {
+        Spinor<Tx> me;
+        load_spinor<Tx>(g, x, grp, blk, off, tt, me);
+        if (AHEAD) {
+            fetch(m0, fw, f);
+            fetch(m0, bw, b);
+        }
+        sched_fence();
+        chunk_store<Tx>(lds, threadIdx.x, me);
+        clover_site(clover, g.V, own, me, out);
+        hop_fence(out);
+    }
+    __syncthreads();
+    if (!ok) return;
+    auto direction = [&](auto mu) __attribute__((always_inline)) {
+        constexpr int MU = decltype(mu)::value;
+        std::integral_constant<int, (MU + 1) % 4> next;
+        if (!AHEAD) fetch(mu, fw, f);
+        hop_apply<MU, true, TL>(links, lds, t, own, f, out);
+        if (AHEAD && MU < 3) fetch(next, fw, f);
+        sched_fence();
+        if (!AHEAD) fetch(mu, bw, b);
+        hop_apply<MU, false, TL>(links, lds, t, own, b, out);
+        if (AHEAD && MU < 3) fetch(next, bw, b);
+        sched_fence();
+    };
+    direction(m0);
+    direction(std::integral_constant<int, 1>{});
+    direction(std::integral_constant<int, 2>{});
+    direction(std::integral_constant<int, 3>{});
+}
+
+// Sites per workgroup: the block cut into equal chunks of at most `most` sites
+struct Chunks {
+    int n, sites;
+};
+Chunks chunks_of(const KGeo &g, int most)
+{
+    const int n = (g.Vb + most - 1) / most;
+    return {n, (g.Vb + n - 1) / n};
+}
+
+// Work item li of a grid over (block, tile of TL right-hand sides, slot), a slot being one chunk or
+// (slots = 1) the whole block: the slots and tiles of a block are consecutive, blocks in
+// contiguous runs per XCD
+struct ChunkItem {
+    int blk, tile, slot;
+};
+__device__ inline ChunkItem chunk_item(const KGeo &g, int ntiles, int slots)
+{
+    const int li = xcd_remap(blockIdx.x, g.nblk * ntiles * slots);
+    ChunkItem w;
+    w.blk = li / (ntiles * slots);
+    const int rem = li - w.blk * ntiles * slots;
+    w.tile = rem / slots;
+    w.slot = rem - w.tile * slots;
+    return w;
+}
+
+// The stencil at tile 4 on a short length of 4 (FP32): chunks of up to 128 sites, two workgroups
+// per CU.  Bound by the traffic between L2 and memory, three quarters of it neighbours' faces (a face
+// in x is every fourth site of the neighbouring block): 32^3 x 64, 24 right-hand sides in FP32 6.5 -> 4.9 ms
+// (10.9 GB once each, 28 GB by the counters, 5.7 TB/s), 16^4 with 20 158 -> 120 us.
+constexpr int DIRAC_TL = 4, DIRAC_SITES = 128;
+
+template <typename Ts, typename Tc>
+__global__ void __launch_bounds__(DIRAC_TL *DIRAC_SITES, 4)
+    k_dirac_chunk(KGeo g, const Tc *__restrict__ links, const Tc *__restrict__ clover,
+                  const uint32_t *__restrict__ blk_coords, const uint32_t *__restrict__ loc_coords,
+                  const Ts *__restrict__ x, Ts *__restrict__ y, int ntiles, Chunks ch, int ngrp)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const ChunkItem w = chunk_item(g, ntiles, ch.n);
+    const int o0 = w.slot * ch.sites, ns = g.Vb - o0 < ch.sites ? g.Vb - o0 : ch.sites;
+    const int lt = w.tile * DIRAC_TL + threadIdx.x % DIRAC_TL, grp = lt / g.S, tt = lt % g.S;
+    const bool ok = (int)threadIdx.x / DIRAC_TL < ns && grp < ngrp;
+    Spinor<Tc> out;
+    using Tx = typename Elem<Ts>::type;
+    dirac_chunk<DIRAC_TL, true>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0,
+                          ns, ok, smem, out);
+    if (ok) store_spinor(g, y, grp, w.blk, o0 + (int)threadIdx.x / DIRAC_TL, tt, out);
+}
+
+// Per (block, tile of T right-hand sides, slot): partial sums of |b - D x|^2 and |b|^2 per right-hand
+// side, FP64.  The T lanes of a site share its FP64 field loads; with T = 2S a tile spans two
 // groups of the native layout (lanes t < S the first, t >= S the second), which halves the
 // field loads per right-hand side.  Lanes of a group beyond the last one add nothing.
-constexpr int RES_SITES = 64;
+// Bound by the field loads: each lane takes 1.7 KB of FP64 links and clover per site through L1
+// beside 0.5 KB of vectors.  Operands two hops ahead (two wavefronts per SIMD, 218 VGPRs) beat
+// three without (7.0 -> 6.4 ms at 32^3 x 64 with 24 right-hand sides in FP32; 8.7 ms without, held to
+// 168 VGPRs it spilled); FP64 storage, where they would take 268, goes without.
+constexpr int RES_THREADS = 256;
 
 template <typename Ts, int T>
-__global__ void __launch_bounds__(RES_SITES * T) k_residual(KGeo g, const double *__restrict__ links,
-                                                            const double *__restrict__ clover,
-                                                            const uint32_t *__restrict__ blk_coords,
-                                                            const uint32_t *__restrict__ loc_coords,
-                                                            const Ts *__restrict__ b, const Ts *__restrict__ x,
-                                                            int ntiles, int ngrp, double *__restrict__ part)
+__global__ void __launch_bounds__(RES_THREADS, 2) k_residual(KGeo g, const double *__restrict__ links,
+                                                          const double *__restrict__ clover,
+                                                          const uint32_t *__restrict__ blk_coords,
+                                                          const uint32_t *__restrict__ loc_coords,
+                                                          const Ts *__restrict__ b, const Ts *__restrict__ x, int ntiles,
+                                                          Chunks ch, int slots, int ngrp, double *__restrict__ part)
 {
-    __shared__ double red[RES_SITES * T / 64][T][2];
-    // tiles of one block on one XCD, consecutively: the block's FP64 fields and its
-    // neighbours' spinors are fetched into that XCD's L2 once for all its tiles
-    const int li = xcd_remap(blockIdx.x, g.nblk * ntiles);
-    const int blk = li / ntiles, tile = li - blk * ntiles;
-    const int lt = tile * T + threadIdx.x % T, grp = lt / g.S, tt = lt % g.S;
-    const int nsite = g.Vb < RES_SITES ? g.Vb : RES_SITES;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[RES_THREADS / 64][T][2];
+    const ChunkItem w = chunk_item(g, ntiles, slots);
+    const int lt = w.tile * T + threadIdx.x % T, grp = lt / g.S, tt = lt % g.S, s = (int)threadIdx.x / T;
+    using Tx = typename Elem<Ts>::type;
     double num = 0, den = 0;
+    const int c0 = slots == 1 ? 0 : w.slot, c1 = slots == 1 ? ch.n : w.slot + 1;
 #pragma unroll 1
-    for (int o = threadIdx.x / T; o < g.Vb && grp < ngrp; o += nsite) {
-        const int off = opaque_index(o);
-        int bc[4], lc[4];
-        decode_site(g, blk_coords, loc_coords, blk, off, bc, lc);
-        Spinor<double> Dx, bb;
-        dirac_site_global<double>(g, links, clover, x, grp, tt, blk, off, bc, lc, Dx, NoSkip{});
-        load_spinor<double>(g, b, grp, blk, off, tt, bb);
+    for (int c = c0; c < c1; ++c) {
+        const int o0 = c * ch.sites, ns = g.Vb - o0 < ch.sites ? g.Vb - o0 : ch.sites;
+        const bool ok = s < ns && grp < ngrp;
+        if (c > c0) __syncthreads();  // every lane has finished reading the last chunk
+        Spinor<double> Dx;
+        dirac_chunk<T, (sizeof(Ts) < 8)>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0, ns,
+                       ok, smem, Dx);
+        if (ok) {
+            Spinor<double> bb;
+            load_spinor<double>(g, b, grp, w.blk, o0 + s, tt, bb);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            const double dr = bb.re[c] - Dx.re[c], di = bb.im[c] - Dx.im[c];
-            num += dr * dr + di * di;
-            den += bb.re[c] * bb.re[c] + bb.im[c] * bb.im[c];
+            for (int k = 0; k < 12; ++k) {
+                const double dr = bb.re[k] - Dx.re[k], di = bb.im[k] - Dx.im[k];
+                num += dr * dr + di * di;
+                den += bb.re[k] * bb.re[k] + bb.im[k] * bb.im[k];
+            }
         }
     }
     num = wave_sum_mod<T>(num);
@@ -114,11 +278,11 @@ __global__ void __launch_bounds__(RES_SITES * T) k_residual(KGeo g, const double
     if (threadIdx.x < T) {
         double sn = 0, sd = 0;
         const int nw = (blockDim.x + 63) >> 6;
-        for (int w = 0; w < nw; ++w) {
-            sn += red[w][threadIdx.x][0];
-            sd += red[w][threadIdx.x][1];
+        for (int k = 0; k < nw; ++k) {
+            sn += red[k][threadIdx.x][0];
+            sd += red[k][threadIdx.x][1];
         }
-        double *p = part + (((long)tile * g.nblk + blk) * T + threadIdx.x) * 2;
+        double *p = part + ((((long)w.tile * g.nblk + w.blk) * slots + w.slot) * T + threadIdx.x) * 2;
         p[0] = sn;
         p[1] = sd;
     }
@@ -174,9 +338,11 @@ int dirac_dispatch(const mrhs_op *op, const Tc *links, const Tc *clover, const v
         // tile 4 only with FP32 arithmetic (FP64 would spill to scratch)
         if constexpr (sizeof(Tc) == 4) {
             if (g.S == 4) {
-                const int nt2 = (ngrp + 1) / 2, ns = g.Vb < 128 ? g.Vb : 128;
-                hipLaunchKernelGGL((k_dirac_2g<Ts, Tc>), dim3(g.nblk * nt2), dim3(round64(ns * 8)), 0, st, g, links,
-                                   clover, op->blk_coords, op->loc_coords, (const Ts *)x, (Ts *)y, nt2, ngrp);
+                const Chunks ch = chunks_of(g, DIRAC_SITES);
+                const int threads = round64(ch.sites * DIRAC_TL);
+                hipLaunchKernelGGL((k_dirac_chunk<Ts, Tc>), dim3(g.nblk * ngrp * ch.n), dim3(threads),
+                                   24 * sizeof(Ts) * threads, st, g, links, clover, op->blk_coords, op->loc_coords,
+                                   (const Ts *)x, (Ts *)y, ngrp, ch, ngrp);
                 break;
             }
             hipLaunchKernelGGL((k_dirac<Ts, Tc, 4>), grid, block, 0, st, g, links, clover, op->blk_coords,
@@ -190,38 +356,57 @@ int dirac_dispatch(const mrhs_op *op, const Tc *links, const Tc *clover, const v
     return hip_check(hipGetLastError(), "k_dirac launch");
 }
 
-// lanes per site of the residual: two groups of 4 right-hand sides, else as many lanes as
-// the short length allows
-int residual_tile(const KGeo &g) { return g.S % 4 == 0 ? 8 : g.S % 2 == 0 ? 2 : 1; }
+// lanes per site of the residual: two groups of 4 right-hand sides (one where there is one only:
+// half of the lanes would idle), else as many lanes as the short length allows
+int residual_tile(const KGeo &g, int n_rhs)
+{
+    if (g.S % 4 == 0) return g.S == 4 && n_rhs <= 4 ? 4 : 8;
+    return g.S % 2 == 0 ? 2 : 1;
+}
 int residual_tiles(const KGeo &g, int n_rhs, int T)
 {
     const int ngrp = (n_rhs + g.S - 1) / g.S;
     return (ngrp * g.S + T - 1) / T;
 }
 
+// A short grid takes one workgroup per chunk (a block's chunks side by side), a long one a workgroup
+// per block, whose chunks follow one another and share one partial sum
+Chunks residual_chunks(const KGeo &g, int T) { return chunks_of(g, RES_THREADS / T); }
+int residual_slots(const KGeo &g, int ntiles, int T) { return (long)g.nblk * ntiles < 2048 ? residual_chunks(g, T).n : 1; }
+
+size_t residual_bytes(const KGeo &g, int n_rhs, int T, int slots)
+{
+    return (size_t)residual_tiles(g, n_rhs, T) * T * g.nblk * slots * 2 * sizeof(double);
+}
+
 template <typename Ts, int T>
-int residual_launch(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, hipStream_t st)
+int residual_launch(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, size_t ws_bytes,
+                    hipStream_t st)
 {
     const KGeo &g = op->k;
-    const int ngrp = (n_rhs + g.S - 1) / g.S;
-    const int ntiles = residual_tiles(g, n_rhs, T);
+    const int ngrp = (n_rhs + g.S - 1) / g.S, ntiles = residual_tiles(g, n_rhs, T);
+    int slots = residual_slots(g, ntiles, T);
+    if (residual_bytes(g, n_rhs, T, slots) > ws_bytes) slots = 1;  // a workspace of the least size
+    const Chunks ch = residual_chunks(g, T);
     double *part = (double *)ws;
-    const int nsite = g.Vb < RES_SITES ? g.Vb : RES_SITES;
-    hipLaunchKernelGGL((k_residual<Ts, T>), dim3(g.nblk * ntiles), dim3(round64(nsite * T)), 0, st, g, op->links64,
-                       op->clover64, op->blk_coords, op->loc_coords, (const Ts *)b, (const Ts *)x, ntiles, ngrp,
-                       part);
+    const int threads = round64(ch.sites * T);
+    hipLaunchKernelGGL((k_residual<Ts, T>), dim3(g.nblk * ntiles * slots), dim3(threads), 24 * sizeof(Ts) * threads, st, g,
+                       op->links64, op->clover64, op->blk_coords, op->loc_coords, (const Ts *)b, (const Ts *)x, ntiles, ch,
+                       slots, ngrp, part);
     if (int rc = hip_check(hipGetLastError(), "k_residual launch")) return rc;
-    hipLaunchKernelGGL((k_residual_finish<T>), dim3(n_rhs), dim3(256), 0, st, part, g.nblk, n_rhs, out);
+    hipLaunchKernelGGL((k_residual_finish<T>), dim3(n_rhs), dim3(256), 0, st, part, g.nblk * slots, n_rhs, out);
     return hip_check(hipGetLastError(), "k_residual_finish launch");
 }
 
 template <typename Ts>
-int residual_dispatch(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, hipStream_t st)
+int residual_dispatch(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, size_t ws_bytes,
+                      hipStream_t st)
 {
-    switch (residual_tile(op->k)) {
-    case 8: return residual_launch<Ts, 8>(op, b, x, n_rhs, out, ws, st);
-    case 2: return residual_launch<Ts, 2>(op, b, x, n_rhs, out, ws, st);
-    default: return residual_launch<Ts, 1>(op, b, x, n_rhs, out, ws, st);
+    switch (residual_tile(op->k, n_rhs)) {
+    case 8: return residual_launch<Ts, 8>(op, b, x, n_rhs, out, ws, ws_bytes, st);
+    case 4: return residual_launch<Ts, 4>(op, b, x, n_rhs, out, ws, ws_bytes, st);
+    case 2: return residual_launch<Ts, 2>(op, b, x, n_rhs, out, ws, ws_bytes, st);
+    default: return residual_launch<Ts, 1>(op, b, x, n_rhs, out, ws, ws_bytes, st);
     }
 }
 
@@ -239,11 +424,16 @@ int launch_dirac(const mrhs_op *op, const void *x, void *y, int n_rhs, hipStream
     }
 }
 
+size_t ws_bytes_residual_least(const mrhs_op *op, int n_rhs)
+{
+    return residual_bytes(op->k, n_rhs, residual_tile(op->k, n_rhs), 1);
+}
+
 size_t ws_bytes_residual(const mrhs_op *op, int n_rhs)
 {
     const KGeo &g = op->k;
-    const int T = residual_tile(g);
-    return (size_t)residual_tiles(g, n_rhs, T) * T * g.nblk * 2 * sizeof(double);
+    const int T = residual_tile(g, n_rhs), nt = residual_tiles(g, n_rhs, T);
+    return residual_bytes(g, n_rhs, T, residual_slots(g, nt, T));
 }
 
 namespace {
@@ -276,22 +466,23 @@ int device_scratch(int device, void **out)
 
 int launch_residual_noalloc(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, hipStream_t st)
 {
-    if (ws_bytes_residual(op, n_rhs) > RESID_SCRATCH_BYTES)
-        return set_error(MRHS_EUNSUPPORTED, "residual partial sums (" + std::to_string(ws_bytes_residual(op, n_rhs)) +
+    if (ws_bytes_residual_least(op, n_rhs) > RESID_SCRATCH_BYTES)
+        return set_error(MRHS_EUNSUPPORTED, "residual partial sums (" + std::to_string(ws_bytes_residual_least(op, n_rhs)) +
                                                 " bytes) exceed the 32 MiB scratch of the allocation-free call");
     void *ws = nullptr;
     if (int rc = device_scratch(op->device, &ws)) return rc;
-    return launch_residual(op, b, x, n_rhs, out, ws, st);
+    return launch_residual(op, b, x, n_rhs, out, ws, RESID_SCRATCH_BYTES, st);
 }
 
-int launch_residual(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, hipStream_t st)
+int launch_residual(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, size_t ws_bytes,
+                    hipStream_t st)
 {
     switch (op->dtype) {
     case MRHS_DTYPE_F64:
-        return residual_dispatch<double>(op, b, x, n_rhs, out, ws, st);
+        return residual_dispatch<double>(op, b, x, n_rhs, out, ws, ws_bytes, st);
     case MRHS_DTYPE_F32:
-        return residual_dispatch<float>(op, b, x, n_rhs, out, ws, st);
+        return residual_dispatch<float>(op, b, x, n_rhs, out, ws, ws_bytes, st);
     default:
-        return residual_dispatch<__half>(op, b, x, n_rhs, out, ws, st);
+        return residual_dispatch<__half>(op, b, x, n_rhs, out, ws, ws_bytes, st);
     }
 }

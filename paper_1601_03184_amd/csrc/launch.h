@@ -13,7 +13,8 @@ int launch_unpack(const mrhs_op *op, const void *native, int dtype, double *cano
 int launch_dirac(const mrhs_op *op, const void *x, void *y, int n_rhs, hipStream_t st);
 int launch_sap(const mrhs_op *op, const void *b, void *x, int n_rhs, int n_sap, int n_mr, void *ws, hipStream_t st,
                bool guess = false);
-int launch_residual(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, hipStream_t st);
+int launch_residual(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, size_t ws_bytes,
+                    hipStream_t st);
 // the same with the library's static per-device scratch instead of a workspace (no allocation)
 int launch_residual_noalloc(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, hipStream_t st);
 int launch_gs(const mrhs_op *op, const void *V, int vdt, void *Q, int qdt, int n_tv, int32_t *status, void *ws,
@@ -25,6 +26,7 @@ size_t ws_bytes_sap_batched(const mrhs_op *const *ops, int n, const int32_t *n_r
 int launch_sap_batched(const mrhs_op *const *ops, int n, const void *const *b, void *const *x, const int32_t *n_rhs,
                        int n_sap, int n_mr, void *ws, hipStream_t st, bool guess = false);
 size_t ws_bytes_residual(const mrhs_op *op, int n_rhs);
+size_t ws_bytes_residual_least(const mrhs_op *op, int n_rhs);  // without the short grids' per-chunk partial sums
 size_t ws_bytes_gs(const mrhs_op *op, int n_tv);
 size_t ws_bytes_coarse(const mrhs_op *op, int n_tv);
 size_t native_elems(const mrhs_op *op, int n_rhs);
