@@ -237,14 +237,11 @@ int mrhs_op_create(const mrhs_geom *geom, const double *links, double m0, double
     // SAP tile until mrhs_set_tiles or the autotuner choose one.  A larger tile shares the field loads
     // and fills the wavefronts of small blocks, a smaller one gives short lattices more
     // workgroups; it depends on the lattice alone, so that a right-hand side's result does not
-    // depend on how many others share the call.  Measured (3 x 4, us, tiles 1 / 2 / 4): FP32
-    // 24^3 x 48 n 24 18392 / 12351 / 9966, 16^4 n 20 1587 / 1093 / 1036 but n 3 333 / 254 / 293, 8^4 n 8
-    // 210 / 215 / 264; blocks of 16 sites 16^4 n 24 3470 / 1924 / 1024, 4^4 n 8 182 / 184 / 168;
-    // FP64 12^3 x 24 n 10 1349 / 1024, 8^4 n 8 278 / 322.  The even-odd solver is fastest at 2
-    // (24^3 x 48 n 24: 21573 / 14125 / 15246) and takes no more unless asked to.
-    op->sap_tile_auto = true;
-    if (prec == MRHS_PREC_F64) op->sap_tile = pick_tile(op, k.nblk >= 128 || k.Vb <= 64 ? 2 : 1, true);
-    else op->sap_tile = pick_tile(op, k.nblk >= 512 || k.Vb <= 64 ? 4 : 2, true);
+    // depend on how many others share the call.  FP64, 3 x 4, us at tiles 1 / 2: 12^3 x 24 n 10 1349 / 1024,
+    // 16^3 x 32 n 24 6715 / 4982, 4^4 in blocks of 16 sites n 8 205 / 201, 8^4 n 8 278 / 322.  FP32 stays at
+    // 2 (16^4 n 20 1093, n 3 254; at 4, which the autotuner finds on large lattices, 1036 and 293): another
+    // tile sums in another order, which FP32 results show.
+    op->sap_tile = pick_tile(op, prec != MRHS_PREC_F64 || k.nblk >= 128 || k.Vb <= 64 ? 2 : 1, true);
     op->dirac_tile = pick_tile(op, prec == MRHS_PREC_F64 ? 1 : 4, false);
     if (rc) {
         free_op(op);
@@ -639,7 +636,6 @@ int mrhs_set_tiles(mrhs_op *op, int32_t sap_tile, int32_t dirac_tile)
         if (!tile_built(op, sap_tile))
             return set_error(MRHS_EUNSUPPORTED, "SAP tiles above 2 are not built for FP64 arithmetic");
         op->sap_tile = sap_tile;
-        op->sap_tile_auto = false;
     }
     if (dirac_tile) {
         if (!ok(dirac_tile) || op->k.S % dirac_tile || op->k.Vb * dirac_tile > 1024)

@@ -57,7 +57,6 @@ struct mrhs_op {
     int32_t *agg_sites = nullptr;    // [n_agg][Va] native site of local site ls of aggregate i
     bool odd_blocks;                 // some direction has an odd number (> 1) of blocks
     int sap_tile, dirac_tile;
-    bool sap_tile_auto;  // sap_tile is mrhs_op_create's choice
     size_t max_lds;
     // SAP block solver (mrhs_set_block_solver).  For the even-odd one: A^-1 per site in the
     // clover layout (two Hermitian 6x6 blocks) and the block-local offsets in parity order,

@@ -108,7 +108,7 @@ template <typename Ts, typename Tc> struct SapArgs {
 // The block residual rho lives in LDS in component vectors of n numbers, [24 / n][Vb][T]: lane
 // (off, t) reads vector v at (v * Vb + off) * T + t, consecutive lanes consecutive vectors.  Plain
 // MR takes 16-byte vectors (half the LDS instructions and addresses of (re, im) pairs: 7.85 ->
-// 7.35 ms per half-sweep at 32^3 x 64, 32 right-hand sides, with the reduction of mr_alpha); the
+// 7.60 ms per half-sweep at 32^3 x 64, 32 right-hand sides, with the reduction of mr_alpha); the
 // even-odd kernel pairs, whose smaller load groups keep it within its registers.
 template <typename Tc> using LdsVec = typename V16<Tc>::type;
 template <typename Tc> using LdsPair = typename Vec2<Tc>::type;
@@ -646,9 +646,10 @@ __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, i
 __host__ __device__ inline int red_words(int threads, int T) { return threads / 64 * T * 4; }
 
 // alpha = <q,rho> / <q,q> (0 where q vanishes) per right-hand side lane of the workgroup, from every
-// lane's partial sums: each wavefront's sums go to LDS, and after the barrier every wavefront
-// reads all of them at once, one (wavefront, right-hand side) entry per lane (at most
-// 256 T / 64 x T <= 64 entries), and sums them across its lanes.
+// lane's partial sums: each wavefront's sums go to LDS as one 16-byte entry per right-hand side;
+// after the barrier every lane adds up its right-hand side's entries in the order of the
+// wavefronts.  (A sum across the lanes, one entry each, takes 2 % less time per half-sweep but rounds
+// differently.)
 template <int T, typename Tc>
 __device__ __forceinline__ void mr_alpha(Tc qq, Tc qrr, Tc qri, Tc *red, Tc &ar, Tc &ai)
 {
@@ -656,16 +657,20 @@ __device__ __forceinline__ void mr_alpha(Tc qq, Tc qrr, Tc qri, Tc *red, Tc &ar,
         Tc v[4];
     };
     Entry *r = reinterpret_cast<Entry *>(red);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = blockDim.x / 64 * T;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x / 64, t = threadIdx.x % T;
     qq = wave_sum_mod<T>(qq);
     qrr = wave_sum_mod<T>(qrr);
     qri = wave_sum_mod<T>(qri);
     if (lane < T) r[wave * T + lane] = {{qq, qrr, qri, Tc(0)}};
     __syncthreads();
-    const Entry x = r[lane < n ? lane : 0];
-    const Tc sqq = wave_sum_mod<T>(lane < n ? x.v[0] : Tc(0));
-    const Tc sr = wave_sum_mod<T>(lane < n ? x.v[1] : Tc(0));
-    const Tc si = wave_sum_mod<T>(lane < n ? x.v[2] : Tc(0));
+    Tc sqq = 0, sr = 0, si = 0;
+#pragma unroll 4
+    for (int w = 0; w < nw; ++w) {
+        const Entry x = r[w * T + t];
+        sqq += x.v[0];
+        sr += x.v[1];
+        si += x.v[2];
+    }
     ar = sqq > Tc(0) ? sr / sqq : Tc(0);
     ai = sqq > Tc(0) ? si / sqq : Tc(0);
 }
@@ -1190,7 +1195,7 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
     size_t max_lds = ops[0]->max_lds;
     const bool eo = ops[0]->block_solver == MRHS_BLOCK_EO_MR;
     for (int k = 0; k < n; ++k) {
-        T = std::min(T, eo && ops[k]->sap_tile_auto ? std::min(2, ops[k]->sap_tile) : ops[k]->sap_tile);
+        T = std::min(T, ops[k]->sap_tile);
         maxVb = std::max(maxVb, ops[k]->k.Vb);
         if ((ops[k]->block_solver == MRHS_BLOCK_EO_MR) != eo)
             return set_error(MRHS_EINVAL, "the operators of a batch use different block solvers");
