@@ -38,7 +38,7 @@ struct GmArgs {
     void *V;      // (m + 1) coarse vectors, FP32 or binary16 (the basis type of gmres_run)
     float *v32;   // binary16 basis: the newest basis vector as FP32 (input of the operator)
     float *w;
-    Z *part;      // [vectors][G][ldc] partial inner products, G x vectors <= GPART
+    Z *part;      // [vectors][G][ldc] partial inner products
     Z *hcur;      // [ldc][m + 1]: the current inner products, then y
     Z *H;         // [ldc][m + 1][m]
     Z *g;         // [ldc][m + 1]
@@ -78,6 +78,8 @@ constexpr int GU = 8;  // basis vectors whose loads an elementwise kernel issues
 __device__ inline long cre(const GmArgs &a, long e, int k) { return (2 * e) * a.ldc + k; }
 
 constexpr int GPART = 512;  // partial-sum blocks per inner-product launch (all vectors together)
+constexpr int FV = 8;       // basis vectors that the fused projection takes
+constexpr int FBLK = 512;   // its partial-sum blocks, each for all vectors
 
 // start: beta = ||b|| (from ||b||^2), g = (beta, 0, ...), H = 0, scale = 1 / beta
 __device__ void gm_start(const GmArgs &a, int k, double b2)
@@ -249,6 +251,83 @@ template <typename TV> __global__ void __launch_bounds__(GTHR) k_gm_axpy(GmArgs 
     a.w[o + a.ldc] = (float)wi;
 }
 
+// The projection w -= sum_i hcur[k][i] V_i (i < nvec <= FV) and the inner products that follow it
+// in one pass over w and the basis: of the new w with every V_i (the second Gram-Schmidt pass
+// projects with them), or with itself (NORM).  A block takes a chunk of entries for all
+// right-hand sides, a thread one right-hand side and every DROWS-th entry of the chunk.  Bound by its
+// reads: an Arnoldi step reads the basis three times instead of four (8192 coarse sites with 64
+// degrees of freedom, 32 right-hand sides: the vector kernels of a solve 3.5 -> 2.7 ms).
+template <typename TV, bool NORM> __global__ void __launch_bounds__(DTHR) k_gm_project(GmArgs a, int nvec)
+{
+    __shared__ Z red[DROWS][32];
+    if (!gm_running(a)) return;
+    constexpr int NA = NORM ? 1 : FV;
+    const int G = gridDim.x, k = threadIdx.x & 31, row = threadIdx.x >> 5;
+    const long chunk = (a.dim + G - 1) / G, e0 = blockIdx.x * chunk, e1 = e0 + chunk < a.dim ? e0 + chunk : a.dim;
+    Z acc[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) acc[i] = {0.0, 0.0};
+    if (k < a.ldc) {
+        Z h[FV];
+#pragma unroll
+        for (int i = 0; i < FV; ++i) {
+            h[i] = {0.0, 0.0};
+            if (i < nvec) h[i] = a.hcur[(long)k * (a.m + 1) + i];
+        }
+        for (long e = e0 + row; e < e1; e += DROWS) {
+            const long o = cre(a, e, k);
+            TV vr[FV], vi[FV];
+#pragma unroll
+            for (int i = 0; i < FV; ++i)
+                if (i < nvec) {
+                    const TV *v = (const TV *)a.V + (long)i * a.cvlen;
+                    vr[i] = v[o];
+                    vi[i] = v[o + a.ldc];
+                }
+            double wr = a.w[o], wi = a.w[o + a.ldc];
+#pragma unroll
+            for (int i = 0; i < FV; ++i)
+                if (i < nvec) {
+                    const Z p = zmul(h[i], {load_as<double>(&vr[i]), load_as<double>(&vi[i])});
+                    wr -= p.re;
+                    wi -= p.im;
+                }
+            const float fr = (float)wr, fi = (float)wi;
+            a.w[o] = fr;
+            a.w[o + a.ldc] = fi;
+            const Z y = {fr, fi};
+            if (NORM) {
+                const Z p = zconjmul(y, y);
+                acc[0].re += p.re;
+                acc[0].im += p.im;
+            } else {
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+                    if (i < nvec) {
+                        const Z p = zconjmul({load_as<double>(&vr[i]), load_as<double>(&vi[i])}, y);
+                        acc[i].re += p.re;
+                        acc[i].im += p.im;
+                    }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        if (!NORM && i >= nvec) break;
+        __syncthreads();
+        red[row][k] = acc[i];
+        __syncthreads();
+        if (row == 0 && k < a.ldc) {
+            Z t = red[0][k];
+            for (int r = 1; r < DROWS; ++r) {
+                t.re += red[r][k].re;
+                t.im += red[r][k].im;
+            }
+            a.part[((long)i * G + blockIdx.x) * a.ldc + k] = t;
+        }
+    }
+}
+
 // V_dst = src * scale[k] (rounded to the basis type); dst32 (nullable): the same values as FP32
 template <typename TV>
 __global__ void __launch_bounds__(GTHR) k_gm_scale(GmArgs a, const float *src, TV *dst, float *dst32, int gated)
@@ -342,7 +421,7 @@ size_t gm_layout(const mrhs_op *op, int n_tv, int n, int m, char *base, GmArgs *
     char *V = take((size_t)vsz * cvlen * (m + 1));
     char *v32 = vsz == 4 ? nullptr : take(sizeof(float) * cvlen);
     char *w = take(sizeof(float) * cvlen);
-    char *part = take(sizeof(Z) * (size_t)GPART * ldc);
+    char *part = take(sizeof(Z) * (size_t)std::max(GPART, FBLK * std::min(FV, m)) * ldc);
     char *hcur = take(sizeof(Z) * (size_t)ldc * (m + 1));
     char *H = take(sizeof(Z) * (size_t)ldc * (m + 1) * m);
     char *g = take(sizeof(Z) * (size_t)ldc * (m + 1));
@@ -483,13 +562,18 @@ int gmres_run(GmArgs &a, const float *b, float *u, int m, double *res_out, int32
     TV *V = (TV *)a.V;
 #define GM_CHECK(what) \
     if (int rc = hip_check(hipGetLastError(), what)) return rc
+    auto finish = [&](int G, int nvec, int col, int step) {
+        hipLaunchKernelGGL(k_gm_finish, dim3((nvec * a.ldc * FR + 255) / 256), dim3(256), 0, st, a, G, nvec, col, step);
+        return hip_check(hipGetLastError(), "k_gm_finish launch");
+    };
+    // blocks of the fused projection: at least 4 entries per thread
+    const int G2 = (int)std::max<long>(1, std::min<long>((a.dim + 4 * DROWS - 1) / (4 * DROWS), FBLK));
     auto dots = [&](auto X, long xstride, int nvec, const float *y, int col, int step) {
         using TX = std::remove_const_t<std::remove_pointer_t<decltype(X)>>;
         const int G = gm_blocks(a, nvec);
         hipLaunchKernelGGL(k_gm_dots<TX>, dim3(G, nvec), dim3(DTHR), 0, st, a, X, xstride, y, step != GM_START ? 1 : 0);
         if (int rc = hip_check(hipGetLastError(), "k_gm_dots launch")) return rc;
-        hipLaunchKernelGGL(k_gm_finish, dim3((nvec * a.ldc * FR + 255) / 256), dim3(256), 0, st, a, G, nvec, col, step);
-        return hip_check(hipGetLastError(), "k_gm_finish launch");
+        return finish(G, nvec, col, step);
     };
     // beta, V_0
     if (int rc = dots(b, 0L, 1, b, 0, GM_START)) return rc;
@@ -501,12 +585,23 @@ int gmres_run(GmArgs &a, const float *b, float *u, int m, double *res_out, int32
         // the operator's input: the basis vector itself, or its FP32 copy for a binary16 basis
         const float *vj = a.v32 ? a.v32 : (const float *)(V + (long)j * a.cvlen);
         if (int rc = apply(vj, a.w)) return rc;
-        for (int pass = 0; pass < 2; ++pass) {
+        if (int rc = dots((const TV *)V, a.cvlen, j + 1, a.w, j, GM_PROJECT)) return rc;
+        if (j < FV) {
+            // up to FV basis vectors: each projection with the inner products that follow it
+            hipLaunchKernelGGL((k_gm_project<TV, false>), dim3(G2), dim3(DTHR), 0, st, a, j + 1);
+            GM_CHECK("k_gm_project launch");
+            if (int rc = finish(G2, j + 1, j, GM_PROJECT)) return rc;
+            hipLaunchKernelGGL((k_gm_project<TV, true>), dim3(G2), dim3(DTHR), 0, st, a, j + 1);
+            GM_CHECK("k_gm_project launch");
+            if (int rc = finish(G2, 1, j, GM_NORM)) return rc;
+        } else {
+            hipLaunchKernelGGL(k_gm_axpy<TV>, dim3(eb), dim3(GTHR), 0, st, a, j + 1);
+            GM_CHECK("k_gm_axpy launch");
             if (int rc = dots((const TV *)V, a.cvlen, j + 1, a.w, j, GM_PROJECT)) return rc;
             hipLaunchKernelGGL(k_gm_axpy<TV>, dim3(eb), dim3(GTHR), 0, st, a, j + 1);
             GM_CHECK("k_gm_axpy launch");
+            if (int rc = dots((const float *)a.w, 0L, 1, a.w, j, GM_NORM)) return rc;
         }
-        if (int rc = dots((const float *)a.w, 0L, 1, a.w, j, GM_NORM)) return rc;
         hipLaunchKernelGGL(k_gm_scale<TV>, dim3(eb), dim3(GTHR), 0, st, a, (const float *)a.w, V + (long)(j + 1) * a.cvlen,
                            a.v32, 1);
         GM_CHECK("k_gm_scale launch");
