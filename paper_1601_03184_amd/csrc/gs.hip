@@ -24,7 +24,6 @@
 // MFMA lane layout of v_mfma_f64_16x16x4f64 (measured on gfx950): lane l supplies A[l%16][l/16]
 // and B[l/16][l%16] and holds D[l/16 + 4r][l%16] in accumulator register r.
 #include <algorithm>
-#include <climits>
 
 #include "launch.h"
 
@@ -72,47 +71,74 @@ __device__ inline RowBlock row_block(int B, int nbq, int h, uint32_t cstr)
     return {(uint32_t)(2 * (6 * h + q)) * cstr, 16 * (B - q * nbq)};
 }
 
-// G (NP x NP, upper triangle, in place) -> R with G = R^dag R.  Flags a pivot that falls to
-// <= 1e-14 of the column's original squared norm, i.e. T_kk <= 1e-7 ||v_k||: the Gram
-// matrix squares the condition number, so below that level CholQR cannot resolve the
+// G (NP x NP, upper triangle, in place) -> R with G = R^dag R, and rd[j] = 1 / R[j][j].  Flags a
+// pivot that falls to <= 1e-14 of the column's original squared norm, i.e. T_kk <= 1e-7 ||v_k||:
+// the Gram matrix squares the condition number, so below that level CholQR cannot resolve the
 // column (an exactly dependent column leaves a pivot of order eps ||v_k||^2, of either
 // sign).  A flagged pivot is replaced by 1 so that no NaN or Inf is produced.  Padding
 // columns (beyond n_tv) get R = 1 on the diagonal and 0 elsewhere.
-__device__ void cholesky_inplace(Cplx *G, const double *diag0, int N, int NP, int *bad)
+// A step subtracts conj(G[j][k]) G[j][l] / pivot from the rows below with row j as it is (one barrier
+// and one reciprocal per step); the rows are scaled to R at the end.  Threads form a 16 x 16 grid
+// over (k, l).
+template <int NP> __device__ void cholesky_inplace(Cplx *G, const double *diag0, double *rd, int N, int *bad)
 {
+    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
     for (int j = 0; j < NP; ++j) {
         __syncthreads();
         const double piv = G[j * NP + j].re;
         const bool pad = j >= N;
         const bool deficient = !pad && !(piv > 1e-14 * diag0[j]);
-        const double d = (deficient || pad) ? 1.0 : sqrt(piv);
-        if (threadIdx.x == 0 && deficient) *bad = 1;
-        __syncthreads();
-        for (int l = j + threadIdx.x; l < NP; l += blockDim.x) {
-            Cplx v = G[j * NP + l];
-            if (l == j) v = {d, 0.0};
-            else v = pad ? Cplx{0.0, 0.0} : Cplx{v.re / d, v.im / d};
-            G[j * NP + l] = v;
+        const double p = deficient || pad ? 1.0 : piv, ip = 1.0 / p;
+        if (threadIdx.x == 0) {
+            if (deficient) *bad = 1;
+            rd[j] = p;
         }
-        __syncthreads();
-        const int m = NP - j - 1;
-        for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
-            const int k = j + 1 + e / m, l = j + 1 + e % m;
-            if (l < k) continue;
-            const Cplx rk = G[j * NP + k], rl = G[j * NP + l];
-            // G[k][l] -= conj(R[j][k]) R[j][l]
-            G[k * NP + l].re -= rk.re * rl.re + rk.im * rl.im;
-            G[k * NP + l].im -= rk.re * rl.im - rk.im * rl.re;
+        if (pad) continue;  // its row is zero
+#pragma unroll
+        for (int a = 0; a < NP / 16; ++a) {
+            const int k = ty + 16 * a;
+            if (k <= j) continue;
+            const Cplx rk = {G[j * NP + k].re * ip, G[j * NP + k].im * ip};
+#pragma unroll
+            for (int b = a; b < NP / 16; ++b) {
+                const int l = tx + 16 * b;
+                if (l < k) continue;
+                const Cplx rl = G[j * NP + l];
+                // G[k][l] -= conj(R[j][k]) R[j][l]
+                G[k * NP + l].re -= rk.re * rl.re + rk.im * rl.im;
+                G[k * NP + l].im -= rk.re * rl.im - rk.im * rl.re;
+            }
         }
     }
     __syncthreads();
+    if (threadIdx.x < NP) rd[threadIdx.x] = 1.0 / sqrt(rd[threadIdx.x]);
+    __syncthreads();
+    for (int e = threadIdx.x; e < NP * NP; e += NTHR) {
+        const int j = e / NP, l = e % NP;
+        if (l < j) continue;
+        const double r = rd[j];
+        if (l == j) G[e] = {1.0 / r, 0.0};
+        else if (j >= N) G[e] = {0.0, 0.0};
+        else G[e] = {G[e].re * r, G[e].im * r};
+    }
+    __syncthreads();
+}
+
+// v plus the value of the lane whose index differs in bit log2(O), O = 1, 2, 4, the sums over the lower
+// bits taken first (with 4, the mirror of the 8 lanes)
+template <int O> __device__ inline double quad_sum(double v)
+{
+    constexpr int ctrl = O == 1 ? 0xB1 : O == 2 ? 0x4E : 0x141;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, false);
+    return v + __hiloint2double(hi, lo);
 }
 
 // X = R^-1 for upper-triangular R (NP x NP in LDS).  Column l is solved by 8 lanes of one
 // wavefront, bottom row first: X[k][l] = (delta_kl - sum_{k<j<=l} R[k][j] X[j][l]) / R[k][k];
 // lane `sub` keeps rows j = sub (mod 8) of the column in registers, the partial sums are
-// combined with shuffles.
-template <int NP> __device__ void tri_inverse(const Cplx *R, Cplx *X)
+// combined across the lanes; rd: the reciprocals of the diagonal.
+template <int NP> __device__ void tri_inverse(const Cplx *R, const double *rd, Cplx *X)
 {
     constexpr int NJ = NP / 8;
     const int l = threadIdx.x >> 3, sub = threadIdx.x & 7;
@@ -134,16 +160,12 @@ template <int NP> __device__ void tri_inverse(const Cplx *R, Cplx *X)
                 }
             }
         }
-        sr += __shfl_xor(sr, 1, 64);
-        si += __shfl_xor(si, 1, 64);
-        sr += __shfl_xor(sr, 2, 64);
-        si += __shfl_xor(si, 2, 64);
-        sr += __shfl_xor(sr, 4, 64);
-        si += __shfl_xor(si, 4, 64);
+        sr = quad_sum<4>(quad_sum<2>(quad_sum<1>(sr)));
+        si = quad_sum<4>(quad_sum<2>(quad_sum<1>(si)));
         if (col && k <= l && sub == (k & 7)) {
-            const double d = R[k * NP + k].re;
-            xr[k >> 3] = (k == l ? 1.0 : -sr) / d;
-            xi[k >> 3] = (k == l ? 0.0 : -si) / d;
+            const double d = rd[k];
+            xr[k >> 3] = k == l ? d : -sr * d;
+            xi[k >> 3] = k == l ? 0.0 : -si * d;
         }
     }
     if (col) {
@@ -434,7 +456,8 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     Cplx *G = X1 + NP * NP;                      // Gram matrix / Cholesky factor / R1^-1 R2^-1
     Cplx *X2 = G + NP * NP;                      // R2^-1
     double *diag0 = reinterpret_cast<double *>(X2 + NP * NP);
-    size_t *coff = reinterpret_cast<size_t *>(diag0 + NP);
+    double *rd = diag0 + NP;                     // 1 / R[j][j]
+    size_t *coff = reinterpret_cast<size_t *>(rd + NP);
     uint32_t *sbase = reinterpret_cast<uint32_t *>(coff + NP);
     __shared__ int bad;
     __shared__ double red[NW];
@@ -476,8 +499,8 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     gram_reduce<NT>(acc, G, NP, lane, wave);
     gram_fix_diag<NT>(G, NP);
     for (int k = threadIdx.x; k < NP; k += blockDim.x) diag0[k] = G[k * NP + k].re;
-    cholesky_inplace(G, diag0, N, NP, &bad);
-    tri_inverse<NP>(G, X1);
+    cholesky_inplace<NP>(G, diag0, rd, N, &bad);
+    tri_inverse<NP>(G, rd, X1);
 
     const Cplx *M = X1;  // Q = V M
     if (sizeof(Tq) == 8 || bad || !one_pass_enough<NP>(X1, diag0, N, red)) {
@@ -517,8 +540,8 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
         gram_reduce<NT>(acc, G, NP, lane, wave);
         gram_fix_diag<NT>(G, NP);
         for (int k = threadIdx.x; k < NP; k += blockDim.x) diag0[k] = 1.0;
-        cholesky_inplace(G, diag0, N, NP, &bad);
-        tri_inverse<NP>(G, X2);
+        cholesky_inplace<NP>(G, diag0, rd, N, &bad);
+        tri_inverse<NP>(G, rd, X2);
         tri_product(X1, X2, G, NP);  // G <- R1^-1 R2^-1
         M = G;
     }
@@ -553,18 +576,23 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
         });
     }
     __syncthreads();
-    if (threadIdx.x == 0 && bad && a.status) atomicMin(a.status, 1 + (int)blockIdx.x);
+    if (threadIdx.x == 0 && bad && a.status) {
+        // the smallest of the flagged halves; 0 (none) counts as the largest, as unsigned v - 1
+        const unsigned v = 1u + blockIdx.x;
+        unsigned *w = reinterpret_cast<unsigned *>(a.status), old = *w;
+        while (old - 1u > v - 1u) {
+            const unsigned seen = atomicCAS(w, old, v);
+            if (seen == old) break;
+            old = seen;
+        }
+    }
 }
 
-__global__ void k_status_init(int32_t *s) { *s = INT_MAX; }
-__global__ void k_status_final(int32_t *s)
-{
-    if (*s == INT_MAX) *s = 0;
-}
+__global__ void k_status_init(int32_t *s) { *s = 0; }
 
 size_t gs_lds(int NP)
 {
-    return sizeof(Cplx) * 3 * NP * NP + (sizeof(double) + sizeof(size_t)) * NP + 4 * SCH;
+    return sizeof(Cplx) * 3 * NP * NP + (2 * sizeof(double) + sizeof(size_t)) * NP + 4 * SCH;
 }
 
 template <typename Tv, typename Tq, int NT> int launch_typed(const GsArgs &a, int n_agg, size_t max_lds, hipStream_t st)
@@ -621,9 +649,5 @@ int launch_gs(const mrhs_op *op, const void *V, int vdt, void *Q, int qdt, int n
     else if (vdt == MRHS_DTYPE_F32) rc = launch_v<float>(a, qdt, op->n_agg, op->max_lds, st);
     else rc = launch_v<__half>(a, qdt, op->n_agg, op->max_lds, st);
     if (rc) return rc;
-    if (status) {
-        hipLaunchKernelGGL(k_status_final, dim3(1), dim3(1), 0, st, status);
-        if (int rc2 = hip_check(hipGetLastError(), "k_status_final launch")) return rc2;
-    }
     return MRHS_OK;
 }
