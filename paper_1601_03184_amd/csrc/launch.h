@@ -11,8 +11,11 @@ int launch_build_fields(mrhs_op *op, const double *links_canon, double m0, doubl
 int launch_pack(const mrhs_op *op, const double *canon, void *native, int dtype, int n_rhs, int *flag, hipStream_t st);
 int launch_unpack(const mrhs_op *op, const void *native, int dtype, double *canon, int n_rhs, hipStream_t st);
 int launch_dirac(const mrhs_op *op, const void *x, void *y, int n_rhs, hipStream_t st);
+// x_last (nullable, one operator): the last sweep writes its x there instead of into x; it may be b
+// where sap_last_sweep_apart holds (a sweep after the first reads neither b nor the neighbours' x)
 int launch_sap(const mrhs_op *op, const void *b, void *x, int n_rhs, int n_sap, int n_mr, void *ws, hipStream_t st,
-               bool guess = false);
+               bool guess = false, void *x_last = nullptr);
+bool sap_last_sweep_apart(const mrhs_op *op, int n_sap);
 int launch_residual(const mrhs_op *op, const void *b, const void *x, int n_rhs, double *out, void *ws, size_t ws_bytes,
                     hipStream_t st);
 // the same with the library's static per-device scratch instead of a workspace (no allocation)
@@ -24,7 +27,7 @@ int launch_coarse(const mrhs_op *op, const void *Q, int qdt, int n_tv, void *Dc,
 size_t ws_bytes_sap(const mrhs_op *op, int n_rhs);
 size_t ws_bytes_sap_batched(const mrhs_op *const *ops, int n, const int32_t *n_rhs);
 int launch_sap_batched(const mrhs_op *const *ops, int n, const void *const *b, void *const *x, const int32_t *n_rhs,
-                       int n_sap, int n_mr, void *ws, hipStream_t st, bool guess = false);
+                       int n_sap, int n_mr, void *ws, hipStream_t st, bool guess = false, void *x_last = nullptr);
 size_t ws_bytes_residual(const mrhs_op *op, int n_rhs);
 size_t ws_bytes_residual_least(const mrhs_op *op, int n_rhs);  // without the short grids' per-chunk partial sums
 size_t ws_bytes_gs(const mrhs_op *op, int n_tv);

@@ -60,8 +60,11 @@ int launch_refine(const mrhs_op *op, void *V, int n_tv, const void *Q, int qdt, 
     if (int rc = launch_restrict(op, Q, qdt, n_tv, V, vdt, w.vc, n_tv, st)) return rc;
     if (int rc = launch_coarse_solve(op, Dc, n_tv, w.vc, w.uc, n_tv, m, tol, nullptr, nullptr, w.gm, st)) return rc;
     if (int rc = launch_prolong(op, Q, qdt, n_tv, w.uc, w.x, vdt, n_tv, st)) return rc;
-    // the smoother on D x = v from the coarse-grid correction; the result replaces v
-    if (int rc = launch_sap(op, V, w.x, n_tv, n_sap, n_mr, w.sap, st, true)) return rc;
+    // the smoother on D x = v from the coarse-grid correction; the result replaces v, written there by
+    // the last sweep where that reads v no more
+    const bool apart = sap_last_sweep_apart(op, n_sap);
+    if (int rc = launch_sap(op, V, w.x, n_tv, n_sap, n_mr, w.sap, st, true, apart ? V : nullptr)) return rc;
+    if (apart) return MRHS_OK;
     const long nel = (long)native_elems(op, n_tv);
     switch (vdt) {
     case MRHS_DTYPE_F64:

@@ -84,6 +84,7 @@ template <typename Ts, typename Tc> struct SapArgs {
     const Ts *b;
     const Ts *xr;           // where neighbours' x is read (x itself, or a snapshot)
     Ts *x;
+    Ts *xw;                 // where the new x is written (x itself, or a caller's other vectors)
     // kept per block between the visits of a colour (arithmetic type, component vectors of 16
     // bytes: SigIndex).  inc (no block has a neighbour of its own colour): the block residual rho
     // after the last visit; a later visit's residual is rho minus the face hops of the change the
@@ -618,7 +619,7 @@ __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, i
     if (on[2]) face_link<2>(a, blk, off, bcp, ff[2], l0);
     if (on[3]) face_link<3>(a, blk, off, bcp, ff[3], l1);
     sched_fence();
-    store_spinor(g, a.x, grp, blk, off, tt, xn);
+    store_spinor(g, a.xw, grp, blk, off, tt, xn);
     if (a.sig_out && a.inc) keep();
     if (on[0]) face_store<0>(a, grp, blk, lcp, tt, ff[0], w[0]);
     if (on[1]) face_store<1>(a, grp, blk, lcp, tt, ff[1], w[1]);
@@ -1188,7 +1189,7 @@ int launch_batched(const SapBatch<Ts, Tc> &B, int threads, size_t lds, hipStream
 
 template <typename Ts, typename Tc>
 int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b, void *const *x, const int32_t *n_rhs,
-                         int n_sap, int n_mr, char *ws, bool guess, hipStream_t st)
+                         int n_sap, int n_mr, char *ws, bool guess, void *x_last, hipStream_t st)
 {
     // one tile for the whole batch: the smallest of the operators' tiles (all divide S)
     int T = 4, maxVb = 0;
@@ -1272,6 +1273,7 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
                 a.sig_in = (a.inc || !eo) && s > 0;
                 a.sig_out = (a.inc || !eo) && s + 1 < n_sap;
                 a.xr = a.x;
+                a.xw = x_last && s + 1 == n_sap ? (Ts *)x_last : a.x;
                 if (a.mode == 2 && op->odd_blocks) {
                     C.src[C.n_inst] = a.x;
                     C.dst[C.n_inst] = snap[k];
@@ -1327,23 +1329,25 @@ size_t ws_bytes_sap_batched(const mrhs_op *const *ops, int n, const int32_t *n_r
 }
 
 int launch_sap_batched(const mrhs_op *const *ops, int n, const void *const *b, void *const *x, const int32_t *n_rhs,
-                       int n_sap, int n_mr, void *ws, hipStream_t st, bool guess)
+                       int n_sap, int n_mr, void *ws, hipStream_t st, bool guess, void *x_last)
 {
     if (n > MAX_BATCH) return set_error(MRHS_EUNSUPPORTED, "more than 8 operators in one batch");
     switch (ops[0]->prec) {
     case MRHS_PREC_F64:
-        return sap_batched_dispatch<double, double>(ops, n, b, x, n_rhs, n_sap, n_mr, (char *)ws, guess, st);
+        return sap_batched_dispatch<double, double>(ops, n, b, x, n_rhs, n_sap, n_mr, (char *)ws, guess, x_last, st);
     case MRHS_PREC_F32:
-        return sap_batched_dispatch<float, float>(ops, n, b, x, n_rhs, n_sap, n_mr, (char *)ws, guess, st);
+        return sap_batched_dispatch<float, float>(ops, n, b, x, n_rhs, n_sap, n_mr, (char *)ws, guess, x_last, st);
     default:
-        return sap_batched_dispatch<__half, float>(ops, n, b, x, n_rhs, n_sap, n_mr, (char *)ws, guess, st);
+        return sap_batched_dispatch<__half, float>(ops, n, b, x, n_rhs, n_sap, n_mr, (char *)ws, guess, x_last, st);
     }
 }
 
 size_t ws_bytes_sap(const mrhs_op *op, int n_rhs) { return ws_bytes_sap_batched(&op, 1, &n_rhs); }
 
 int launch_sap(const mrhs_op *op, const void *b, void *x, int n_rhs, int n_sap, int n_mr, void *ws, hipStream_t st,
-               bool guess)
+               bool guess, void *x_last)
 {
-    return launch_sap_batched(&op, 1, &b, &x, &n_rhs, n_sap, n_mr, ws, st, guess);
+    return launch_sap_batched(&op, 1, &b, &x, &n_rhs, n_sap, n_mr, ws, st, guess, x_last);
 }
+
+bool sap_last_sweep_apart(const mrhs_op *op, int n_sap) { return n_sap > 1 && !op->odd_blocks; }
