@@ -121,12 +121,12 @@ int dirac_apply_mrhs(const mrhs_op *op, const void *x, void *y, int32_t n_rhs, v
  * vectors of the op's element type, x != b; x is overwritten.  ws: workspace of at
  * least mrhs_workspace_bytes(op, n_rhs) bytes.  It carries a block's residual from one visit
  * to the next, so that a later visit forms only the hops across the block's faces (the same
- * residual up to rounding order): when no direction holds an odd number (> 1) of blocks, the block
- * residual rho_j after its MR steps (one vector set in the arithmetic type) and every block's
- * outgoing face hops of its last change of x (12 numbers per face site and right-hand side), a
- * later residual being rho_j minus the neighbours' face hops; otherwise, with the plain MR block
- * solver, sigma_j = b_j - D_j x_j and a snapshot of x, a later residual being sigma_j minus the
- * face hops of x. */
+ * residual up to rounding order): the block residual rho_j after its MR steps (one vector set in
+ * the arithmetic type) and every block's outgoing face hops of its last change of x (12 numbers
+ * per face site and right-hand side), a later residual being rho_j minus the neighbours' face
+ * hops.  When a direction holds an odd number (> 1) of blocks there are two sets of face hops
+ * (the second also takes a snapshot of x in the first sweep from a guess), and FP32 plain MR keeps
+ * sigma_j = b_j - D_j x_j and the face hops of x instead. */
 int sap_smooth_mrhs(const mrhs_op *op, const void *b, void *x, int32_t n_rhs, int32_t n_sap, int32_t n_mr,
                     void *ws, size_t ws_bytes, void *stream);
 

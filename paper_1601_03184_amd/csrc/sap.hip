@@ -78,7 +78,6 @@ template <typename Ts, typename Tc> struct SapArgs {
     const int32_t *blocks;  // block ids of this colour
     int nblocks;            // number of blocks of this colour
     int ntiles;             // right-hand-side tiles per block
-    int colour;
     int mode;               // 0: x = 0 everywhere; 1: x = 0 on this colour's blocks; 2: general
     int n_mr;
     const Ts *b;
@@ -86,17 +85,23 @@ template <typename Ts, typename Tc> struct SapArgs {
     Ts *x;
     Ts *xw;                 // where the new x is written (x itself, or a caller's other vectors)
     // kept per block between the visits of a colour (arithmetic type, component vectors of 16
-    // bytes: SigIndex).  inc (no block has a neighbour of its own colour): the block residual rho
-    // after the last visit; a later visit's residual is rho minus the face hops of the change the
-    // other colour made in between, which the other colour left in `face`.  Otherwise
-    // sigma = b - D_j x_j, a later visit's residual being sigma - (face hops of x).
+    // bytes: sig_ptr).  inc: the block residual rho after the last visit; a later visit's residual is
+    // rho minus the face hops of the neighbours' changes of x since.  Every neighbour has changed
+    // once since then, the last time it was visited, and left its hops of that change in the
+    // face buffer.  Otherwise (FP32 plain MR where a block can neighbour one of its own colour)
+    // sigma = b - D_j x_j, a later visit's residual being sigma minus the face hops of x, which
+    // then are what the face buffer holds.
     Tc *sig;
     int sig_in;             // this colour's rho or sigma is valid (read it instead of forming b - D x)
     int sig_out;            // write it for the next visit of this colour
     int inc;
-    // inc: every block's outgoing hops across its faces, of its last change of x: per face site the
-    // two spin rows (1 -+ g_mu) U_mu applied to the change, which the neighbour adds to its residual
-    Tc *face;
+    // Every block's outgoing hops across its faces: per face site the two spin rows (1 -+ g_mu)
+    // U_mu applied to its last change of x (or to x), which the neighbour adds up.  With an odd number
+    // of blocks in a direction the blocks at its ends have the same colour and are visited together: the
+    // buffers then alternate from sweep to sweep, a visit reading neighbours of the other colour
+    // from face_o, those of its own colour from face_s (null: not visited yet, x = 0).
+    Tc *face_w;
+    const Tc *face_o, *face_s;
     FaceGeo fg;
     int f_out;              // write this visit's faces (a later visit reads them)
     // even-odd block solver: A^-1 per site (clover layout), block offsets in parity order,
@@ -360,12 +365,12 @@ template <typename Tc> struct HalfSpinor {
 };
 
 // first component vector of a site's entry on face `minus` of direction MU of block blk
-template <int MU, typename Ts, typename Tc>
-__device__ __forceinline__ typename V16<Tc>::type *face_ptr(const SapArgs<Ts, Tc> &a, int grp, int blk, bool minus, int f, int tt)
+template <int MU, typename Ts, typename Tc, typename Tp>
+__device__ __forceinline__ auto face_ptr(const SapArgs<Ts, Tc> &a, Tp *face, int grp, int blk, bool minus, int f, int tt)
 {
-    using V = typename V16<Tc>::type;
+    using V = std::conditional_t<std::is_const<Tp>::value, const typename V16<Tc>::type, typename V16<Tc>::type>;
     const KGeo &g = a.g;
-    V *base = reinterpret_cast<V *>(a.face) + ((size_t)grp * g.nblk + blk) * (size_t)(a.fg.per_blk * g.S);
+    V *base = reinterpret_cast<V *>(face) + ((size_t)grp * g.nblk + blk) * (size_t)(a.fg.per_blk * g.S);
     return base + (uint32_t)((a.fg.base[MU] + (minus ? (12 / V16<Tc>::n) * a.fg.vf[MU] : 0) + f) * g.S + tt);
 }
 
@@ -386,6 +391,12 @@ template <int MU> __device__ __forceinline__ int face_nbr(const KGeo &g, int blk
     return minus ? blk + (bc > 0 ? -g.bstr[MU] : wrap) : blk + (bc + 1 < g.nb[MU] ? g.bstr[MU] : -wrap);
 }
 
+// the block across the +MU face (fwd) or the -MU face has the block's own colour
+template <int MU> __device__ __forceinline__ bool own_colour(const KGeo &g, int bc, bool fwd)
+{
+    return (g.nb[MU] & 1) && bc == (fwd ? g.nb[MU] - 1 : 0);
+}
+
 // What the neighbour across the +MU face (fwd) or the -MU face left for this site
 template <int MU, typename Ts, typename Tc>
 __device__ __forceinline__ void face_load(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp, int tt, bool fwd,
@@ -395,7 +406,8 @@ __device__ __forceinline__ void face_load(const SapArgs<Ts, Tc> &a, int grp, int
     const int bc = unpack_coord(bcp, MU);
     // both neighbours are uniform over the workgroup, the choice is the lane's
     const int nf = face_nbr<MU>(a.g, blk, bc, false), nb = face_nbr<MU>(a.g, blk, bc, true);
-    const typename V16<Tc>::type *p = face_ptr<MU>(a, grp, fwd ? nf : nb, fwd, face_index<MU>(a, lcp), tt);
+    const Tc *bf = own_colour<MU>(a.g, bc, true) ? a.face_s : a.face_o, *bb = own_colour<MU>(a.g, bc, false) ? a.face_s : a.face_o;
+    const auto *p = face_ptr<MU>(a, fwd ? bf : bb, grp, fwd ? nf : nb, fwd, face_index<MU>(a, lcp), tt);
     const uint32_t str = (uint32_t)(a.fg.vf[MU] * a.g.S);
 #pragma unroll
     for (int v = 0; v < 12 / n; ++v) {
@@ -438,18 +450,29 @@ __device__ __forceinline__ void face_round(const SapArgs<Ts, Tc> &a, int grp, in
 {
     const KGeo &g = a.g;
     HalfSpinor<Tc> w[ND];
-    auto fwd = [&](int mu) __attribute__((always_inline)) { return unpack_coord(lcp, mu) + 1 == g.b[mu] && g.nb[mu] > 1; };
-    auto bwd = [&](int mu) __attribute__((always_inline)) { return unpack_coord(lcp, mu) == 0 && g.nb[mu] > 1; };
+    // the lane is on the face (and the neighbour there has been visited)
+    auto fwd = [&](auto m) __attribute__((always_inline)) {
+        constexpr int MU = decltype(m)::value;
+        return unpack_coord(lcp, MU) + 1 == g.b[MU] && g.nb[MU] > 1 &&
+               (a.face_s || !own_colour<MU>(g, unpack_coord(bcp, MU), true));
+    };
+    auto bwd = [&](auto m) __attribute__((always_inline)) {
+        constexpr int MU = decltype(m)::value;
+        return unpack_coord(lcp, MU) == 0 && g.nb[MU] > 1 &&
+               (a.face_s || !own_colour<MU>(g, unpack_coord(bcp, MU), false));
+    };
     auto load = [&](auto m) __attribute__((always_inline)) {
         constexpr int MU = MU0 + decltype(m)::value;
-        const bool ff = fwd(MU);
-        if (ff || bwd(MU)) face_load<MU>(a, grp, blk, bcp, lcp, tt, ff, w[MU - MU0]);
+        std::integral_constant<int, MU> mu;
+        const bool ff = fwd(mu);
+        if (ff || bwd(mu)) face_load<MU>(a, grp, blk, bcp, lcp, tt, ff, w[MU - MU0]);
     };
     auto add = [&](auto m) __attribute__((always_inline)) {
         constexpr int MU = MU0 + decltype(m)::value;
-        const bool ff = fwd(MU);
-        if (ff || bwd(MU)) face_add<MU>(w[MU - MU0], ff ? Tc(-1) : Tc(1), r);
-        if (g.b[MU] == 1 && g.nb[MU] > 1) {  // uniform: the site is on the backward face as well
+        std::integral_constant<int, MU> mu;
+        const bool ff = fwd(mu);
+        if (ff || bwd(mu)) face_add<MU>(w[MU - MU0], ff ? Tc(-1) : Tc(1), r);
+        if (g.b[MU] == 1 && ff && bwd(mu)) {  // uniform: the site is on the backward face as well
             HalfSpinor<Tc> v;
             face_load<MU>(a, grp, blk, bcp, lcp, tt, false, v);
             face_add<MU>(v, Tc(1), r);
@@ -470,24 +493,17 @@ __device__ __forceinline__ void face_round(const SapArgs<Ts, Tc> &a, int grp, in
     }
 }
 
-// residual of a visit that reads faces: r (the kept rho, or b) minus the face hops, which are summed
-// in the order of the full stencil
+// f = the hops across the block's faces, summed in the order of the full stencil
 template <typename Ts, typename Tc>
-__device__ __forceinline__ void face_residual(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp, int tt,
-                                     Spinor<Tc> &r)
+__device__ __forceinline__ void face_sum(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp, int tt,
+                                         Spinor<Tc> &f)
 {
-    Spinor<Tc> f;
     spinor_zero(f);
     if constexpr (sizeof(Tc) == 4) {
         face_round<0, 4>(a, grp, blk, bcp, lcp, tt, f);
     } else {
         face_round<0, 2>(a, grp, blk, bcp, lcp, tt, f);
         face_round<2, 2>(a, grp, blk, bcp, lcp, tt, f);
-    }
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        r.re[c] -= f.re[c];
-        r.im[c] -= f.im[c];
     }
 }
 
@@ -553,7 +569,7 @@ __device__ __forceinline__ void face_store(const SapArgs<Ts, Tc> &a, int grp, in
                                            const HalfSpinor<Tc> &w)
 {
     constexpr int n = V16<Tc>::n;
-    typename V16<Tc>::type *p = face_ptr<MU>(a, grp, blk, !fwd, face_index<MU>(a, lcp), tt);
+    typename V16<Tc>::type *p = face_ptr<MU>(a, a.face_w, grp, blk, !fwd, face_index<MU>(a, lcp), tt);
     const uint32_t str = (uint32_t)(a.fg.vf[MU] * a.g.S);
 #pragma unroll
     for (int v = 0; v < 12 / n; ++v) {
@@ -568,9 +584,9 @@ __device__ __forceinline__ void face_store(const SapArgs<Ts, Tc> &a, int grp, in
     }
 }
 
-// The end of a visit on one site: x (+)= e, and with the incremental residual the faces of the
-// change of the stored x (the correction as rounded to the storage type) and, kept, rho for later
-// visits (keep(): stores it).  A load waits for every store issued before it, so the loads come
+// The end of a visit on one site: x (+)= e, the faces of the change of the stored x (the correction
+// as rounded to the storage type; without inc of x) and, with inc, rho for later visits (keep():
+// stores it).  A load waits for every store issued before it, so the loads come
 // first, in two rounds (the old x and the links of directions 0, 1; the links of 2, 3), and the
 // stores after the last of them.
 template <typename Ts, typename Tc, typename Keep>
@@ -599,8 +615,12 @@ __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, i
             xn.re[c] = xo.re[c] + e.re[c];
             xn.im[c] = xo.im[c] + e.im[c];
             Ts sr = store_as<Ts>(xn.re[c]), si = store_as<Ts>(xn.im[c]);
-            e.re[c] = load_as<Tc>(&sr) - xo.re[c];
-            e.im[c] = load_as<Tc>(&si) - xo.im[c];
+            e.re[c] = load_as<Tc>(&sr);
+            e.im[c] = load_as<Tc>(&si);
+            if (a.inc) {
+                e.re[c] -= xo.re[c];
+                e.im[c] -= xo.im[c];
+            }
         }
     } else {
 #pragma unroll
@@ -719,36 +739,32 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
     }
 
     // 1. residual on the block: b - D x, or the kept rho or sigma minus the face hops
-    const int colour = a.colour, mode = a.mode;
-    const uint32_t *bcs = a.blk_coords;
-    const uint32_t bcp = bcs[blk];
-    auto skip = [=](int nblk) { return mode == 1 && block_colour(g, bcs, nblk) == colour; };
+    const uint32_t bcp = a.blk_coords[blk];
     // Without inc, the face hops F of this visit (what the other blocks' x contribute) are what
     // sigma for the next visit needs as well (sigma' = rho + F, step 4): where step 1 forms them on
     // their own they are kept in this site's sigma slot until step 4.
-    const bool keep_f = !a.inc && a.sig_out && a.sig_in;
+    const bool by_faces = a.sig_in || a.mode == 1, keep_f = !a.inc && a.sig_out && by_faces;
     if (active) {
         Spinor<Tc> r;
         if (a.mode == 0) {
             load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
-        } else if (a.inc && (a.sig_in || a.mode == 1)) {
-            // rho minus the other colour's change across the faces; the first visit of the second
-            // colour from zero (x vanishes on the block and the other colour's change is its x)
-            // likewise with b for rho
+        } else if (by_faces) {
+            // the kept rho or sigma, or at the first visit of the second colour from zero (x vanishes on
+            // the block) b, minus what comes across the faces
+            Spinor<Tc> f;
             if (a.sig_in) sig_load(g, a.sig, grp, blk, off, tt, r);
             else load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
-            face_residual(a, grp, blk, bcp, lcp, tt, r);
+            face_sum(a, grp, blk, bcp, lcp, tt, f);
+            if (keep_f) sig_store(g, a.sig, grp, blk, off, tt, f);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                r.re[c] -= f.re[c];
+                r.im[c] -= f.im[c];
+            }
         } else {
             Spinor<Tc> bb;
-            if (a.sig_in) {
-                spinor_zero(r);
-                face_hops_global<Tc>(g, a.links, a.xr, grp, tt, blk, off, bc, lc, r, skip);
-                sig_load(g, a.sig, grp, blk, off, tt, bb);
-                if (keep_f) sig_store(g, a.sig, grp, blk, off, tt, r);
-            } else {
-                dirac_site_global<Tc>(g, a.links, a.clover, a.xr, grp, tt, blk, off, bc, lc, r, skip);
-                load_spinor<Tc>(g, a.b, grp, blk, off, tt, bb);
-            }
+            dirac_site_global<Tc>(g, a.links, a.clover, a.xr, grp, tt, blk, off, bc, lc, r, NoSkip{});
+            load_spinor<Tc>(g, a.b, grp, blk, off, tt, bb);
 #pragma unroll
             for (int c = 0; c < 12; ++c) {
                 r.re[c] = bb.re[c] - r.re[c];
@@ -843,7 +859,7 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
             int bc2[4], lc2[4];
             decode_site(g, a.blk_coords, a.loc_coords, blk, opaque_index(off), bc2, lc2);
             spinor_zero(sg);
-            face_hops_global<Tc>(g, a.links, a.xr, grp, tt, blk, off, bc2, lc2, sg, skip);
+            face_hops_global<Tc>(g, a.links, a.xr, grp, tt, blk, off, bc2, lc2, sg, NoSkip{});
         }
         Spinor<Tc> rr;
         lds_load<Tc>(rho, str, me, rr);
@@ -880,7 +896,7 @@ __device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho,
     hop_fence(h);
 }
 
-// The residual of one site, to LDS.  With inc a later visit starts from what the last one left:
+// The residual of one site, to LDS.  A later visit starts from what the last one left:
 // the Schur residual rho on the even sites (kept in sig) and zero on the odd ones, whose
 // equations that visit's reconstruction solved.
 template <typename Ts, typename Tc, int T>
@@ -891,7 +907,7 @@ __device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, LdsPair<Tc> *rho, i
     Spinor<Tc> r;
     if (a.mode == 0) {
         load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
-    } else if (a.inc && (a.sig_in || a.mode == 1)) {
+    } else if (a.sig_in || a.mode == 1) {
         const uint32_t bcp = a.blk_coords[blk], lcp = a.loc_coords[off];
         const int odd = (unpack_coord(lcp, 0) + unpack_coord(lcp, 1) + unpack_coord(lcp, 2) + unpack_coord(lcp, 3)) & 1;
         if (a.sig_in) {
@@ -900,14 +916,17 @@ __device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, LdsPair<Tc> *rho, i
         } else {
             load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
         }
-        face_residual(a, grp, blk, bcp, lcp, tt, r);
+        Spinor<Tc> f;
+        face_sum(a, grp, blk, bcp, lcp, tt, f);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            r.re[c] -= f.re[c];
+            r.im[c] -= f.im[c];
+        }
     } else {
         int bc[4], lc[4];
         decode_site(g, a.blk_coords, a.loc_coords, blk, off, bc, lc);
-        const int colour = a.colour, mode = a.mode;
-        const uint32_t *bcs = a.blk_coords;
-        auto skip = [=](int nblk) { return mode == 1 && block_colour(g, bcs, nblk) == colour; };
-        dirac_site_global<Tc>(g, a.links, a.clover, a.xr, grp, tt, blk, off, bc, lc, r, skip);
+        dirac_site_global<Tc>(g, a.links, a.clover, a.xr, grp, tt, blk, off, bc, lc, r, NoSkip{});
         Spinor<Tc> bb;
         load_spinor<Tc>(g, a.b, grp, blk, off, tt, bb);
 #pragma unroll
@@ -1093,8 +1112,10 @@ __device__ inline void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile,
 }
 
 // Several operators (lattices of uneven size, each with its own right-hand sides) in one
-// launch per half-sweep: workgroup w (after the XCD remap) belongs to the instance whose
-// range [first[k], first[k+1]) holds it.  Descriptors travel by value in the kernel
+// launch per half-sweep: workgroup w belongs to the instance whose range [first[k], first[k+1])
+// holds it.  The ranges start at multiples of 8, so that every instance is spread over all XCDs in
+// contiguous runs (a run of the whole batch had left one XCD with most of the small lattices'
+// workgroups).  Descriptors travel by value in the kernel
 // arguments, so a captured graph replays without host memory.
 constexpr int MAX_BATCH = 8;
 
@@ -1108,11 +1129,12 @@ template <typename Ts, typename Tc, int T, bool LL>
 __global__ void __launch_bounds__(256 * T, sizeof(Tc) == 4 ? 4 : 1) k_sap_batched(SapBatch<Ts, Tc> B)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int w = xcd_remap(blockIdx.x, B.first[B.n_inst]);
     int k = 0;
-    while (k + 1 < B.n_inst && w >= B.first[k + 1]) ++k;
+    while (k + 1 < B.n_inst && (int)blockIdx.x >= B.first[k + 1]) ++k;
     const SapArgs<Ts, Tc> &a = B.inst[k];
-    const int li = w - B.first[k];
+    const int w = blockIdx.x - B.first[k], n = a.nblocks * a.ntiles;
+    if (w >= n) return;  // padding of an instance's range
+    const int li = xcd_remap(w, n);
     const int bi = li / a.ntiles, tile = li - bi * a.ntiles;
     sap_block<Ts, Tc, T, LL>(a, a.blocks[bi], tile, smem);
 }
@@ -1122,11 +1144,12 @@ template <typename Ts, typename Tc, int T>
 __global__ void __launch_bounds__(128 * T, (sizeof(Tc) == 4 && T == 2) ? 3 : 1) k_sap_batched_eo(SapBatch<Ts, Tc> B)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int w = xcd_remap(blockIdx.x, B.first[B.n_inst]);
     int k = 0;
-    while (k + 1 < B.n_inst && w >= B.first[k + 1]) ++k;
+    while (k + 1 < B.n_inst && (int)blockIdx.x >= B.first[k + 1]) ++k;
     const SapArgs<Ts, Tc> &a = B.inst[k];
-    const int li = w - B.first[k];
+    const int w = blockIdx.x - B.first[k], n = a.nblocks * a.ntiles;
+    if (w >= n) return;  // padding of an instance's range
+    const int li = xcd_remap(w, n);
     const int bi = li / a.ntiles, tile = li - bi * a.ntiles;
     sap_block_eo<Ts, Tc, T>(a, a.blocks[bi], tile, smem);
 }
@@ -1166,6 +1189,13 @@ template <> const double *op_cloverinv<double>(const mrhs_op *op) { return op->c
 template <> const float *op_cloverinv<float>(const mrhs_op *op) { return op->cloverinv32; }
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
+
+// bytes of the second face buffer of a lattice with an odd number of blocks in a direction, and of
+// the snapshot of x in the same place
+template <typename Ts, typename Tc> size_t odd_bytes(const mrhs_op *op, int n_rhs)
+{
+    return align256(std::max(face_elems<Tc>(op, n_rhs) * sizeof(Tc), native_elems(op, n_rhs) * sizeof(Ts)));
+}
 
 template <typename Ts, typename Tc, int T, bool EO, bool LL = false>
 int launch_batched(const SapBatch<Ts, Tc> &B, int threads, size_t lds, hipStream_t st)
@@ -1225,6 +1255,7 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
     B.n_inst = n;
     char *wp = ws;
     Ts *snap[MAX_BATCH] = {};
+    Tc *face[MAX_BATCH][2] = {};
     for (int k = 0; k < n; ++k) {
         const mrhs_op *op = ops[k];
         SapArgs<Ts, Tc> &a = B.inst[k];
@@ -1240,17 +1271,17 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
         a.cloverinv = op_cloverinv<Tc>(op);
         a.eo_sites = op->eo_sites;
         a.Ve = op->k.Vb / 2;
-        if (op->odd_blocks) {
-            snap[k] = (Ts *)wp;
-            wp += align256(native_elems(op, n_rhs[k]) * sizeof(Ts));
-        }
+        a.fg = face_geo<Tc>(op->k);
         a.sig = (Tc *)wp;
         wp += align256(native_elems(op, n_rhs[k]) * sizeof(Tc));
-        a.face = nullptr;
-        a.fg = face_geo<Tc>(op->k);
-        if (!op->odd_blocks) {
-            a.face = (Tc *)wp;
-            wp += align256(face_elems<Tc>(op, n_rhs[k]) * sizeof(Tc));
+        face[k][0] = face[k][1] = (Tc *)wp;
+        wp += align256(face_elems<Tc>(op, n_rhs[k]) * sizeof(Tc));
+        if (op->odd_blocks) {
+            // the second face buffer, first used in the second sweep, shares its space with the
+            // snapshot of x that the first sweep from a guess takes
+            face[k][1] = (Tc *)wp;
+            snap[k] = (Ts *)wp;
+            wp += odd_bytes<Ts, Tc>(op, n_rhs[k]);
         }
     }
     for (int s = 0; s < n_sap; ++s)
@@ -1260,28 +1291,28 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
             for (int k = 0; k < n; ++k) {
                 const mrhs_op *op = ops[k];
                 SapArgs<Ts, Tc> &a = B.inst[k];
-                a.colour = c;
                 a.blocks = op->colour_blocks + (c == 0 ? 0 : op->n_colour[0]);
                 a.nblocks = op->n_colour[c];
                 a.mode = s == 0 && !guess ? c : 2;  // from zero, x vanishes on blocks not yet visited
-                // the incremental residual where no block neighbours one of its own colour: every
-                // visit but the call's last one leaves the hops of its change of x for the other colour
-                a.inc = !op->odd_blocks;
-                a.f_out = a.inc && !(s + 1 == n_sap && c == 1);
-                // rho or sigma carries a colour's residual from one visit to the next (sigma with plain
-                // MR only)
-                a.sig_in = (a.inc || !eo) && s > 0;
-                a.sig_out = (a.inc || !eo) && s + 1 < n_sap;
+                // sigma and the face hops of x instead of the incremental residual only where that
+                // is how FP32 plain MR has rounded
+                a.inc = eo || sizeof(Tc) == 8 || !op->odd_blocks;
+                a.f_out = !(s + 1 == n_sap && c == 1);
+                a.sig_in = s > 0;
+                a.sig_out = s + 1 < n_sap;
+                a.face_w = face[k][s & 1];
+                a.face_o = face[k][c == 0 ? (s + 1) & 1 : s & 1];
+                a.face_s = s > 0 ? face[k][(s + 1) & 1] : nullptr;
                 a.xr = a.x;
                 a.xw = x_last && s + 1 == n_sap ? (Ts *)x_last : a.x;
-                if (a.mode == 2 && op->odd_blocks) {
+                if (a.mode == 2 && s == 0 && op->odd_blocks) {
                     C.src[C.n_inst] = a.x;
                     C.dst[C.n_inst] = snap[k];
                     C.n[C.n_inst] = (long)native_elems(op, n_rhs[k]);
                     ++C.n_inst;
                     a.xr = snap[k];
                 }
-                B.first[k + 1] = B.first[k] + a.nblocks * a.ntiles;
+                B.first[k + 1] = B.first[k] + (a.nblocks * a.ntiles + 7) / 8 * 8;
             }
             if (C.n_inst) {
                 hipLaunchKernelGGL(k_copy_batched<Ts>, dim3(2048), dim3(256), 0, st, C);
@@ -1318,12 +1349,13 @@ size_t ws_bytes_sap_batched(const mrhs_op *const *ops, int n, const int32_t *n_r
 {
     size_t w = 0;
     for (int k = 0; k < n; ++k) {
-        const size_t ne = native_elems(ops[k], n_rhs[k]);
-        const size_t tc = ops[k]->prec == MRHS_PREC_F64 ? sizeof(double) : sizeof(float);
-        if (ops[k]->odd_blocks) w += align256(ne * dtype_size(ops[k]->dtype));  // snapshot of x
-        else if (tc == 8) w += align256(face_elems<double>(ops[k], n_rhs[k]) * tc);
-        else w += align256(face_elems<float>(ops[k], n_rhs[k]) * tc);
-        w += align256(ne * tc);                                                  // sigma / rho
+        const mrhs_op *op = ops[k];
+        const bool f64 = op->prec == MRHS_PREC_F64;
+        w += align256(native_elems(op, n_rhs[k]) * (f64 ? sizeof(double) : sizeof(float)));  // sigma / rho
+        w += align256(f64 ? face_elems<double>(op, n_rhs[k]) * sizeof(double) : face_elems<float>(op, n_rhs[k]) * sizeof(float));
+        if (op->odd_blocks)
+            w += f64 ? odd_bytes<double, double>(op, n_rhs[k])
+                     : op->dtype == MRHS_DTYPE_F16 ? odd_bytes<__half, float>(op, n_rhs[k]) : odd_bytes<float, float>(op, n_rhs[k]);
     }
     return w;
 }
@@ -1350,4 +1382,4 @@ int launch_sap(const mrhs_op *op, const void *b, void *x, int n_rhs, int n_sap, 
     return launch_sap_batched(&op, 1, &b, &x, &n_rhs, n_sap, n_mr, ws, st, guess, x_last);
 }
 
-bool sap_last_sweep_apart(const mrhs_op *op, int n_sap) { return n_sap > 1 && !op->odd_blocks; }
+bool sap_last_sweep_apart(const mrhs_op *, int n_sap) { return n_sap > 1; }

@@ -26,6 +26,14 @@ CASES = [
     ([4, 4, 4, 4], [2, 2, 2, 2], F16, 4, 7, 3, 2, 2, 1),   # even-odd
     ([8, 4, 8, 4], [4, 4, 4, 4], F32, 4, 6, 3, 0, 4, 1),
     ([4, 4, 8, 4], [2, 4, 4, 2], F64, 2, 3, 3, 2, 1, 1),
+    # odd block counts: neighbours of the own colour, face buffers alternating from sweep to sweep
+    ([6, 6, 2, 2], [2, 2, 2, 2], F32, 4, 5, 4, 2, 4, 0),
+    ([6, 2, 10, 4], [2, 2, 2, 2], F64, 4, 3, 3, 2, 2, 0),
+    ([3, 3, 4, 4], [1, 1, 2, 2], F64, 1, 2, 3, 2, 1, 0),   # three blocks, one site thick
+    ([3, 5, 2, 2], [1, 1, 2, 1], F32, 2, 3, 3, 2, 2, 0),
+    ([12, 4, 4, 8], [4, 4, 4, 4], F16, 4, 6, 3, 3, 4, 0),
+    ([6, 4, 6, 2], [2, 2, 2, 2], F32, 4, 4, 4, 2, 2, 1),
+    ([4, 6, 2, 10], [2, 2, 2, 2], F64, 2, 2, 3, 2, 1, 1),
 ]
 
 
