@@ -586,9 +586,7 @@ __device__ __forceinline__ void face_store(const SapArgs<Ts, Tc> &a, int grp, in
 
 // The end of a visit on one site: x (+)= e, the faces of the change of the stored x (the correction
 // as rounded to the storage type; without inc of x) and, with inc, rho for later visits (keep():
-// stores it).  A load waits for every store issued before it, so the loads come
-// first, in two rounds (the old x and the links of directions 0, 1; the links of 2, 3), and the
-// stores after the last of them.
+// stores it).  The links of two directions are loaded ahead.
 template <typename Ts, typename Tc, typename Keep>
 __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, int blk, int off, uint32_t bcp,
                                             uint32_t lcp, int tt, Spinor<Tc> &e, Keep keep)
@@ -603,7 +601,7 @@ __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, i
         on[mu] = a.f_out && g.nb[mu] > 1 && (ff[mu] || l == 0);
     }
     FaceLink<Tc> l0, l1;
-    HalfSpinor<Tc> w[2];
+    HalfSpinor<Tc> w;
     if (on[0]) face_link<0>(a, blk, off, bcp, ff[0], l0);
     if (on[1]) face_link<1>(a, blk, off, bcp, ff[1], l1);
     Spinor<Tc> xn;
@@ -632,29 +630,36 @@ __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, i
             e.im[c] = load_as<Tc>(&si);
         }
     }
-    sched_fence();
-    if (on[0]) face_hop<0>(l0, ff[0], e, w[0]);
-    if (on[1]) face_hop<1>(l1, ff[1], e, w[1]);
-    sched_fence();
-    if (on[2]) face_link<2>(a, blk, off, bcp, ff[2], l0);
-    if (on[3]) face_link<3>(a, blk, off, bcp, ff[3], l1);
-    sched_fence();
     store_spinor(g, a.xw, grp, blk, off, tt, xn);
     if (a.sig_out && a.inc) keep();
-    if (on[0]) face_store<0>(a, grp, blk, lcp, tt, ff[0], w[0]);
-    if (on[1]) face_store<1>(a, grp, blk, lcp, tt, ff[1], w[1]);
     sched_fence();
-    if (on[2]) face_hop<2>(l0, ff[2], e, w[0]);
-    if (on[2]) face_store<2>(a, grp, blk, lcp, tt, ff[2], w[0]);
-    if (on[3]) face_hop<3>(l1, ff[3], e, w[1]);
-    if (on[3]) face_store<3>(a, grp, blk, lcp, tt, ff[3], w[1]);
+    if (on[0]) {
+        face_hop<0>(l0, ff[0], e, w);
+        face_store<0>(a, grp, blk, lcp, tt, ff[0], w);
+    }
+    if (on[2]) face_link<2>(a, blk, off, bcp, ff[2], l0);
+    sched_fence();
+    if (on[1]) {
+        face_hop<1>(l1, ff[1], e, w);
+        face_store<1>(a, grp, blk, lcp, tt, ff[1], w);
+    }
+    if (on[3]) face_link<3>(a, blk, off, bcp, ff[3], l1);
+    sched_fence();
+    if (on[2]) {
+        face_hop<2>(l0, ff[2], e, w);
+        face_store<2>(a, grp, blk, lcp, tt, ff[2], w);
+    }
+    if (on[3]) {
+        face_hop<3>(l1, ff[3], e, w);
+        face_store<3>(a, grp, blk, lcp, tt, ff[3], w);
+    }
     // a block one site thick: every site is on the -MU face as well
     auto thin = [&](auto m) __attribute__((always_inline)) {
         constexpr int MU = decltype(m)::value;
         if (g.b[MU] == 1 && on[MU]) {
             face_link<MU>(a, blk, off, bcp, false, l0);
-            face_hop<MU>(l0, false, e, w[0]);
-            face_store<MU>(a, grp, blk, lcp, tt, false, w[0]);
+            face_hop<MU>(l0, false, e, w);
+            face_store<MU>(a, grp, blk, lcp, tt, false, w);
         }
     };
     thin(std::integral_constant<int, 0>{});
