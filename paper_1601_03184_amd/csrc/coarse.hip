@@ -353,8 +353,14 @@ __global__ void __launch_bounds__(NTHR, sizeof(Tc) == 4 && sizeof(Tq) <= 4 ? 4 :
             lv = reinterpret_cast<const f4v *>(links)[(size_t)(uint32_t)ns * 18 + q];
         }
     };
+    // the links go to LDS at the end of a chunk's products, which do not read them: the barrier at
+    // the top of the next chunk covers them as well
+    const auto store_links = [&]() {
+        if (STAGE && self && threadIdx.x < CHS * 18) reinterpret_cast<f4v *>(Us)[threadIdx.x] = lv;
+    };
     __syncthreads();  // the site table
     load_rows(0);
+    store_links();
 
     for (int s0 = 0; s0 < nsites; s0 += CHS) {
         __syncthreads();
@@ -363,10 +369,6 @@ __global__ void __launch_bounds__(NTHR, sizeof(Tc) == 4 && sizeof(Tq) <= 4 ? 4 :
 #pragma unroll
             for (int it = 0; it < RMAX; ++it)  // component 2 it + up: of half 0 for it < 3
                 qst[((it >= 3 ? CHS * 6 : 0) + (2 * it) % 6) * QST] = rok ? rv[it] : make_float2(0.f, 0.f);
-        }
-        if (STAGE && self) {
-            if (threadIdx.x < CHS * 18) reinterpret_cast<f4v *>(Us)[threadIdx.x] = lv;
-            __syncthreads();
         }
         if (kok) {
             // column (h', k') = (up, kt) at site st of the chunk
@@ -400,6 +402,7 @@ __global__ void __launch_bounds__(NTHR, sizeof(Tc) == 4 && sizeof(Tq) <= 4 ? 4 :
         }
         if (wave + NW < ntile) tile_products<2>(qb, wb, accr, acci);
         else if (wave < ntile) tile_products<1>(qb, wb, accr, acci);
+        if (s0 + CHS < nsites) store_links();
     }
     // D_c(i, i) or D_c(i, i + mu); for a face also D_c(i + mu, i) = sigma3 D_c(i, i + mu)^dag sigma3
     // into the -mu slot of aggregate j = i + mu (each slot has exactly one writer)
