@@ -14,9 +14,12 @@
 //      the two inner products per step reduced across the block with wavefront shuffles
 //      and one LDS exchange, and the correction e kept in registers,
 //   3. writes x|_j (+)= e, its residual and its own faces.
-// 32^3 x 64, 32 right-hand sides in FP32, 3 x 4: 49.5 -> 46.5 ms per call with the face buffers (of the
-// 30 vector sets that a call must move at 4.4 TB/s, 22 ms); the even-odd solver, which formed the
-// full residual at every visit, 3.59 -> 2.84 ms at 16^3 x 32 with 24.
+// Bound by the vector units: an MR step issues 8 us of instructions per workgroup (of 9), and at tile
+// 4 the one workgroup of a CU has nothing to run beside its loads and stores (of about 55 us 9 for the
+// residual, 3-10 for the end).  32^3 x 64, 32 right-hand sides in FP32, 3 x 4, tile 4: 49.5 -> 46.5 ms per call
+// with the face buffers (of the 30 vector sets that a call must move at 4.4 TB/s, 22 ms), 42.2 with the reductions
+// by lane exchanges, 16-byte LDS vectors and the end of a visit without spills; the even-odd solver, which
+// formed the full residual at every visit, 3.59 -> 2.54 ms at 16^3 x 32 with 24.
 // The links and clover of a site are loaded once per stencil for all T lanes of the site.
 // With the even-odd block solver (k_sap_batched_eo) step 2 runs on the block's Schur
 // complement over its even sites instead (sap_block_eo).
@@ -231,11 +234,19 @@ __device__ inline void mr_products(const LV *rho, int str, int idx, const Spinor
 }
 
 // The links a block operator uses, staged in LDS once per workgroup (the "links in LDS"
-// variant, for the tile of four right-hand sides): U_mu(x) for the block's sites x whose
+// variants): U_mu(x) for the block's sites x whose
 // +mu neighbour is inside the block (local coordinate l_mu < b_mu - 1; every site when the
 // block spans the lattice in mu and keeps its wrap-around hop).  Per direction they form a
 // box of extents e_mu,nu = b_nu, except e_mu,mu = b_mu - 1, stored lexicographically after
 // the boxes of the lower directions, 18 reals per link.
+//
+// A tile of T right-hand sides stages the first T directions: what a 4^4 block's workgroups can
+// hold in the 160 KiB of a CU beside rho, as many of them as their registers allow (FP32: one at
+// tile 4, two at tile 2, four at tile 1; FP64 half as many).  The other directions are read through L1
+// in every MR step, 72 bytes per lane and hop in FP32, which bounds the small tiles; us without / with,
+// 3 x 4: FP32 16^3 x 32 n 24 tile 1 3645 / 3359, tile 2 2467 / 2278, 16^4 n 20 tile 2 1208 / 1118; FP64
+// 12^3 x 24 n 10 tile 1 1170 / 1091, tile 2 880 / 836; 4^4 and 8^4 within 2 %.
+constexpr int staged_links(int T) { return T; }
 struct LinkBox {
     int base[4];  // first link of direction mu
     int s[4][4];  // lexicographic strides of direction mu's box
@@ -701,9 +712,9 @@ __device__ __forceinline__ void mr_alpha(Tc qq, Tc qrr, Tc qri, Tc *red, Tc &ar,
     ai = sqq > Tc(0) ? si / sqq : Tc(0);
 }
 
-// One workgroup's share of a half-sweep: block blk, right-hand-side tile `tile`.  LL: the
-// block's links are staged in LDS (after rho and the reduction scratch) for the MR steps.
-template <typename Ts, typename Tc, int T, bool LL>
+// One workgroup's share of a half-sweep: block blk, right-hand-side tile `tile`.  The block's links in
+// the first NL directions are staged in LDS (after rho and the reduction scratch) for the MR steps.
+template <typename Ts, typename Tc, int T, int NL>
 __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int tile, unsigned char *smem)
 {
     using LV = LdsVec<Tc>;
@@ -711,7 +722,7 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
     LV *rho = reinterpret_cast<LV *>(smem);
     const int str = g.Vb * T;
     Tc *red_s = reinterpret_cast<Tc *>(rho + 24 / V16<Tc>::n * str);  // [waves][T][4]
-    Tc *ul = red_s + red_words(blockDim.x, T);  // used only with LL
+    Tc *ul = red_s + red_words(blockDim.x, T);  // used only with NL > 0
 
     const int off = threadIdx.x / T, t = threadIdx.x % T;
     const bool active = off < g.Vb;
@@ -721,18 +732,18 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
     if (active) decode_site(g, a.blk_coords, a.loc_coords, blk, off, bc, lc);
     const uint32_t lcp = active ? a.loc_coords[off] : 0u;  // local coordinates, 8 bits each
     // links in LDS: this site's index in each direction's box; the T lanes of a site copy
-    // its four forward links (lane t: directions t, t + T, ...)
+    // its forward links (lane t: directions t, t + T, ...)
     int cf[4] = {0, 0, 0, 0}, sb[4] = {0, 0, 0, 0};
-    if (LL) {
+    if (NL) {
         const LinkBox lb = link_box(g);
 #pragma unroll
-        for (int mu = 0; mu < 4; ++mu) {
+        for (int mu = 0; mu < NL; ++mu) {
             cf[mu] = lb.base[mu] + lc[0] * lb.s[mu][0] + lc[1] * lb.s[mu][1] + lc[2] * lb.s[mu][2] + lc[3] * lb.s[mu][3];
             sb[mu] = lb.s[mu][mu];
         }
         if (active) {
             using V2 = typename Vec2<Tc>::type;
-            for (int mu = t; mu < 4; mu += T) {
+            for (int mu = t; mu < NL; mu += T) {
                 if (lc[mu] + 1 < g.b[mu] || g.nb[mu] == 1) {
                     const V2 *src = reinterpret_cast<const V2 *>(a.links + ((size_t)(blk * g.Vb + off) * 4 + mu) * 18);
                     V2 *dst = reinterpret_cast<V2 *>(ul + cf[mu] * 18);
@@ -813,13 +824,13 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
             };
             // (the LDS link indices are hidden like ns: the links are re-read in every step)
             auto hops = [&]() {
-                block_hops<0, Tc, LL>(g, a.links, rho, T, ns, off, t, lcp, q, ul, LL ? opaque_index(cf[0]) : 0, sb[0]);
+                block_hops<0, Tc, (NL > 0)>(g, a.links, rho, T, ns, off, t, lcp, q, ul, NL > 0 ? opaque_index(cf[0]) : 0, sb[0]);
                 hop_fence(q);
-                block_hops<1, Tc, LL>(g, a.links, rho, T, ns, off, t, lcp, q, ul, LL ? opaque_index(cf[1]) : 0, sb[1]);
+                block_hops<1, Tc, (NL > 1)>(g, a.links, rho, T, ns, off, t, lcp, q, ul, NL > 1 ? opaque_index(cf[1]) : 0, sb[1]);
                 hop_fence(q);
-                block_hops<2, Tc, LL>(g, a.links, rho, T, ns, off, t, lcp, q, ul, LL ? opaque_index(cf[2]) : 0, sb[2]);
+                block_hops<2, Tc, (NL > 2)>(g, a.links, rho, T, ns, off, t, lcp, q, ul, NL > 2 ? opaque_index(cf[2]) : 0, sb[2]);
                 hop_fence(q);
-                block_hops<3, Tc, LL>(g, a.links, rho, T, ns, off, t, lcp, q, ul, LL ? opaque_index(cf[3]) : 0, sb[3]);
+                block_hops<3, Tc, (NL > 3)>(g, a.links, rho, T, ns, off, t, lcp, q, ul, NL > 3 ? opaque_index(cf[3]) : 0, sb[3]);
                 hop_fence(q);
             };
             // Every wavefront starts the step together after the barrier; the clover term is read
@@ -1130,7 +1141,7 @@ template <typename Ts, typename Tc> struct SapBatch {
     int n_inst;
 };
 
-template <typename Ts, typename Tc, int T, bool LL>
+template <typename Ts, typename Tc, int T, int NL>
 __global__ void __launch_bounds__(256 * T, sizeof(Tc) == 4 ? 4 : 1) k_sap_batched(SapBatch<Ts, Tc> B)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1141,7 +1152,7 @@ __global__ void __launch_bounds__(256 * T, sizeof(Tc) == 4 ? 4 : 1) k_sap_batche
     if (w >= n) return;  // padding of an instance's range
     const int li = xcd_remap(w, n);
     const int bi = li / a.ntiles, tile = li - bi * a.ntiles;
-    sap_block<Ts, Tc, T, LL>(a, a.blocks[bi], tile, smem);
+    sap_block<Ts, Tc, T, NL>(a, a.blocks[bi], tile, smem);
 }
 
 // the same with the even-odd block solver
@@ -1202,10 +1213,10 @@ template <typename Ts, typename Tc> size_t odd_bytes(const mrhs_op *op, int n_rh
     return align256(std::max(face_elems<Tc>(op, n_rhs) * sizeof(Tc), native_elems(op, n_rhs) * sizeof(Ts)));
 }
 
-template <typename Ts, typename Tc, int T, bool EO, bool LL = false>
+template <typename Ts, typename Tc, int T, bool EO, int NL = 0>
 int launch_batched(const SapBatch<Ts, Tc> &B, int threads, size_t lds, hipStream_t st)
 {
-    const void *fn = EO ? (const void *)k_sap_batched_eo<Ts, Tc, T> : (const void *)k_sap_batched<Ts, Tc, T, LL>;
+    const void *fn = EO ? (const void *)k_sap_batched_eo<Ts, Tc, T> : (const void *)k_sap_batched<Ts, Tc, T, NL>;
     static size_t done = 0;
     if (lds > 65536 && lds > done) {
         if (int rc = hip_check(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
@@ -1217,7 +1228,7 @@ int launch_batched(const SapBatch<Ts, Tc> &B, int threads, size_t lds, hipStream
         hipLaunchKernelGGL((k_sap_batched_eo<Ts, Tc, T>), dim3(B.first[B.n_inst]), dim3(threads), lds, st, B);
         return hip_check(hipGetLastError(), "k_sap_batched_eo launch");
     } else {
-        hipLaunchKernelGGL((k_sap_batched<Ts, Tc, T, LL>), dim3(B.first[B.n_inst]), dim3(threads), lds, st, B);
+        hipLaunchKernelGGL((k_sap_batched<Ts, Tc, T, NL>), dim3(B.first[B.n_inst]), dim3(threads), lds, st, B);
         return hip_check(hipGetLastError(), "k_sap_batched launch");
     }
 }
@@ -1240,12 +1251,16 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
     const int eo_threads = round64(maxVb / 2 * T);  // even-odd: one even and one odd site per thread
     size_t lds = sizeof(Tc) * (24 * (size_t)maxVb * T + red_words(threads, T));
     if (maxVb * T > 1024 || lds > max_lds) return set_error(MRHS_EUNSUPPORTED, "batched SAP tile does not fit");
-    // the plain MR kernel at tile 4 with FP32 arithmetic stages the block's links in LDS when
-    // they fit beside rho
+    // the plain MR kernel stages the links of staged_links(T) directions in LDS where they fit beside rho
+    // without taking a workgroup from a CU, which 1024 threads of the FP32 kernels fill, 512 of FP64's
     int max_links = 0;
-    for (int k = 0; k < n; ++k) max_links = std::max(max_links, link_box(ops[k]->k).n);
+    for (int k = 0; k < n; ++k) {
+        const LinkBox lb = link_box(ops[k]->k);
+        max_links = std::max(max_links, staged_links(T) == 4 ? lb.n : lb.base[staged_links(T)]);
+    }
     const size_t lds_ll = lds + sizeof(Tc) * 18 * (size_t)max_links;
-    const bool ll = !eo && sizeof(Tc) == 4 && T == 4 && lds_ll <= max_lds;
+    const int per_cu = std::max(1, (sizeof(Tc) == 4 ? 1024 : 512) / threads);
+    const bool ll = !eo && lds_ll * per_cu <= max_lds;
     if (ll) lds = lds_ll;
     if (n_sap == 0) {
         if (guess) return MRHS_OK;  // no sweep: x keeps the starting guess
@@ -1327,8 +1342,14 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
             int rc;
             const int thr = eo ? eo_threads : threads;
             switch (T * 2 + (eo ? 1 : 0)) {
-            case 2: rc = launch_batched<Ts, Tc, 1, false>(B, thr, lds, st); break;
-            case 4: rc = launch_batched<Ts, Tc, 2, false>(B, thr, lds, st); break;
+            case 2:
+                rc = ll ? launch_batched<Ts, Tc, 1, false, staged_links(1)>(B, thr, lds, st)
+                        : launch_batched<Ts, Tc, 1, false>(B, thr, lds, st);
+                break;
+            case 4:
+                rc = ll ? launch_batched<Ts, Tc, 2, false, staged_links(2)>(B, thr, lds, st)
+                        : launch_batched<Ts, Tc, 2, false>(B, thr, lds, st);
+                break;
             case 3: rc = launch_batched<Ts, Tc, 1, true>(B, thr, lds, st); break;
             case 5: rc = launch_batched<Ts, Tc, 2, true>(B, thr, lds, st); break;
             default:
@@ -1336,7 +1357,7 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
                 if constexpr (sizeof(Tc) == 4) {
                     if (T == 4) {
                         rc = eo ? launch_batched<Ts, Tc, 4, true>(B, thr, lds, st)
-                           : ll ? launch_batched<Ts, Tc, 4, false, true>(B, thr, lds, st)
+                           : ll ? launch_batched<Ts, Tc, 4, false, staged_links(4)>(B, thr, lds, st)
                                 : launch_batched<Ts, Tc, 4, false>(B, thr, lds, st);
                         break;
                     }
