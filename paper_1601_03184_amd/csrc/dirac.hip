@@ -99,6 +99,47 @@ template <typename Tx> struct HopIn {
     int site;  // native site of the neighbour
 };
 
+// Fields of a chunk's sites in LDS (the residual's FP64 ones): links and clover, 72 numbers each, padded
+// to a stride that spreads eight sites over the banks
+constexpr int FIELD_REALS = 72, FIELD_STRIDE = 74;
+template <typename Tf> using FieldVec = __attribute__((ext_vector_type(2))) Tf;
+constexpr size_t field_bytes(int sites) { return 2 * sizeof(double) * FIELD_STRIDE * (size_t)sites; }
+
+// N numbers of a field in LDS; the pointer is made a local one, or the compiler merges these loads with
+// those of lanes that read global memory into flat ones
+template <int N, typename Tf, typename T> __device__ __forceinline__ void staged_load(const Tf *f, T (&v)[N])
+{
+    const auto *p = (const __attribute__((address_space(3))) FieldVec<Tf> *)f;
+#pragma unroll
+    for (int c = 0; c < N / 2; ++c) {
+        const FieldVec<Tf> q = p[c];
+        v[2 * c] = (T)q.x;
+        v[2 * c + 1] = (T)q.y;
+    }
+}
+
+// TL lanes per site copy 36 two-number vectors of each field
+template <int TL, typename Tf>
+__device__ __forceinline__ void fields_load(const Tf *__restrict__ src, int ns, FieldVec<Tf> (&v)[(35 + TL) / TL])
+{
+    const auto *p = reinterpret_cast<const FieldVec<Tf> *>(src);
+#pragma unroll
+    for (int k = 0; k < (35 + TL) / TL; ++k) {
+        const int i = k * (int)blockDim.x + threadIdx.x, last = ns * (FIELD_REALS / 2) - 1;
+        v[k] = p[i < last ? i : last];
+    }
+}
+template <int TL, typename Tf>
+__device__ __forceinline__ void fields_store(Tf *dst, int ns, const FieldVec<Tf> (&v)[(35 + TL) / TL])
+{
+    auto *p = reinterpret_cast<FieldVec<Tf> *>(dst);
+#pragma unroll
+    for (int k = 0; k < (35 + TL) / TL; ++k) {
+        const int i = k * (int)blockDim.x + threadIdx.x, s = i / (FIELD_REALS / 2);
+        if (i < ns * (FIELD_REALS / 2)) p[s * (FIELD_STRIDE / 2) + (i - s * (FIELD_REALS / 2))] = v[k];
+    }
+}
+
 template <int MU, bool FWD, typename Tx, typename Ts>
 __device__ __forceinline__ void hop_fetch(const KGeo &g, const Ts *__restrict__ x, int grp, int tt, int blk, int off, int o0,
                                           int ns, const int (&bc)[4], const int (&lc)[4], HopIn<Tx> &h)
@@ -110,18 +151,24 @@ __device__ __forceinline__ void hop_fetch(const KGeo &g, const Ts *__restrict__ 
     if (h.lds < 0) load_spinor<Tx>(g, x, grp, n.blk, n.off, tt, h.chi);
 }
 
-template <int MU, bool FWD, int TL, typename Tc, typename Tx, typename Tf>
-__device__ __forceinline__ void hop_apply(const Tf *__restrict__ links, const typename ChunkVec<Tx>::type *lds, int t,
-                                          int own, HopIn<Tx> &h, Spinor<Tc> &out)
+template <int MU, bool FWD, int TL, bool STAGED, typename Tc, typename Tx, typename Tf>
+__device__ __forceinline__ void hop_apply(const Tf *__restrict__ links, const Tf *fl, const typename ChunkVec<Tx>::type *lds,
+                                          int t, int own, HopIn<Tx> &h, Spinor<Tc> &out)
 {
     Tc U[18];
-    load_link(links, 0L, MU, FWD ? own : h.site, U);
+    if constexpr (STAGED) {
+        if (FWD) staged_load<18>(fl + (int)threadIdx.x / TL * FIELD_STRIDE + 18 * MU, U);
+        else if (h.lds >= 0) staged_load<18>(fl + h.lds * FIELD_STRIDE + 18 * MU, U);
+        else load_link(links, 0L, MU, h.site, U);
+    } else {
+        load_link(links, 0L, MU, FWD ? own : h.site, U);
+    }
     if (h.lds >= 0) chunk_load<Tx>(lds, h.lds * TL + t, h.chi);
     hop_accumulate<MU, FWD ? -1 : 1, !FWD>(U, h.chi, out);
     hop_fence(out);
 }
 
-template <int TL, bool AHEAD, typename Tc, typename Tx, typename Tf>
+template <int TL, bool AHEAD, bool STAGED, typename Tc, typename Tx, typename Tf>
 __device__ __forceinline__ void dirac_chunk(const KGeo &g, const Tf *__restrict__ links, const Tf *__restrict__ clover,
                                             const uint32_t *__restrict__ blk_coords,
                                             const uint32_t *__restrict__ loc_coords, const Tx *__restrict__ x, int grp,
@@ -140,29 +187,53 @@ __device__ __forceinline__ void dirac_chunk(const KGeo &g, const Tf *__restrict_
     std::integral_constant<int, 0> m0;
     std::true_type fw;
     std::false_type bw;
-    if (ok) {
+    Tf *fl = reinterpret_cast<Tf *>(lds + 24 / ChunkVec<Tx>::n * (int)blockDim.x);  // used only with STAGED
+    if constexpr (STAGED) {
         Spinor<Tx> me;
-        load_spinor<Tx>(g, x, grp, blk, off, tt, me);
-        if (AHEAD) {
+        if (ok) load_spinor<Tx>(g, x, grp, blk, off, tt, me);
+        FieldVec<Tf> fv[2][(35 + TL) / TL];
+        const size_t first = (size_t)(blk * g.Vb + o0) * FIELD_REALS;
+        Tf *fc = fl + ns * FIELD_STRIDE;
+        fields_load<TL>(links + first, ns, fv[0]);
+        fields_load<TL>(clover + first, ns, fv[1]);
+        if (AHEAD && ok) {
             fetch(m0, fw, f);
             fetch(m0, bw, b);
         }
         sched_fence();
-        chunk_store<Tx>(lds, threadIdx.x, me);
-        clover_site(clover, g.V, own, me, out);
+        if (ok) chunk_store<Tx>(lds, threadIdx.x, me);
+        fields_store<TL>(fl, ns, fv[0]);
+        fields_store<TL>(fc, ns, fv[1]);
+        __syncthreads();
+        if (!ok) return;
+        chunk_load<Tx>(lds, threadIdx.x, me);
+        clover_site(fc + (off - o0) * FIELD_STRIDE, g.V, 0L, me, out);
         hop_fence(out);
+    } else {
+        if (ok) {
+            Spinor<Tx> me;
+            load_spinor<Tx>(g, x, grp, blk, off, tt, me);
+            if (AHEAD) {
+                fetch(m0, fw, f);
+                fetch(m0, bw, b);
+            }
+            sched_fence();
+            chunk_store<Tx>(lds, threadIdx.x, me);
+            clover_site(clover, g.V, own, me, out);
+            hop_fence(out);
+        }
+        __syncthreads();
+        if (!ok) return;
     }
-    __syncthreads();
-    if (!ok) return;
     auto direction = [&](auto mu) __attribute__((always_inline)) {
         constexpr int MU = decltype(mu)::value;
         std::integral_constant<int, (MU + 1) % 4> next;
         if (!AHEAD) fetch(mu, fw, f);
-        hop_apply<MU, true, TL>(links, lds, t, own, f, out);
+        hop_apply<MU, true, TL, STAGED>(links, fl, lds, t, own, f, out);
         if (AHEAD && MU < 3) fetch(next, fw, f);
         sched_fence();
         if (!AHEAD) fetch(mu, bw, b);
-        hop_apply<MU, false, TL>(links, lds, t, own, b, out);
+        hop_apply<MU, false, TL, STAGED>(links, fl, lds, t, own, b, out);
         if (AHEAD && MU < 3) fetch(next, bw, b);
         sched_fence();
     };
@@ -218,7 +289,7 @@ __global__ void __launch_bounds__(DIRAC_TL *DIRAC_SITES, 4)
     const bool ok = (int)threadIdx.x / DIRAC_TL < ns && grp < ngrp;
     Spinor<Tc> out;
     using Tx = typename Elem<Ts>::type;
-    dirac_chunk<DIRAC_TL, true>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0,
+    dirac_chunk<DIRAC_TL, true, false>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0,
                           ns, ok, smem, out);
     if (ok) store_spinor(g, y, grp, w.blk, o0 + (int)threadIdx.x / DIRAC_TL, tt, out);
 }
@@ -227,11 +298,18 @@ __global__ void __launch_bounds__(DIRAC_TL *DIRAC_SITES, 4)
 // side, FP64.  The T lanes of a site share its FP64 field loads; with T = 2S a tile spans two
 // groups of the native layout (lanes t < S the first, t >= S the second), which halves the
 // field loads per right-hand side.  Lanes of a group beyond the last one add nothing.
-// Bound by the field loads: each lane takes 1.7 KB of FP64 links and clover per site through L1
-// beside 0.5 KB of vectors.  Operands two hops ahead (two wavefronts per SIMD, 218 VGPRs) beat
-// three without (7.0 -> 6.4 ms at 32^3 x 64 with 24 right-hand sides in FP32; 8.7 ms without, held to
-// 168 VGPRs it spilled); FP64 storage, where they would take 268, goes without.
+// Bound by the traffic between L2 and memory (42 GB by the counters at 32^3 x 64 with 32 right-hand sides
+// in FP32, faces five times what must move) and by the FP64 links and clover, 1.7 KB per lane and site.
+// Operands two hops ahead (two wavefronts per SIMD) beat three without (7.0 -> 6.4 ms with 24
+// right-hand sides; 8.7 ms without, held to 168 VGPRs it spilled); FP64 storage, where they would take
+// 268, goes without.
 constexpr int RES_THREADS = 256;
+
+// The fields go through LDS where the eight lanes of a site would each take them through L1 and two
+// workgroups still fit in a CU (62 KiB each; with FP64 storage 87, with four lanes 100): 32^3 x 64 with
+// 32 right-hand sides in FP32 9.3 ms site by site, 8.1 with the spinors alone in LDS, 7.4 with both, 16^4 with 20
+// 213, 193 and 182 us.
+template <typename Ts, int T> constexpr bool residual_staged() { return T == 8 && sizeof(Ts) < 8; }
 
 template <typename Ts, int T>
 __global__ void __launch_bounds__(RES_THREADS, 2) k_residual(KGeo g, const double *__restrict__ links,
@@ -254,7 +332,7 @@ __global__ void __launch_bounds__(RES_THREADS, 2) k_residual(KGeo g, const doubl
         const bool ok = s < ns && grp < ngrp;
         if (c > c0) __syncthreads();  // every lane has finished reading the last chunk
         Spinor<double> Dx;
-        dirac_chunk<T, (sizeof(Ts) < 8)>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0, ns,
+        dirac_chunk<T, (sizeof(Ts) < 8), residual_staged<Ts, T>()>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0, ns,
                        ok, smem, Dx);
         if (ok) {
             Spinor<double> bb;
@@ -390,7 +468,8 @@ int residual_launch(const mrhs_op *op, const void *b, const void *x, int n_rhs, 
     const Chunks ch = residual_chunks(g, T);
     double *part = (double *)ws;
     const int threads = round64(ch.sites * T);
-    hipLaunchKernelGGL((k_residual<Ts, T>), dim3(g.nblk * ntiles * slots), dim3(threads), 24 * sizeof(Ts) * threads, st, g,
+    const size_t lds = 24 * sizeof(Ts) * threads + (residual_staged<Ts, T>() ? field_bytes(ch.sites) : 0);
+    hipLaunchKernelGGL((k_residual<Ts, T>), dim3(g.nblk * ntiles * slots), dim3(threads), lds, st, g,
                        op->links64, op->clover64, op->blk_coords, op->loc_coords, (const Ts *)b, (const Ts *)x, ntiles, ch,
                        slots, ngrp, part);
     if (int rc = hip_check(hipGetLastError(), "k_residual launch")) return rc;
