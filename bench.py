@@ -55,8 +55,8 @@ TOL = {"f32": 1e-5, "f16_storage": 5e-3, "f64": 1e-12}
 # with (SHA-1 of the files below); otherwise the bench reports traffic as null.
 SAP_SOURCES = ["paper_1601_03184_amd/csrc/sap.hip", "paper_1601_03184_amd/csrc/stencil.h",
                "paper_1601_03184_amd/csrc/internal.h"]
-SAP_TRAFFIC = {"sources_sha1": "e995143935673a2b9ee3cbc50ac794ba20eabc0a", "fetch_scale": 2.0, "write_scale": 1.0,
-               "kib": {4: (37813987, 39813120)}}
+SAP_TRAFFIC = {"sources_sha1": "72e16e6c34c6c2ae128325c671a2ee3fc0c87159", "fetch_scale": 2.0, "write_scale": 1.0,
+               "kib": {4: (22266644, 39813120)}}
 
 
 def sources_sha1():
@@ -107,9 +107,10 @@ def sap_flops_per_call(V, n, n_sap, n_mr, block):
 def sap_bytes_per_call(V, n, n_sap, store_b, field_b, sigma_b=4):
     """Algorithmic HBM bytes of a SAP call: per half-sweep the fields of that colour's sites
     once; in the first sweep b read, in later ones the kept block residual (arithmetic type)
-    and the own x read; x written; the other colour's x (first black half-sweep) or change of x
-    (later visits) that the face hops read, counted once per site; the block residual and the
-    change of x written where a later visit reads them."""
+    and the own x read; x written; the neighbours' outgoing face hops (of x at the first black
+    half-sweep, of their change of x later) read; the block residual and the own face hops
+    written where a later visit reads them (12 reals per face site: at 4^4 blocks as many as the
+    block's spinors hold)."""
     half = V // 2
     s = pm.SPINOR_REALS * store_b
     sg = pm.SPINOR_REALS * sigma_b
@@ -123,14 +124,12 @@ def sap_bytes_per_call(V, n, n_sap, store_b, field_b, sigma_b=4):
                 total += half * n * s                     # b read
             else:
                 total += half * n * (sg + s)              # block residual and the own x read
-            if sweep == 0 and c == 1:
-                total += half * n * s                     # the other colour's x
-            elif sweep > 0:
-                total += half * n * sg                    # the other colour's change of x
+            if sweep > 0 or c == 1:
+                total += half * n * sg                    # the neighbours' face hops
             if sweep + 1 < n_sap:
                 total += half * n * sg                    # block residual written
             if not (sweep + 1 == n_sap and c == 1):
-                total += half * n * sg                    # change of x written
+                total += half * n * sg                    # face hops written
     return total
 
 
@@ -836,7 +835,7 @@ def main():
     d_bytes = V * n * pm.stencil_bytes_per_site_rhs(n, 4, 4)
     copy = copy_ceiling()
     # tile 4 on a short length of 4 runs two groups per workgroup
-    dname = "k_dirac_2g" if tiles["dirac"] == 4 and S == 4 else "k_dirac"
+    dname = "k_dirac_chunk" if tiles["dirac"] == 4 and S == 4 else "k_dirac"
     stencil = {"kernel": "%s (FP32, %d RHS, tile %d)" % (dname, n, tiles["dirac"]), "ms": round(d_ms, 4),
                "GBs": round(d_bytes / d_ms / 1e6, 1), "frac_hbm": round(d_bytes / d_ms / 1e6 / HBM_PEAK_GBS, 4),
                "frac_of_copy": round(d_bytes / d_ms / 1e6 / copy["GBs"], 4),

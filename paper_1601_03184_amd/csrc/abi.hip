@@ -237,11 +237,12 @@ int mrhs_op_create(const mrhs_geom *geom, const double *links, double m0, double
     // SAP tile until mrhs_set_tiles or the autotuner choose one.  A larger tile shares the field loads
     // and fills the wavefronts of small blocks, a smaller one gives short lattices more
     // workgroups; it depends on the lattice alone, so that a right-hand side's result does not
-    // depend on how many others share the call.  FP64, 3 x 4, us at tiles 1 / 2: 12^3 x 24 n 10 1349 / 1024,
-    // 16^3 x 32 n 24 6715 / 4982, 4^4 in blocks of 16 sites n 8 205 / 201, 8^4 n 8 278 / 322.  FP32 stays at
-    // 2 (16^4 n 20 1093, n 3 254; at 4, which the autotuner finds on large lattices, 1036 and 293): another
-    // tile sums in another order, which FP32 results show.
-    op->sap_tile = pick_tile(op, prec != MRHS_PREC_F64 || k.nblk >= 128 || k.Vb <= 64 ? 2 : 1, true);
+    // depend on how many others share the call.  FP64, 3 x 4, us at tiles 1 / 2: 12^3 x 24 n 10 1091 / 836,
+    // 16^3 x 32 n 24 6214 / 4767, 12^4 n 3 and 12 307 / 329 and 552 / 369, 8^3 x 16 n 4, 12 and 24 274 / 310,
+    // 320 / 329 and 490 / 349, 8^4 n 8 276 / 311, 4^4 in blocks of 16 sites n 8 208 / 208.
+    // FP32 stays at 2; a tile of 4, which the autotuner finds on large lattices, sums in another order, and
+    // FP32 results show it.
+    op->sap_tile = pick_tile(op, prec != MRHS_PREC_F64 || k.nblk >= 64 || k.Vb <= 64 ? 2 : 1, true);
     op->dirac_tile = pick_tile(op, prec == MRHS_PREC_F64 ? 1 : 4, false);
     if (rc) {
         free_op(op);

@@ -233,7 +233,8 @@ __device__ inline void part_column(const CoarseArgs<Tq> &a, const Tc *__restrict
 // during the products of the current one; the columns load a hop's operands during the
 // previous hop's arithmetic; lanes cover 4 vectors x 8 sites, 128-byte runs (vectors across the
 // lanes had made every load 16-byte pieces of sixteen lines): 32^3 x 64, 32 vectors in FP32 14.6 ->
-// 11.5 ms, 16^4 with 20 408 -> 328 us, against 5.3 ms of matrix-core work.  The (aggregate, part)
+// 11.4 ms, 16^4 with 20 408 -> 300 us.  Bound by the matrix cores (5.3 of the 11.4 ms) and the vector
+// units (3.3 ms), which do not overlap, and the loads of the columns.  The (aggregate, part)
 // items are taken in contiguous runs per XCD, so that concurrent
 // workgroups of one XCD read neighbouring aggregates (the face parts' neighbours) through
 // the same L2, and the vector-unit-heavy self parts share CUs with the latency-bound faces.

@@ -256,7 +256,7 @@ template <typename TV> __global__ void __launch_bounds__(GTHR) k_gm_axpy(GmArgs 
 // projects with them), or with itself (NORM).  A block takes a chunk of entries for all
 // right-hand sides, a thread one right-hand side and every DROWS-th entry of the chunk.  Bound by its
 // reads: an Arnoldi step reads the basis three times instead of four (8192 coarse sites with 64
-// degrees of freedom, 32 right-hand sides: the vector kernels of a solve 3.5 -> 2.7 ms).
+// degrees of freedom, 32 right-hand sides: the vector kernels of a solve 3.5 -> 2.6 ms).
 template <typename TV, bool NORM> __global__ void __launch_bounds__(DTHR) k_gm_project(GmArgs a, int nvec)
 {
     __shared__ Z red[DROWS][32];

@@ -14,8 +14,8 @@
 //
 // The second Gram product (half of the matrix-core work) is skipped where it cannot change the
 // stored Q (one_pass_enough).  Bound by the FP64 matrix cores, with the reads of V (two passes, three
-// with the second product) close behind: 32^3 x 64, 32 vectors in FP32 10.8 -> 5.6 ms (19.3 GB,
-// 3.5 TB/s), 24^3 x 48, 24 vectors, Q in binary16 3.84 -> 2.20 ms.
+// with the second product) close behind: 32^3 x 64, 32 vectors in FP32 10.8 -> 5.5 ms (19.3 GB,
+// 3.5 TB/s), 24^3 x 48, 24 vectors, Q in binary16 3.84 -> 2.03 ms, 16^4 with 20 415 -> 196 us.
 //
 // V is read in 16-row blocks that each wavefront loads one block ahead of the one on the matrix
 // cores; the row offsets of the aggregate's sites are staged in LDS.  Q1 is never stored: each

@@ -116,8 +116,8 @@ template <typename Ts, typename Tc> struct SapArgs {
 
 // The block residual rho lives in LDS in component vectors of n numbers, [24 / n][Vb][T]: lane
 // (off, t) reads vector v at (v * Vb + off) * T + t, consecutive lanes consecutive vectors.  Plain
-// MR takes 16-byte vectors (half the LDS instructions and addresses of (re, im) pairs: 7.85 ->
-// 7.60 ms per half-sweep at 32^3 x 64, 32 right-hand sides, with the reduction of mr_alpha); the
+// MR takes 16-byte vectors (half the LDS instructions and addresses of (re, im) pairs: with the lane
+// exchanges of mr_alpha 7.8 -> 7.1 ms per half-sweep at 32^3 x 64, 32 right-hand sides, tile 4); the
 // even-odd kernel pairs, whose smaller load groups keep it within its registers.
 template <typename Tc> using LdsVec = typename V16<Tc>::type;
 template <typename Tc> using LdsPair = typename Vec2<Tc>::type;
