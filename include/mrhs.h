@@ -119,14 +119,16 @@ int dirac_apply_mrhs(const mrhs_op *op, const void *x, void *y, int32_t n_rhs, v
  * b - D x is formed on that colour's blocks, then every block j adds n_mr minimal-
  * residual steps on D_j = I_j^T D I_j (step length 0 when <q,q> = 0).  b, x: native
  * vectors of the op's element type, x != b; x is overwritten.  ws: workspace of at
- * least mrhs_workspace_bytes(op, n_rhs) bytes.  It carries a block's residual from one visit
- * to the next, so that a later visit forms only the hops across the block's faces (the same
- * residual up to rounding order): the block residual rho_j after its MR steps (one vector set in
- * the arithmetic type) and every block's outgoing face hops of its last change of x (12 numbers
- * per face site and right-hand side), a later residual being rho_j minus the neighbours' face
- * hops.  When a direction holds an odd number (> 1) of blocks there are two sets of face hops
- * (the second also takes a snapshot of x in the first sweep from a guess), and FP32 plain MR keeps
- * sigma_j = b_j - D_j x_j and the face hops of x instead. */
+ * least mrhs_workspace_bytes(op, n_rhs) bytes.  It carries what a later visit of a block needs, so that
+ * this forms no hop from the neighbours' vectors: every block's outgoing face hops (12 numbers per
+ * face site and right-hand side), and with plain MR a block residual (one vector set), both in the
+ * arithmetic type.  Plain MR keeps the residual rho_j after its MR steps and the face hops of the last
+ * change of x; a later residual is rho_j minus the neighbours' face hops: that of the correction before
+ * it was rounded to x's storage type, so that with FP16 storage the roundings of a block's own x stay out of
+ * its later residuals.  The even-odd solver forms every later residual from x as stored, b - D_j x_j minus
+ * the neighbours' face hops of x.  When a direction holds an odd number (> 1) of blocks there are two sets of
+ * face hops (the second also takes a snapshot of x in the first sweep from a guess), and FP32 plain MR
+ * keeps sigma_j = rho_j plus the neighbours' face hops of x, and the face hops of x, instead. */
 int sap_smooth_mrhs(const mrhs_op *op, const void *b, void *x, int32_t n_rhs, int32_t n_sap, int32_t n_mr,
                     void *ws, size_t ws_bytes, void *stream);
 

@@ -12,7 +12,8 @@ int launch_pack(const mrhs_op *op, const double *canon, void *native, int dtype,
 int launch_unpack(const mrhs_op *op, const void *native, int dtype, double *canon, int n_rhs, hipStream_t st);
 int launch_dirac(const mrhs_op *op, const void *x, void *y, int n_rhs, hipStream_t st);
 // x_last (nullable, one operator): the last sweep writes its x there instead of into x; it may be b
-// where sap_last_sweep_apart holds (a sweep after the first reads neither b nor the neighbours' x)
+// where sap_last_sweep_apart holds (a sweep after the first reads no neighbour's x, and b at most on
+// the visited block, by the workgroup that then writes there)
 int launch_sap(const mrhs_op *op, const void *b, void *x, int n_rhs, int n_sap, int n_mr, void *ws, hipStream_t st,
                bool guess = false, void *x_last = nullptr);
 bool sap_last_sweep_apart(const mrhs_op *op, int n_sap);

@@ -5,10 +5,10 @@
 // colour x a tile of T right-hand sides; thread (off, t) owns one site of the block and
 // one right-hand side.  The workgroup
 //   1. forms the residual r = b - D x on its block: the full stencil on a first visit from a
-//      guess, afterwards the block's kept residual minus the hops across its faces, which the
-//      neighbours left, spin-projected and multiplied by the link, in face buffers (read once and
-//      in order, a quarter of the loads of reading the neighbours' spinors across the faces; all
-//      of them in flight at once),
+//      guess, afterwards the block's kept residual (even-odd: b - D_j x_j, formed again from the stored
+//      x) minus the hops across its faces, which the neighbours left, spin-projected and multiplied by
+//      the link, in face buffers (read once and in order, a quarter of the loads of reading the
+//      neighbours' spinors across the faces; all of them in flight at once),
 //   2. runs n_mr minimal-residual steps on the block operator D_j = I_j^T D I_j with the
 //      block residual rho kept in LDS ([24][Vb][T], conflict-free for the thread order),
 //      the two inner products per step reduced across the block with wavefront shuffles
@@ -19,7 +19,8 @@
 // residual, 3-10 for the end).  32^3 x 64, 32 right-hand sides in FP32, 3 x 4, tile 4: 49.5 -> 46.5 ms per call
 // with the face buffers (of the 30 vector sets that a call must move at 4.4 TB/s, 22 ms), 42.2 with the reductions
 // by lane exchanges, 16-byte LDS vectors and the end of a visit without spills; the even-odd solver, which
-// formed the full residual at every visit, 3.59 -> 2.54 ms at 16^3 x 32 with 24.
+// formed the full residual at every visit from global memory, 3.34 -> 2.85 ms at 16^3 x 32 with 24, 3 x 3 (2.60
+// with a kept Schur residual, which the roundings of x left: see sap_block_eo).
 // The links and clover of a site are loaded once per stencil for all T lanes of the site.
 // With the even-odd block solver (k_sap_batched_eo) step 2 runs on the block's Schur
 // complement over its even sites instead (sap_block_eo).
@@ -87,7 +88,7 @@ template <typename Ts, typename Tc> struct SapArgs {
     const Ts *xr;           // where neighbours' x is read (x itself, or a snapshot)
     Ts *x;
     Ts *xw;                 // where the new x is written (x itself, or a caller's other vectors)
-    // kept per block between the visits of a colour (arithmetic type, component vectors of 16
+    // plain MR: kept per block between the visits of a colour (arithmetic type, component vectors of 16
     // bytes: sig_ptr).  inc: the block residual rho after the last visit; a later visit's residual is
     // rho minus the face hops of the neighbours' changes of x since.  Every neighbour has changed
     // once since then, the last time it was visited, and left its hops of that change in the
@@ -95,7 +96,7 @@ template <typename Ts, typename Tc> struct SapArgs {
     // sigma = b - D_j x_j, a later visit's residual being sigma minus the face hops of x, which
     // then are what the face buffer holds.
     Tc *sig;
-    int sig_in;             // this colour's rho or sigma is valid (read it instead of forming b - D x)
+    int sig_in;             // a later visit: this colour's rho or sigma is valid, the neighbours' faces are
     int sig_out;            // write it for the next visit of this colour
     int inc;
     // Every block's outgoing hops across its faces: per face site the two spin rows (1 -+ g_mu)
@@ -888,15 +889,7 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
     }
 }
 
-// The even-odd block solver (DD-alpha-AMG's): with a block's sites split by the parity of
-// their block-local coordinate sum (every block extent even, so each hop inside the block
-// joins opposite parities), D_j = A + H is solved through the Schur complement over the
-// even sites, S = A_ee - H_eo A_oo^-1 H_oe:
-//   rhat_e = r_e - H_eo A_oo^-1 r_o,  n_mr MR steps on S e_e = rhat_e,  e_o = A_oo^-1 (r_o - H_oe e_e).
-// Threads take the block's sites in parity order (the even half first), so each phase runs
-// on whole wavefronts of one parity.  LDS holds rho on the even sites; on the odd sites it
-// holds -A_oo^-1 H_oe rho for the step in progress, so that the even sites' hops add
-// -H_eo A_oo^-1 H_oe rho to A_ee rho directly.
+// h += the hops inside the block on one of the even-odd solver's sites
 template <typename Ts, typename Tc, int T>
 __device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int ns, int off, int t,
                                uint32_t lc, Spinor<Tc> &h)
@@ -912,9 +905,8 @@ __device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho,
     hop_fence(h);
 }
 
-// The residual of one site, to LDS.  A later visit starts from what the last one left:
-// the Schur residual rho on the even sites (kept in sig) and zero on the odd ones, whose
-// equations that visit's reconstruction solved.
+// The residual of one site at a first visit, to LDS: b (x = 0 everywhere), b minus the face hops (x = 0
+// on the block), or from a guess the full b - D x.
 template <typename Ts, typename Tc, int T>
 __device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, LdsPair<Tc> *rho, int blk, int off, int grp,
                                    int tt, int t)
@@ -923,17 +915,10 @@ __device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, LdsPair<Tc> *rho, i
     Spinor<Tc> r;
     if (a.mode == 0) {
         load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
-    } else if (a.sig_in || a.mode == 1) {
-        const uint32_t bcp = a.blk_coords[blk], lcp = a.loc_coords[off];
-        const int odd = (unpack_coord(lcp, 0) + unpack_coord(lcp, 1) + unpack_coord(lcp, 2) + unpack_coord(lcp, 3)) & 1;
-        if (a.sig_in) {
-            spinor_zero(r);
-            if (!odd) sig_load(g, a.sig, grp, blk, off, tt, r);
-        } else {
-            load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
-        }
+    } else if (a.mode == 1) {
+        load_spinor<Tc>(g, a.b, grp, blk, off, tt, r);
         Spinor<Tc> f;
-        face_sum(a, grp, blk, bcp, lcp, tt, f);
+        face_sum(a, grp, blk, a.blk_coords[blk], a.loc_coords[off], tt, f);
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             r.re[c] -= f.re[c];
@@ -954,13 +939,57 @@ __device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, LdsPair<Tc> *rho, i
     lds_store<Tc>(rho, g.Vb * T, off * T + t, r);
 }
 
+// The residual of one site at a later visit: b - D_j x_j, the block's x as stored read from LDS, minus
+// the face hops of the neighbours' x.
+template <typename Ts, typename Tc, int T>
+__device__ inline void eo_residual_again(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int blk, int off, int grp,
+                                         int tt, int t, Spinor<Tc> &r)
+{
+    const KGeo &g = a.g;
+    const int str = g.Vb * T, ns = opaque_index(blk * g.Vb + off), me = off * T + t;
+    const uint32_t lcp = a.loc_coords[off];
+    {
+        Spinor<Tc> own;
+        Tc A[36];
+        lds_load_half<0, Tc>(rho, str, me, own);
+        load_clover_half<0>(a.clover, g.V, ns, A);
+        clover_half<0>(A, own, r);
+    }
+    hop_fence(r);
+    {
+        Spinor<Tc> own;
+        Tc A[36];
+        lds_load_half<1, Tc>(rho, str, me, own);
+        load_clover_half<1>(a.clover, g.V, ns, A);
+        clover_half<1>(A, own, r);
+    }
+    hop_fence(r);
+    eo_hops<Ts, Tc, T>(a, rho, ns, off, t, lcp, r);
+    {
+        Spinor<Tc> f;
+        face_sum(a, grp, blk, a.blk_coords[blk], lcp, tt, f);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            r.re[c] += f.re[c];
+            r.im[c] += f.im[c];
+        }
+    }
+    hop_fence(r);
+    Spinor<Tc> bb;
+    load_spinor<Tc>(g, a.b, grp, blk, off, tt, bb);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        r.re[c] = bb.re[c] - r.re[c];
+        r.im[c] = bb.im[c] - r.im[c];
+    }
+}
+
 template <typename Ts, typename Tc, int T>
 __device__ inline void eo_update_x(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int blk, int off,
                                    int grp, int tt, int t)
 {
     Spinor<Tc> e;
     lds_load<Tc>(rho, a.g.Vb * T, off * T + t, e);
-    // (the Schur residual is kept in step 4)
     finish_site(a, grp, blk, off, a.blk_coords[blk], a.loc_coords[off], tt, e, []() {});
 }
 
@@ -991,8 +1020,30 @@ __device__ inline void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile,
     // local coordinates of the even and the odd site, 8 bits each
     const uint32_t lce = active ? a.loc_coords[se] : 0u, lco = active ? a.loc_coords[so] : 0u;
 
-    // 1. residual on the block (sites u and u + Ve in site order), to LDS
-    if (active) {
+    // 1. residual on the block (sites u and u + Ve in site order), to LDS.  A later visit forms it from the
+    // stored x, not from the Schur residual of the last one: what rounding x to its storage type took away
+    // is then part of the residual and is corrected, where it would add up from sweep to sweep (binary16
+    // storage, 8^4: relative error 2.2e-4 at any number of sweeps, against 3.0e-4 to 5.2e-4 at 2 to 6).
+    if (a.sig_in) {
+        if (active) {
+            Spinor<Tc> x;
+            load_spinor<Tc>(g, a.x, grp, blk, u, tt, x);
+            lds_store<Tc>(rho, str, u * T + t, x);
+            load_spinor<Tc>(g, a.x, grp, blk, u + Ve, tt, x);
+            lds_store<Tc>(rho, str, (u + Ve) * T + t, x);
+        }
+        __syncthreads();
+        Spinor<Tc> r0, r1;
+        if (active) {
+            eo_residual_again<Ts, Tc, T>(a, rho, blk, u, grp, tt, t, r0);
+            eo_residual_again<Ts, Tc, T>(a, rho, blk, u + Ve, grp, tt, t, r1);
+        }
+        __syncthreads();
+        if (active) {
+            lds_store<Tc>(rho, str, u * T + t, r0);
+            lds_store<Tc>(rho, str, (u + Ve) * T + t, r1);
+        }
+    } else if (active) {
         eo_residual<Ts, Tc, T>(a, rho, blk, u, grp, tt, t);
         eo_residual<Ts, Tc, T>(a, rho, blk, u + Ve, grp, tt, t);
     }
@@ -1085,14 +1136,10 @@ __device__ inline void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile,
         }
     }
 
-    // 4. odd: e_o = A_oo^-1 r_o + A_oo^-1 H_oe (-e_e); with inc the Schur residual is kept first
+    // 4. odd: e_o = A_oo^-1 r_o + A_oo^-1 H_oe (-e_e)
     __syncthreads();
     if (active) {
         Spinor<Tc> m;
-        if (a.sig_out && a.inc) {
-            lds_load<Tc>(rho, str, me, m);
-            sig_store(g, a.sig, grp, blk, se, tt, m);
-        }
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             m.re[c] = -ee.re[c];
@@ -1314,9 +1361,9 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
                 a.blocks = op->colour_blocks + (c == 0 ? 0 : op->n_colour[0]);
                 a.nblocks = op->n_colour[c];
                 a.mode = s == 0 && !guess ? c : 2;  // from zero, x vanishes on blocks not yet visited
-                // sigma and the face hops of x instead of the incremental residual only where that
-                // is how FP32 plain MR has rounded
-                a.inc = eo || sizeof(Tc) == 8 || !op->odd_blocks;
+                // plain MR: the incremental residual, but sigma and the face hops of x where that is how
+                // FP32 has rounded.  Even-odd keeps no residual and reads the face hops of x.
+                a.inc = !eo && (sizeof(Tc) == 8 || !op->odd_blocks);
                 a.f_out = !(s + 1 == n_sap && c == 1);
                 a.sig_in = s > 0;
                 a.sig_out = s + 1 < n_sap;
