@@ -577,8 +577,8 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     }
     __syncthreads();
     if (threadIdx.x == 0 && bad && a.status) {
-        // the smallest of the flagged halves; 0 (none) counts as the largest, as unsigned v - 1
-        const unsigned v = 1u + blockIdx.x;
+        // the smallest of the flagged halves (wi = 2 i + h); 0 (none) counts as the largest, as unsigned v - 1
+        const unsigned v = 1u + (unsigned)wi;
         unsigned *w = reinterpret_cast<unsigned *>(a.status), old = *w;
         while (old - 1u > v - 1u) {
             const unsigned seen = atomicCAS(w, old, v);
