@@ -79,16 +79,15 @@ __device__ inline RowBlock row_block(int B, int nbq, int h, uint32_t cstr)
 // columns (beyond n_tv) get R = 1 on the diagonal and 0 elsewhere.
 // A step subtracts conj(G[j][k]) G[j][l] / pivot from the rows below with row j as it is (one barrier
 // and one reciprocal per step); the rows are scaled to R at the end.  Threads form a 16 x 16 grid
-// over (k, l).
-template <int NP> __device__ void cholesky_inplace(Cplx *G, const double *diag0, double *rd, int N, int *bad)
+// over (k, l).  TINY: pivots whose reciprocal may overflow; the quotients are formed one by one.
+template <int NP, bool TINY> __device__ void cholesky_steps(Cplx *G, const double *diag0, double *rd, int N, int *bad)
 {
     const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
     for (int j = 0; j < NP; ++j) {
-        __syncthreads();
         const double piv = G[j * NP + j].re;
         const bool pad = j >= N;
         const bool deficient = !pad && !(piv > 1e-14 * diag0[j]);
-        const double p = deficient || pad ? 1.0 : piv, ip = 1.0 / p;
+        const double p = deficient || pad ? 1.0 : piv, ip = TINY ? 0.0 : 1.0 / p;
         if (threadIdx.x == 0) {
             if (deficient) *bad = 1;
             rd[j] = p;
@@ -98,7 +97,7 @@ template <int NP> __device__ void cholesky_inplace(Cplx *G, const double *diag0,
         for (int a = 0; a < NP / 16; ++a) {
             const int k = ty + 16 * a;
             if (k <= j) continue;
-            const Cplx rk = {G[j * NP + k].re * ip, G[j * NP + k].im * ip};
+            const Cplx g = G[j * NP + k], rk = TINY ? Cplx{g.re / p, g.im / p} : Cplx{g.re * ip, g.im * ip};
 #pragma unroll
             for (int b = a; b < NP / 16; ++b) {
                 const int l = tx + 16 * b;
@@ -109,8 +108,20 @@ template <int NP> __device__ void cholesky_inplace(Cplx *G, const double *diag0,
                 G[k * NP + l].im -= rk.re * rl.im - rk.im * rl.re;
             }
         }
+        __syncthreads();
     }
     __syncthreads();
+}
+
+// tiny: whether a diagonal element lies below TINY_NORM (pivots are at least 1e-14 of it)
+constexpr double TINY_NORM = 0x1p-900;
+
+template <int NP>
+__device__ void cholesky_inplace(Cplx *G, const double *diag0, double *rd, int N, int *bad, const int *tiny)
+{
+    __syncthreads();
+    if (*tiny) cholesky_steps<NP, true>(G, diag0, rd, N, bad);
+    else cholesky_steps<NP, false>(G, diag0, rd, N, bad);
     if (threadIdx.x < NP) rd[threadIdx.x] = 1.0 / sqrt(rd[threadIdx.x]);
     __syncthreads();
     for (int e = threadIdx.x; e < NP * NP; e += NTHR) {
@@ -459,7 +470,7 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     double *rd = diag0 + NP;                     // 1 / R[j][j]
     size_t *coff = reinterpret_cast<size_t *>(rd + NP);
     uint32_t *sbase = reinterpret_cast<uint32_t *>(coff + NP);
-    __shared__ int bad;
+    __shared__ int bad, tiny;
     __shared__ double red[NW];
 
     const Tv *V = static_cast<const Tv *>(a.V);
@@ -468,7 +479,7 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t cstr = (uint32_t)a.g.Vb * (uint32_t)a.g.S;
     const size_t gstr = (size_t)a.g.nblk * 24 * cstr;  // one group of S test vectors
-    if (threadIdx.x == 0) bad = 0;
+    if (threadIdx.x == 0) bad = tiny = 0;
     for (int k = threadIdx.x; k < NP; k += blockDim.x) coff[k] = (size_t)(k / a.g.S) * gstr + (k % a.g.S);
     int staged = -1;  // first site of the staged range
 
@@ -498,8 +509,11 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
     __syncthreads();
     gram_reduce<NT>(acc, G, NP, lane, wave);
     gram_fix_diag<NT>(G, NP);
-    for (int k = threadIdx.x; k < NP; k += blockDim.x) diag0[k] = G[k * NP + k].re;
-    cholesky_inplace<NP>(G, diag0, rd, N, &bad);
+    for (int k = threadIdx.x; k < NP; k += blockDim.x) {
+        diag0[k] = G[k * NP + k].re;
+        if (k < N && diag0[k] < TINY_NORM) tiny = 1;
+    }
+    cholesky_inplace<NP>(G, diag0, rd, N, &bad, &tiny);
     tri_inverse<NP>(G, rd, X1);
 
     const Cplx *M = X1;  // Q = V M
@@ -540,7 +554,7 @@ __global__ void __launch_bounds__(NTHR, 3) k_block_gs(GsArgs a)
         gram_reduce<NT>(acc, G, NP, lane, wave);
         gram_fix_diag<NT>(G, NP);
         for (int k = threadIdx.x; k < NP; k += blockDim.x) diag0[k] = 1.0;
-        cholesky_inplace<NP>(G, diag0, rd, N, &bad);
+        cholesky_inplace<NP>(G, diag0, rd, N, &bad, &tiny);
         tri_inverse<NP>(G, rd, X2);
         tri_product(X1, X2, G, NP);  // G <- R1^-1 R2^-1
         M = G;
