@@ -298,12 +298,18 @@ __global__ void __launch_bounds__(DIRAC_TL *DIRAC_SITES, 4)
 // side, FP64.  The T lanes of a site share its FP64 field loads; with T = 2S a tile spans two
 // groups of the native layout (lanes t < S the first, t >= S the second), which halves the
 // field loads per right-hand side.  Lanes of a group beyond the last one add nothing.
+// A right-hand side's sums do not depend on how many others share the call, on the slots or on the
+// workspace: a block's chunks are the same at tiles 4 and 8, a chunk is summed over runs of 8 sites (32 at
+// tile 2, 64 at tile 1) by one tree and over the runs in order, a block over its chunks in order.
 // Bound by the traffic between L2 and memory (42 GB by the counters at 32^3 x 64 with 32 right-hand sides
 // in FP32, faces five times what must move) and by the FP64 links and clover, 1.7 KB per lane and site.
 // Operands two hops ahead (two wavefronts per SIMD) beat three without (7.0 -> 6.4 ms with 24
 // right-hand sides; 8.7 ms without, held to 168 VGPRs it spilled); FP64 storage, where they would take
 // 268, goes without.
 constexpr int RES_THREADS = 256;
+template <int T> constexpr int res_sites() { return RES_THREADS / (T == 4 ? 8 : T); }  // of a chunk, at most
+constexpr int RES_SLOTS = 256 / res_sites<8>();  // chunks of a block, at most (blocks hold up to 256 sites)
+template <int T> constexpr int res_runs() { return T == 4 ? 2 : 1; }                   // of sites in a wavefront
 
 // The fields go through LDS where the eight lanes of a site would each take them through L1 and two
 // workgroups still fit in a CU (62 KiB each; with FP64 storage 87, with four lanes 100): 32^3 x 64 with
@@ -320,20 +326,38 @@ __global__ void __launch_bounds__(RES_THREADS, 2) k_residual(KGeo g, const doubl
                                                           Chunks ch, int slots, int ngrp, double *__restrict__ part)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[RES_THREADS / 64][T][2];
+    constexpr int RUNS = res_sites<T>() * T / 64 * res_runs<T>();
+    __shared__ double red[2][RUNS][T][2];
     const ChunkItem w = chunk_item(g, ntiles, slots);
     const int lt = w.tile * T + threadIdx.x % T, grp = lt / g.S, tt = lt % g.S, s = (int)threadIdx.x / T;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nruns = (int)blockDim.x / 64 * res_runs<T>();
     using Tx = typename Elem<Ts>::type;
-    double num = 0, den = 0;
+    double sn = 0, sd = 0;  // the block's sums (threads below T)
+    // one chunk's sums over its runs, added to the block's
+    auto add_chunk = [&](int c) {
+        if (threadIdx.x >= T) return;
+        double cn = 0, cd = 0;
+        for (int k = 0; k < nruns; ++k) {
+            cn += red[c & 1][k][threadIdx.x][0];
+            cd += red[c & 1][k][threadIdx.x][1];
+        }
+        sn += cn;
+        sd += cd;
+    };
     const int c0 = slots == 1 ? 0 : w.slot, c1 = slots == 1 ? ch.n : w.slot + 1;
 #pragma unroll 1
     for (int c = c0; c < c1; ++c) {
         const int o0 = c * ch.sites, ns = g.Vb - o0 < ch.sites ? g.Vb - o0 : ch.sites;
         const bool ok = s < ns && grp < ngrp;
-        if (c > c0) __syncthreads();  // every lane has finished reading the last chunk
+        double num = 0, den = 0;
+        if (c > c0) {
+            __syncthreads();  // every lane has finished reading the last chunk and has left its sums
+            add_chunk(c - 1);
+        }
         Spinor<double> Dx;
-        dirac_chunk<T, (sizeof(Ts) < 8), residual_staged<Ts, T>()>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0, ns,
-                       ok, smem, Dx);
+        dirac_chunk<T, (sizeof(Ts) < 8), residual_staged<Ts, T>()>(g, links, clover, blk_coords, loc_coords,
+                                                                   reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0,
+                                                                   ns, ok, smem, Dx);
         if (ok) {
             Spinor<double> bb;
             load_spinor<double>(g, b, grp, w.blk, o0 + s, tt, bb);
@@ -344,40 +368,55 @@ __global__ void __launch_bounds__(RES_THREADS, 2) k_residual(KGeo g, const doubl
                 den += bb.re[k] * bb.re[k] + bb.im[k] * bb.im[k];
             }
         }
-    }
-    num = wave_sum_mod<T>(num);
-    den = wave_sum_mod<T>(den);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane < T) {
-        red[wave][lane][0] = num;
-        red[wave][lane][1] = den;
+        if constexpr (T == 4) {
+            // two runs of 8 sites per wavefront, lanes 0 .. 31 and 32 .. 63
+            num = lane_xor_sum<4>(lane_xor_sum<8>(lane_xor_sum<16>(num)));
+            den = lane_xor_sum<4>(lane_xor_sum<8>(lane_xor_sum<16>(den)));
+        } else {
+            num = wave_sum_mod<T>(num);
+            den = wave_sum_mod<T>(den);
+        }
+        if ((lane & (64 / res_runs<T>() - 1)) < T) {
+            double *p = red[c & 1][res_runs<T>() * wave + lane / (64 / res_runs<T>())][lane % T];
+            p[0] = num;
+            p[1] = den;
+        }
     }
     __syncthreads();
+    add_chunk(c1 - 1);
     if (threadIdx.x < T) {
-        double sn = 0, sd = 0;
-        const int nw = (blockDim.x + 63) >> 6;
-        for (int k = 0; k < nw; ++k) {
-            sn += red[k][threadIdx.x][0];
-            sd += red[k][threadIdx.x][1];
-        }
         double *p = part + ((((long)w.tile * g.nblk + w.blk) * slots + w.slot) * T + threadIdx.x) * 2;
         p[0] = sn;
         p[1] = sd;
     }
 }
 
-// out[k] = sqrt(sum num / sum den), summed over blocks in a fixed order
+// out[k] = sqrt(sum num / sum den), summed over a block's slots and over the blocks in a fixed order
 template <int T>
-__global__ void k_residual_finish(const double *__restrict__ part, int nblk, int n_rhs, double *__restrict__ out)
+__global__ void k_residual_finish(const double *__restrict__ part, int nblk, int slots, double *__restrict__ out)
 {
     __shared__ double sn[256], sd[256];
     const int k = blockIdx.x;
     const int tile = k / T, t = k % T;
     double a = 0, d = 0;
     for (int blk = threadIdx.x; blk < nblk; blk += blockDim.x) {
-        const double *p = part + (((long)tile * nblk + blk) * T + t) * 2;
-        a += p[0];
-        d += p[1];
+        const double *p = part + (((long)tile * nblk + blk) * slots * T + t) * 2;
+        double bn = p[0], bd = p[1];
+        if (slots > 1) {
+            double cn[RES_SLOTS], cd[RES_SLOTS];  // all loads in flight
+#pragma unroll
+            for (int c = 1; c < RES_SLOTS; ++c) {
+                cn[c] = c < slots ? p[c * T * 2] : 0.0;
+                cd[c] = c < slots ? p[c * T * 2 + 1] : 0.0;
+            }
+#pragma unroll
+            for (int c = 1; c < RES_SLOTS; ++c) {
+                bn += cn[c];
+                bd += cd[c];
+            }
+        }
+        a += bn;
+        d += bd;
     }
     sn[threadIdx.x] = a;
     sd[threadIdx.x] = d;
@@ -389,7 +428,7 @@ __global__ void k_residual_finish(const double *__restrict__ part, int nblk, int
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0 && k < n_rhs) out[k] = sqrt(sn[0]) / sqrt(sd[0]);
+    if (threadIdx.x == 0) out[k] = sqrt(sn[0]) / sqrt(sd[0]);
 }
 
 int round64(int n) { return (n + 63) / 64 * 64; }
@@ -434,27 +473,26 @@ int dirac_dispatch(const mrhs_op *op, const Tc *links, const Tc *clover, const v
     return hip_check(hipGetLastError(), "k_dirac launch");
 }
 
-// lanes per site of the residual: two groups of 4 right-hand sides (one where there is one only:
-// half of the lanes would idle), else as many lanes as the short length allows
+// lanes per site of the residual: 8 where the short length allows (two groups of 4), else as many as
+// it allows; 4 where there are no more right-hand sides (half of the lanes would idle: 32^4, FP32, 950 -> 615 us)
 int residual_tile(const KGeo &g, int n_rhs)
 {
-    if (g.S % 4 == 0) return g.S == 4 && n_rhs <= 4 ? 4 : 8;
+    if (g.S % 4 == 0) return n_rhs <= 4 ? 4 : 8;
     return g.S % 2 == 0 ? 2 : 1;
 }
-int residual_tiles(const KGeo &g, int n_rhs, int T)
-{
-    const int ngrp = (n_rhs + g.S - 1) / g.S;
-    return (ngrp * g.S + T - 1) / T;
-}
+int residual_tiles(int n_rhs, int T) { return (n_rhs + T - 1) / T; }
 
 // A short grid takes one workgroup per chunk (a block's chunks side by side), a long one a workgroup
 // per block, whose chunks follow one another and share one partial sum
-Chunks residual_chunks(const KGeo &g, int T) { return chunks_of(g, RES_THREADS / T); }
+Chunks residual_chunks(const KGeo &g, int T)
+{
+    return chunks_of(g, T >= 4 ? res_sites<8>() : T == 2 ? res_sites<2>() : res_sites<1>());
+}
 int residual_slots(const KGeo &g, int ntiles, int T) { return (long)g.nblk * ntiles < 2048 ? residual_chunks(g, T).n : 1; }
 
 size_t residual_bytes(const KGeo &g, int n_rhs, int T, int slots)
 {
-    return (size_t)residual_tiles(g, n_rhs, T) * T * g.nblk * slots * 2 * sizeof(double);
+    return (size_t)residual_tiles(n_rhs, T) * T * g.nblk * slots * 2 * sizeof(double);
 }
 
 template <typename Ts, int T>
@@ -462,7 +500,7 @@ int residual_launch(const mrhs_op *op, const void *b, const void *x, int n_rhs, 
                     hipStream_t st)
 {
     const KGeo &g = op->k;
-    const int ngrp = (n_rhs + g.S - 1) / g.S, ntiles = residual_tiles(g, n_rhs, T);
+    const int ngrp = (n_rhs + g.S - 1) / g.S, ntiles = residual_tiles(n_rhs, T);
     int slots = residual_slots(g, ntiles, T);
     if (residual_bytes(g, n_rhs, T, slots) > ws_bytes) slots = 1;  // a workspace of the least size
     const Chunks ch = residual_chunks(g, T);
@@ -473,7 +511,7 @@ int residual_launch(const mrhs_op *op, const void *b, const void *x, int n_rhs, 
                        op->links64, op->clover64, op->blk_coords, op->loc_coords, (const Ts *)b, (const Ts *)x, ntiles, ch,
                        slots, ngrp, part);
     if (int rc = hip_check(hipGetLastError(), "k_residual launch")) return rc;
-    hipLaunchKernelGGL((k_residual_finish<T>), dim3(n_rhs), dim3(256), 0, st, part, g.nblk * slots, n_rhs, out);
+    hipLaunchKernelGGL((k_residual_finish<T>), dim3(n_rhs), dim3(256), 0, st, part, g.nblk, slots, out);
     return hip_check(hipGetLastError(), "k_residual_finish launch");
 }
 
@@ -511,7 +549,7 @@ size_t ws_bytes_residual_least(const mrhs_op *op, int n_rhs)
 size_t ws_bytes_residual(const mrhs_op *op, int n_rhs)
 {
     const KGeo &g = op->k;
-    const int T = residual_tile(g, n_rhs), nt = residual_tiles(g, n_rhs, T);
+    const int T = residual_tile(g, n_rhs), nt = residual_tiles(n_rhs, T);
     return residual_bytes(g, n_rhs, T, residual_slots(g, nt, T));
 }
 
