@@ -151,9 +151,8 @@ int mrhs_residual_norms(const mrhs_op *op, const void *b, const void *x, int32_t
  * of ws.  Each device holds one copy of the array until the process ends; the first call on
  * a device looks up its address (no allocation).  The call allocates nothing and never
  * synchronises.  The partial sums take 16 bytes per block and right-hand side, n_rhs rounded
- * up to 4 (up to four right-hand sides) or a multiple of 8 at short lengths 4 and 8, to a multiple of S
- * below; where a short grid takes one workgroup per 32 sites (128 at short length 2) of a block, that many
- * times more, if they fit.  Requests above 32 MiB with one partial sum per block return
+ * up to a multiple of 8 at short lengths 4 and 8, of S below (a short grid takes one workgroup per 32
+ * sites of a block, 128 at short length 2, and that many times more, if they fit); larger requests return
  * MRHS_EUNSUPPORTED (at 48^3 x 96 with 4^4 blocks: up to 48 right-hand sides).  All calls on one
  * device share the array and it keeps the last call's partial sums: calls that overlap in time on
  * one device (other streams, other threads) race and give wrong norms; the caller serialises them. */

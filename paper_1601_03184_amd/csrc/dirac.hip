@@ -5,6 +5,8 @@
 // and one right-hand side.  The T lanes of a site issue the same link and clover loads,
 // so the operator is fetched once per site for the whole tile (the mat-vec -> mat-mat
 // argument of Sec. 6); tiles of one block share an XCD's L2 through xcd_remap.
+#include <algorithm>
+#include <climits>
 #include <mutex>
 #include <type_traits>
 
@@ -541,16 +543,18 @@ int launch_dirac(const mrhs_op *op, const void *x, void *y, int n_rhs, hipStream
     }
 }
 
+// what the entry points ask for: the partial sums of one workgroup per block at the tile of many
+// right-hand sides (at least what tile 4 takes)
 size_t ws_bytes_residual_least(const mrhs_op *op, int n_rhs)
 {
-    return residual_bytes(op->k, n_rhs, residual_tile(op->k, n_rhs), 1);
+    return residual_bytes(op->k, n_rhs, residual_tile(op->k, INT_MAX), 1);
 }
 
 size_t ws_bytes_residual(const mrhs_op *op, int n_rhs)
 {
     const KGeo &g = op->k;
     const int T = residual_tile(g, n_rhs), nt = residual_tiles(n_rhs, T);
-    return residual_bytes(g, n_rhs, T, residual_slots(g, nt, T));
+    return std::max(residual_bytes(g, n_rhs, T, residual_slots(g, nt, T)), ws_bytes_residual_least(op, n_rhs));
 }
 
 namespace {
