@@ -25,7 +25,8 @@
  * kernel layout and a status word, used by mrhs_pack for its FP16 range flag) and, on
  * the first switch to the even-odd block solver, what mrhs_set_block_solver allocates
  * (A^-1 per site and the block's parity order), until mrhs_op_destroy.  No other call
- * allocates device memory; scratch space is passed in as a caller-owned workspace.
+ * allocates device memory; scratch space is passed in as a caller-owned workspace, aligned to 8
+ * bytes (4 suffice for the SAP with FP32 arithmetic).
  *
  * Asynchrony: every call only enqueues work on the given HIP stream (a hipStream_t
  * passed as void*, NULL = the default stream), except mrhs_op_create, mrhs_op_destroy

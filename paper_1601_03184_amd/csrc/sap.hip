@@ -42,16 +42,15 @@ struct FaceGeo {
     int per_blk;   // vectors of one block, in units of S
 };
 
-// 16-byte component vectors
-template <typename Tc> struct V16;
-template <> struct V16<float> {
-    typedef float type __attribute__((ext_vector_type(4)));
-    static constexpr int n = 4;
+// 16-byte component vectors: type in LDS, mem in the caller's workspace, which is aligned to the
+// arithmetic type and to no more (a 16-byte load takes any multiple of 4 bytes)
+template <typename Tc> struct V16 {
+    static constexpr int n = 16 / sizeof(Tc);
+    typedef Tc type __attribute__((ext_vector_type(16 / sizeof(Tc))));
+    typedef Tc mem __attribute__((ext_vector_type(16 / sizeof(Tc)), aligned(alignof(Tc))));
 };
-template <> struct V16<double> {
-    typedef double type __attribute__((ext_vector_type(2)));
-    static constexpr int n = 2;
-};
+static_assert(alignof(V16<float>::mem) == alignof(float) && alignof(V16<double>::mem) == alignof(double),
+              "the workspace needs no more than the arithmetic type's alignment");
 
 template <typename Tc> FaceGeo face_geo(const KGeo &g)
 {
@@ -329,9 +328,9 @@ __device__ inline void block_hops(const KGeo &g, const Tc *__restrict__ links, c
 // what is kept between visits is read and written by this kernel alone, so it takes a layout of
 // its own with a quarter of the load and store instructions of the native one
 template <typename Tc>
-__device__ __forceinline__ typename V16<Tc>::type *sig_ptr(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt)
+__device__ __forceinline__ typename V16<Tc>::mem *sig_ptr(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt)
 {
-    using V = typename V16<Tc>::type;
+    using V = typename V16<Tc>::mem;
     V *base = reinterpret_cast<V *>(sig) + ((size_t)grp * g.nblk + blk) * (24 / V16<Tc>::n) * (size_t)(g.Vb * g.S);
     return base + (uint32_t)(off * g.S + tt);
 }
@@ -340,11 +339,11 @@ template <typename Tc>
 __device__ __forceinline__ void sig_load(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt, Spinor<Tc> &s)
 {
     constexpr int n = V16<Tc>::n;
-    const typename V16<Tc>::type *p = sig_ptr(g, sig, grp, blk, off, tt);
+    const typename V16<Tc>::mem *p = sig_ptr(g, sig, grp, blk, off, tt);
     const uint32_t str = (uint32_t)(g.Vb * g.S);
 #pragma unroll
     for (int v = 0; v < 24 / n; ++v) {
-        const auto q = p[v * str];
+        const typename V16<Tc>::type q = p[v * str];
 #pragma unroll
         for (int c = 0; c < n; c += 2) {
             s.re[(v * n + c) / 2] = q[c];
@@ -357,7 +356,7 @@ template <typename Tc>
 __device__ __forceinline__ void sig_store(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt, const Spinor<Tc> &s)
 {
     constexpr int n = V16<Tc>::n;
-    typename V16<Tc>::type *p = sig_ptr(g, sig, grp, blk, off, tt);
+    typename V16<Tc>::mem *p = sig_ptr(g, sig, grp, blk, off, tt);
     const uint32_t str = (uint32_t)(g.Vb * g.S);
 #pragma unroll
     for (int v = 0; v < 24 / n; ++v) {
@@ -380,7 +379,7 @@ template <typename Tc> struct HalfSpinor {
 template <int MU, typename Ts, typename Tc, typename Tp>
 __device__ __forceinline__ auto face_ptr(const SapArgs<Ts, Tc> &a, Tp *face, int grp, int blk, bool minus, int f, int tt)
 {
-    using V = std::conditional_t<std::is_const<Tp>::value, const typename V16<Tc>::type, typename V16<Tc>::type>;
+    using V = std::conditional_t<std::is_const<Tp>::value, const typename V16<Tc>::mem, typename V16<Tc>::mem>;
     const KGeo &g = a.g;
     V *base = reinterpret_cast<V *>(face) + ((size_t)grp * g.nblk + blk) * (size_t)(a.fg.per_blk * g.S);
     return base + (uint32_t)((a.fg.base[MU] + (minus ? (12 / V16<Tc>::n) * a.fg.vf[MU] : 0) + f) * g.S + tt);
@@ -423,7 +422,7 @@ __device__ __forceinline__ void face_load(const SapArgs<Ts, Tc> &a, int grp, int
     const uint32_t str = (uint32_t)(a.fg.vf[MU] * a.g.S);
 #pragma unroll
     for (int v = 0; v < 12 / n; ++v) {
-        const auto q = p[v * str];
+        const typename V16<Tc>::type q = p[v * str];
 #pragma unroll
         for (int c = 0; c < n; c += 2) {
             const int k = (v * n + c) / 2;
@@ -581,7 +580,7 @@ __device__ __forceinline__ void face_store(const SapArgs<Ts, Tc> &a, int grp, in
                                            const HalfSpinor<Tc> &w)
 {
     constexpr int n = V16<Tc>::n;
-    typename V16<Tc>::type *p = face_ptr<MU>(a, a.face_w, grp, blk, !fwd, face_index<MU>(a, lcp), tt);
+    typename V16<Tc>::mem *p = face_ptr<MU>(a, a.face_w, grp, blk, !fwd, face_index<MU>(a, lcp), tt);
     const uint32_t str = (uint32_t)(a.fg.vf[MU] * a.g.S);
 #pragma unroll
     for (int v = 0; v < 12 / n; ++v) {
