@@ -667,14 +667,9 @@ int launch_coarse_self_inverse(const mrhs_op *op, const float *Dc, int n_tv, flo
                                hipStream_t st)
 {
     const size_t lds = coarse_inverse_lds_bytes(n_tv);
-    static size_t done = 0;
-    if (lds > 65536 && lds > done) {
-        if (int rc = hip_check(hipFuncSetAttribute((const void *)k_coarse_self_inverse,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                               "hipFuncSetAttribute(coarse self inverse LDS)"))
-            return rc;
-        done = lds;
-    }
+    if (int rc = allow_lds((const void *)k_coarse_self_inverse, lds, coarse_inverse_lds_bytes(32),
+                           "hipFuncSetAttribute(coarse self inverse LDS)"))
+        return rc;
     if (status) {
         hipLaunchKernelGGL(k_inv_status_init, dim3(1), dim3(1), 0, st, status);
         if (int rc = hip_check(hipGetLastError(), "k_inv_status_init launch")) return rc;

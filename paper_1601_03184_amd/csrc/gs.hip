@@ -613,14 +613,7 @@ template <typename Tv, typename Tq, int NT> int launch_typed(const GsArgs &a, in
 {
     const size_t lds = gs_lds(NT * 16);
     if (lds > max_lds) return set_error(MRHS_EUNSUPPORTED, "Gram-Schmidt LDS exceeds the workgroup limit");
-    static size_t done = 0;
-    if (lds > 65536 && lds > done) {
-        if (int rc = hip_check(hipFuncSetAttribute((const void *)k_block_gs<Tv, Tq, NT>,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                               "hipFuncSetAttribute(gs LDS)"))
-            return rc;
-        done = lds;
-    }
+    if (int rc = allow_lds((const void *)k_block_gs<Tv, Tq, NT>, lds, lds, "hipFuncSetAttribute(gs LDS)")) return rc;
     hipLaunchKernelGGL((k_block_gs<Tv, Tq, NT>), dim3(2 * n_agg), dim3(NTHR), lds, st, a);
     return hip_check(hipGetLastError(), "k_block_gs launch");
 }

@@ -4,6 +4,16 @@
 
 #include "internal.h"
 
+// Lets kernel fn be launched with up to `most` bytes of dynamic LDS on the current device; lds: what
+// this launch takes (the first 64 KiB need no call).  `most` is one value per kernel, whatever the launch,
+// and nothing is remembered: the limit is per device, and a smaller one set by another thread in
+// between would refuse the launch.
+inline int allow_lds(const void *fn, size_t lds, size_t most, const char *what)
+{
+    if (lds <= 65536) return MRHS_OK;
+    return hip_check(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most), what);
+}
+
 // A^-1 of the op's clover term per site (FP64, and FP32 when the op has FP32 fields);
 // *bad (device) is set to 1 where a 6x6 block has no usable pivot
 int launch_clover_inverse(mrhs_op *op, int *bad, hipStream_t st);

@@ -1260,16 +1260,10 @@ template <typename Ts, typename Tc> size_t odd_bytes(const mrhs_op *op, int n_rh
 }
 
 template <typename Ts, typename Tc, int T, bool EO, int NL = 0>
-int launch_batched(const SapBatch<Ts, Tc> &B, int threads, size_t lds, hipStream_t st)
+int launch_batched(const SapBatch<Ts, Tc> &B, int threads, size_t lds, size_t max_lds, hipStream_t st)
 {
     const void *fn = EO ? (const void *)k_sap_batched_eo<Ts, Tc, T> : (const void *)k_sap_batched<Ts, Tc, T, NL>;
-    static size_t done = 0;
-    if (lds > 65536 && lds > done) {
-        if (int rc = hip_check(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                               "hipFuncSetAttribute(batched sap LDS)"))
-            return rc;
-        done = lds;
-    }
+    if (int rc = allow_lds(fn, lds, max_lds, "hipFuncSetAttribute(batched sap LDS)")) return rc;
     if constexpr (EO) {
         hipLaunchKernelGGL((k_sap_batched_eo<Ts, Tc, T>), dim3(B.first[B.n_inst]), dim3(threads), lds, st, B);
         return hip_check(hipGetLastError(), "k_sap_batched_eo launch");
@@ -1285,7 +1279,7 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
 {
     // one tile for the whole batch: the smallest of the operators' tiles (all divide S)
     int T = 4, maxVb = 0;
-    size_t max_lds = ops[0]->max_lds;
+    const size_t max_lds = ops[0]->max_lds;
     const bool eo = ops[0]->block_solver == MRHS_BLOCK_EO_MR;
     for (int k = 0; k < n; ++k) {
         T = std::min(T, ops[k]->sap_tile);
@@ -1389,22 +1383,22 @@ int sap_batched_dispatch(const mrhs_op *const *ops, int n, const void *const *b,
             const int thr = eo ? eo_threads : threads;
             switch (T * 2 + (eo ? 1 : 0)) {
             case 2:
-                rc = ll ? launch_batched<Ts, Tc, 1, false, staged_links(1)>(B, thr, lds, st)
-                        : launch_batched<Ts, Tc, 1, false>(B, thr, lds, st);
+                rc = ll ? launch_batched<Ts, Tc, 1, false, staged_links(1)>(B, thr, lds, max_lds, st)
+                        : launch_batched<Ts, Tc, 1, false>(B, thr, lds, max_lds, st);
                 break;
             case 4:
-                rc = ll ? launch_batched<Ts, Tc, 2, false, staged_links(2)>(B, thr, lds, st)
-                        : launch_batched<Ts, Tc, 2, false>(B, thr, lds, st);
+                rc = ll ? launch_batched<Ts, Tc, 2, false, staged_links(2)>(B, thr, lds, max_lds, st)
+                        : launch_batched<Ts, Tc, 2, false>(B, thr, lds, max_lds, st);
                 break;
-            case 3: rc = launch_batched<Ts, Tc, 1, true>(B, thr, lds, st); break;
-            case 5: rc = launch_batched<Ts, Tc, 2, true>(B, thr, lds, st); break;
+            case 3: rc = launch_batched<Ts, Tc, 1, true>(B, thr, lds, max_lds, st); break;
+            case 5: rc = launch_batched<Ts, Tc, 2, true>(B, thr, lds, max_lds, st); break;
             default:
                 // tile 4 only with FP32 arithmetic (FP64 would spill to scratch)
                 if constexpr (sizeof(Tc) == 4) {
                     if (T == 4) {
-                        rc = eo ? launch_batched<Ts, Tc, 4, true>(B, thr, lds, st)
-                           : ll ? launch_batched<Ts, Tc, 4, false, staged_links(4)>(B, thr, lds, st)
-                                : launch_batched<Ts, Tc, 4, false>(B, thr, lds, st);
+                        rc = eo ? launch_batched<Ts, Tc, 4, true>(B, thr, lds, max_lds, st)
+                           : ll ? launch_batched<Ts, Tc, 4, false, staged_links(4)>(B, thr, lds, max_lds, st)
+                                : launch_batched<Ts, Tc, 4, false>(B, thr, lds, max_lds, st);
                         break;
                     }
                 }
