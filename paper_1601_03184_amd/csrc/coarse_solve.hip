@@ -79,7 +79,8 @@ __device__ inline long cre(const GmArgs &a, long e, int k) { return (2 * e) * a.
 
 constexpr int GPART = 512;  // partial-sum blocks per inner-product launch (all vectors together)
 constexpr int FV = 8;       // basis vectors that the fused projection takes
-constexpr int FBLK = 512;   // its partial-sum blocks, each for all vectors
+constexpr int FBLK = 512;   // its chunks, each with partial sums for all vectors
+static_assert(FV <= DROWS, "k_gm_project adds up one vector per row");
 
 // start: beta = ||b|| (from ||b||^2), g = (beta, 0, ...), H = 0, scale = 1 / beta
 __device__ void gm_start(const GmArgs &a, int k, double b2)
@@ -253,21 +254,28 @@ template <typename TV> __global__ void __launch_bounds__(GTHR) k_gm_axpy(GmArgs 
 
 // The projection w -= sum_i hcur[k][i] V_i (i < nvec <= FV) and the inner products that follow it
 // in one pass over w and the basis: of the new w with every V_i (the second Gram-Schmidt pass
-// projects with them), or with itself (NORM).  A block takes a chunk of entries for all
-// right-hand sides, a thread one right-hand side and every DROWS-th entry of the chunk.  Bound by its
-// reads: an Arnoldi step reads the basis three times instead of four (8192 coarse sites with 64
-// degrees of freedom, 32 right-hand sides: the vector kernels of a solve 3.5 -> 2.6 ms).
-template <typename TV, bool NORM> __global__ void __launch_bounds__(DTHR) k_gm_project(GmArgs a, int nvec)
+// projects with them), or with itself (NORM).  Chunk vb of the G chunks of entries is taken for all
+// right-hand sides by ldc of a row's 32 lanes, a thread one right-hand side and every DROWS-th entry; a
+// workgroup takes nv chunks side by side.  Bound by its reads: an Arnoldi step reads the basis three
+// times instead of four (8192 coarse sites with 64 degrees of freedom, 32 right-hand sides: the vector
+// kernels of a solve 3.5 -> 2.6 ms).  With few right-hand sides the lanes of one chunk leave most of a
+// wavefront idle and the workgroups, one per CU, take two rounds: two chunks where they fit (4096 sites,
+// 64 degrees of freedom, 8 iterations for 1, 8 and 16 right-hand sides 4620, 3930 and 4270 us with one
+// chunk, 3700, 3610 and 4000 with two; 4280, 3990 and 4650 with the projection on its own).
+template <typename TV, bool NORM>
+__global__ void __launch_bounds__(DTHR) k_gm_project(GmArgs a, int G, int nvec, int nv)
 {
-    __shared__ Z red[DROWS][32];
-    if (!gm_running(a)) return;
     constexpr int NA = NORM ? 1 : FV;
-    const int G = gridDim.x, k = threadIdx.x & 31, row = threadIdx.x >> 5;
-    const long chunk = (a.dim + G - 1) / G, e0 = blockIdx.x * chunk, e1 = e0 + chunk < a.dim ? e0 + chunk : a.dim;
+    __shared__ Z red[NA][DROWS][32];
+    if (!gm_running(a)) return;
+    const int lane = threadIdx.x & 31, row = threadIdx.x >> 5, v = lane / a.ldc, k = lane - v * a.ldc;
+    const int vb = blockIdx.x * nv + v;
+    const bool ok = v < nv && vb < G;
+    const long chunk = (a.dim + G - 1) / G, e0 = vb * chunk, e1 = e0 + chunk < a.dim ? e0 + chunk : a.dim;
     Z acc[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) acc[i] = {0.0, 0.0};
-    if (k < a.ldc) {
+    if (ok) {
         Z h[FV];
 #pragma unroll
         for (int i = 0; i < FV; ++i) {
@@ -280,9 +288,9 @@ template <typename TV, bool NORM> __global__ void __launch_bounds__(DTHR) k_gm_p
 #pragma unroll
             for (int i = 0; i < FV; ++i)
                 if (i < nvec) {
-                    const TV *v = (const TV *)a.V + (long)i * a.cvlen;
-                    vr[i] = v[o];
-                    vi[i] = v[o + a.ldc];
+                    const TV *p = (const TV *)a.V + (long)i * a.cvlen;
+                    vr[i] = p[o];
+                    vi[i] = p[o + a.ldc];
                 }
             double wr = a.w[o], wi = a.w[o + a.ldc];
 #pragma unroll
@@ -311,20 +319,17 @@ template <typename TV, bool NORM> __global__ void __launch_bounds__(DTHR) k_gm_p
             }
         }
     }
+    // the rows' sums, vector i's added up in order by row i
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        if (!NORM && i >= nvec) break;
-        __syncthreads();
-        red[row][k] = acc[i];
-        __syncthreads();
-        if (row == 0 && k < a.ldc) {
-            Z t = red[0][k];
-            for (int r = 1; r < DROWS; ++r) {
-                t.re += red[r][k].re;
-                t.im += red[r][k].im;
-            }
-            a.part[((long)i * G + blockIdx.x) * a.ldc + k] = t;
+    for (int i = 0; i < NA; ++i) red[i][row][lane] = acc[i];
+    __syncthreads();
+    if (row < (NORM ? 1 : nvec) && ok) {
+        Z t = red[row][0][lane];
+        for (int r = 1; r < DROWS; ++r) {
+            t.re += red[row][r][lane].re;
+            t.im += red[row][r][lane].im;
         }
+        a.part[((long)row * G + vb) * a.ldc + k] = t;
     }
 }
 
@@ -566,8 +571,9 @@ int gmres_run(GmArgs &a, const float *b, float *u, int m, double *res_out, int32
         hipLaunchKernelGGL(k_gm_finish, dim3((nvec * a.ldc * FR + 255) / 256), dim3(256), 0, st, a, G, nvec, col, step);
         return hip_check(hipGetLastError(), "k_gm_finish launch");
     };
-    // blocks of the fused projection: at least 4 entries per thread
+    // chunks of the fused projection: at least 4 entries per thread
     const int G2 = (int)std::max<long>(1, std::min<long>((a.dim + 4 * DROWS - 1) / (4 * DROWS), FBLK));
+    const int nv = a.ldc <= 16 ? 2 : 1;  // and how many of them a workgroup takes
     auto dots = [&](auto X, long xstride, int nvec, const float *y, int col, int step) {
         using TX = std::remove_const_t<std::remove_pointer_t<decltype(X)>>;
         const int G = gm_blocks(a, nvec);
@@ -588,10 +594,10 @@ int gmres_run(GmArgs &a, const float *b, float *u, int m, double *res_out, int32
         if (int rc = dots((const TV *)V, a.cvlen, j + 1, a.w, j, GM_PROJECT)) return rc;
         if (j < FV) {
             // up to FV basis vectors: each projection with the inner products that follow it
-            hipLaunchKernelGGL((k_gm_project<TV, false>), dim3(G2), dim3(DTHR), 0, st, a, j + 1);
+            hipLaunchKernelGGL((k_gm_project<TV, false>), dim3((G2 + nv - 1) / nv), dim3(DTHR), 0, st, a, G2, j + 1, nv);
             GM_CHECK("k_gm_project launch");
             if (int rc = finish(G2, j + 1, j, GM_PROJECT)) return rc;
-            hipLaunchKernelGGL((k_gm_project<TV, true>), dim3(G2), dim3(DTHR), 0, st, a, j + 1);
+            hipLaunchKernelGGL((k_gm_project<TV, true>), dim3((G2 + nv - 1) / nv), dim3(DTHR), 0, st, a, G2, j + 1, nv);
             GM_CHECK("k_gm_project launch");
             if (int rc = finish(G2, 1, j, GM_NORM)) return rc;
         } else {
