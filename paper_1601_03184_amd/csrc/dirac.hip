@@ -43,7 +43,7 @@ __global__ void __launch_bounds__(256 * T) k_dirac(KGeo g, const Tc *__restrict_
 }
 
 // The stencil with the workgroup's own sites in LDS.  A workgroup takes a chunk of consecutive sites
-// of a block for TL right-hand sides (TL lanes per site; TL = 2 S: two groups of the layout): every
+// of a block for TL right-hand sides (TL lanes per site; lane t has lane (tile TL + t) % S of a group): every
 // spinor of the chunk is read once from global memory instead of once per neighbour, and a
 // hop reads LDS where the neighbour lies in the chunk, global memory where it does not (the
 // lanes of either kind share the hop's arithmetic).  With AHEAD the global operands of a hop are
@@ -245,6 +245,8 @@ __device__ __forceinline__ void dirac_chunk(const KGeo &g, const Tf *__restrict_
     direction(std::integral_constant<int, 3>{});
 }
 
+int round64(int n) { return (n + 63) / 64 * 64; }
+
 // Sites per workgroup: the block cut into equal chunks of at most `most` sites
 struct Chunks {
     int n, sites;
@@ -276,10 +278,15 @@ __device__ inline ChunkItem chunk_item(const KGeo &g, int ntiles, int slots)
 // per CU.  Bound by the traffic between L2 and memory, three quarters of it neighbours' faces (a face
 // in x is every fourth site of the neighbouring block): 32^3 x 64, 24 right-hand sides in FP32 6.5 -> 4.9 ms
 // (10.9 GB once each, 28 GB by the counters, 5.7 TB/s), 16^4 with 20 158 -> 120 us.
-constexpr int DIRAC_TL = 4, DIRAC_SITES = 128;
+// TL lanes per site: 4, one group, or where 8 still share a wavefront at most (DIRAC_SMALL sites, several
+// groups) two groups: 8 right-hand sides in FP32 at 4 / 8 lanes, us: one site per block at 16^4 431 / 245, 4
+// sites at 24^4 695 / 427, 8 sites 412 / 306, 12 sites 303 / 325.
+// Binary16 spinors are converted where they are used and are not loaded two hops ahead: with 128 VGPRs
+// that spilled 19 (16^4, 20 right-hand sides 104 / 86 us ahead / not ahead, 24^4 with 24 735 / 582).
+constexpr int DIRAC_THREADS = 512, DIRAC_SMALL = 8;
 
-template <typename Ts, typename Tc>
-__global__ void __launch_bounds__(DIRAC_TL *DIRAC_SITES, 4)
+template <typename Ts, typename Tc, int TL>
+__global__ void __launch_bounds__(DIRAC_THREADS, 4)
     k_dirac_chunk(KGeo g, const Tc *__restrict__ links, const Tc *__restrict__ clover,
                   const uint32_t *__restrict__ blk_coords, const uint32_t *__restrict__ loc_coords,
                   const Ts *__restrict__ x, Ts *__restrict__ y, int ntiles, Chunks ch, int ngrp)
@@ -287,13 +294,24 @@ __global__ void __launch_bounds__(DIRAC_TL *DIRAC_SITES, 4)
     extern __shared__ __align__(16) unsigned char smem[];
     const ChunkItem w = chunk_item(g, ntiles, ch.n);
     const int o0 = w.slot * ch.sites, ns = g.Vb - o0 < ch.sites ? g.Vb - o0 : ch.sites;
-    const int lt = w.tile * DIRAC_TL + threadIdx.x % DIRAC_TL, grp = lt / g.S, tt = lt % g.S;
-    const bool ok = (int)threadIdx.x / DIRAC_TL < ns && grp < ngrp;
+    const int lt = w.tile * TL + threadIdx.x % TL, grp = lt / g.S, tt = lt % g.S;
+    const bool ok = (int)threadIdx.x / TL < ns && grp < ngrp;
     Spinor<Tc> out;
     using Tx = typename Elem<Ts>::type;
-    dirac_chunk<DIRAC_TL, true, false>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk, o0,
-                          ns, ok, smem, out);
-    if (ok) store_spinor(g, y, grp, w.blk, o0 + (int)threadIdx.x / DIRAC_TL, tt, out);
+    dirac_chunk<TL, (sizeof(Ts) > 2), false>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk,
+                                 o0, ns, ok, smem, out);
+    if (ok) store_spinor(g, y, grp, w.blk, o0 + (int)threadIdx.x / TL, tt, out);
+}
+
+template <typename Ts, typename Tc, int TL>
+void dirac_chunk_launch(const mrhs_op *op, const Tc *links, const Tc *clover, const void *x, void *y, int ngrp,
+                        hipStream_t st)
+{
+    const KGeo &g = op->k;
+    const Chunks ch = chunks_of(g, DIRAC_THREADS / TL);
+    const int threads = round64(ch.sites * TL), ntiles = (ngrp * g.S + TL - 1) / TL;
+    hipLaunchKernelGGL((k_dirac_chunk<Ts, Tc, TL>), dim3(g.nblk * ntiles * ch.n), dim3(threads), 24 * sizeof(Ts) * threads,
+                       st, g, links, clover, op->blk_coords, op->loc_coords, (const Ts *)x, (Ts *)y, ntiles, ch, ngrp);
 }
 
 // Per (block, tile of T right-hand sides, slot): partial sums of |b - D x|^2 and |b|^2 per right-hand
@@ -433,8 +451,6 @@ __global__ void k_residual_finish(const double *__restrict__ part, int nblk, int
     if (threadIdx.x == 0) out[k] = sqrt(sn[0]) / sqrt(sd[0]);
 }
 
-int round64(int n) { return (n + 63) / 64 * 64; }
-
 template <typename Ts, typename Tc>
 int dirac_dispatch(const mrhs_op *op, const Tc *links, const Tc *clover, const void *x, void *y, int n_rhs,
                    hipStream_t st)
@@ -457,11 +473,8 @@ int dirac_dispatch(const mrhs_op *op, const Tc *links, const Tc *clover, const v
         // tile 4 only with FP32 arithmetic (FP64 would spill to scratch)
         if constexpr (sizeof(Tc) == 4) {
             if (g.S == 4) {
-                const Chunks ch = chunks_of(g, DIRAC_SITES);
-                const int threads = round64(ch.sites * DIRAC_TL);
-                hipLaunchKernelGGL((k_dirac_chunk<Ts, Tc>), dim3(g.nblk * ngrp * ch.n), dim3(threads),
-                                   24 * sizeof(Ts) * threads, st, g, links, clover, op->blk_coords, op->loc_coords,
-                                   (const Ts *)x, (Ts *)y, ngrp, ch, ngrp);
+                if (g.Vb <= DIRAC_SMALL && ngrp > 1) dirac_chunk_launch<Ts, Tc, 8>(op, links, clover, x, y, ngrp, st);
+                else dirac_chunk_launch<Ts, Tc, 4>(op, links, clover, x, y, ngrp, st);
                 break;
             }
             hipLaunchKernelGGL((k_dirac<Ts, Tc, 4>), grid, block, 0, st, g, links, clover, op->blk_coords,
