@@ -26,7 +26,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 __device__ inline f4 mfma32(float x, float y, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0); }
 
 constexpr int TTHR = 256;  // 4 wavefronts
-constexpr int PSPLIT = 4;  // workgroups per aggregate half in the prolongation
+constexpr int PSPLIT = 4;  // workgroups per aggregate half in the prolongation, at most
 constexpr int TNW = TTHR / 64;
 
 template <typename T> __device__ inline float to_f32(T v) { return (float)v; }
@@ -35,6 +35,8 @@ template <> __device__ inline float to_f32<__half>(__half v) { return __half2flo
 struct TransArgs {
     KGeo g;
     int Va, n_agg, N, n, ldc;
+    int sshift;  // log2 of the short length S
+    size_t gsz;  // elements of one group
     const int32_t *agg_sites;
     const void *Q;  // native test vectors (N of them)
     const void *y;  // native fine vectors (n of them)
@@ -44,10 +46,9 @@ struct TransArgs {
 };
 
 // vector k of a native set: group and lane part of the element offset
-__device__ inline size_t tcol_off(const KGeo &g, int k)
+__device__ inline size_t tcol_off(const TransArgs &a, int k)
 {
-    const int grp = k / g.S, t = k - grp * g.S;
-    return (size_t)grp * g.nblk * 24 * g.Vb * g.S + t;
+    return (size_t)(k >> a.sshift) * a.gsz + (k & ((1 << a.sshift) - 1));
 }
 
 __device__ inline void stage_agg_sites(const TransArgs &a, int i, uint32_t *sbase)
@@ -114,12 +115,12 @@ __global__ void __launch_bounds__(TTHR) k_restrict(TransArgs a)
 #pragma unroll
     for (int t = 0; t < NJ; ++t) {
         const int j = 16 * t + (lane & 15);
-        qp[t] = static_cast<const Tq *>(a.Q) + (j < a.N ? tcol_off(a.g, j) : 0);
+        qp[t] = static_cast<const Tq *>(a.Q) + (j < a.N ? tcol_off(a, j) : 0);
     }
 #pragma unroll
     for (int t = 0; t < NK; ++t) {
         const int k = 16 * t + (lane & 15);
-        yp[t] = static_cast<const Ty *>(a.y) + (k < a.n ? tcol_off(a.g, k) : 0);
+        yp[t] = static_cast<const Ty *>(a.y) + (k < a.n ? tcol_off(a, k) : 0);
     }
     const int nbq = (a.Va + 15) / 16, nblocks = 6 * nbq;
     using Raw = RestrictRaw<Tq, Ty, NJ, NK>;
@@ -215,8 +216,8 @@ __global__ void __launch_bounds__(TTHR) k_restrict(TransArgs a)
 }
 
 // ---------------------------------------------------------------------------------------
-// prolongation: PSPLIT workgroups per (aggregate i, half h), each taking every PSPLIT-th
-// group of 16-row blocks (the output rows are independent).  (y_c)^h_i is staged in LDS;
+// prolongation: up to PSPLIT workgroups per (aggregate i, half h), as many as its 16-row blocks fill with
+// a block per wavefront, each taking every PSPLIT-th group of them (the output rows are independent).  (y_c)^h_i is staged in LDS;
 // each wavefront forms 16-row blocks of Q^h_i (y_c)^h_i, K = the test vectors.  Operand row
 // 4g + q of a block is site s0 + 4q + g, so that accumulator register q of the four lane
 // groups g = l/16 holds four neighbouring sites and a store covers their runs side by side.
@@ -248,19 +249,20 @@ __global__ void __launch_bounds__(TTHR) k_prolong(TransArgs a)
         const int k = 16 * t + (lane & 15);
         kok[t] = k < nw;
         kin[t] = k < a.n;
-        yoff[t] = kok[t] ? tcol_off(a.g, k) : 0;
+        yoff[t] = kok[t] ? tcol_off(a, k) : 0;
     }
     const int nbq = (a.Va + 15) / 16, nblocks = 6 * nbq;
     const int r16 = lane & 15, asite = 4 * (r16 & 3) + (r16 >> 2);  // A operand row -> site of the block
     // this lane's columns j = 4 ks + l/16: vectors out of range read vector 0 and meet zero rows
     // of (y_c)^h_i
+    const int KS = (a.N + 3) / 4;
     size_t qoff[8];
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
+        if (ks >= KS) break;
         const int j = 4 * ks + (lane >> 4);
-        qoff[ks] = j < a.N ? tcol_off(a.g, j) : 0;
+        qoff[ks] = j < a.N ? tcol_off(a, j) : 0;
     }
-    const int KS = (a.N + 3) / 4;
     for (int B = wave + TNW * (int)blockIdx.y; B < nblocks; B += TNW * (int)gridDim.y) {
         const RowBlock rb = row_block(B, nbq, h, cstr);
         const int n = rb.s0 + asite;
@@ -714,6 +716,8 @@ TransArgs trans_args(const mrhs_op *op, int n_tv, int n)
     a.N = n_tv;
     a.n = n;
     a.ldc = (n + 3) / 4 * 4;
+    while ((1 << a.sshift) < op->k.S) ++a.sshift;
+    a.gsz = (size_t)op->k.nblk * 24 * op->k.Vb * op->k.S;
     a.agg_sites = op->agg_sites;
     return a;
 }
@@ -732,7 +736,7 @@ template <typename Tq, typename Ty> int restrict_typed(const TransArgs &a, hipSt
 template <typename Tq, typename Ty> int prolong_typed(const TransArgs &a, hipStream_t st)
 {
     const size_t lds = sizeof(uint32_t) * a.Va + sizeof(float) * 2048;
-    const dim3 grid(2 * a.n_agg, PSPLIT);
+    const dim3 grid(2 * a.n_agg, std::min(PSPLIT, (6 * ((a.Va + 15) / 16) + TNW - 1) / TNW));
     if (a.n > 16) hipLaunchKernelGGL((k_prolong<Tq, Ty, 2>), grid, dim3(TTHR), lds, st, a);
     else hipLaunchKernelGGL((k_prolong<Tq, Ty, 1>), grid, dim3(TTHR), lds, st, a);
     return hip_check(hipGetLastError(), "k_prolong launch");
