@@ -5,7 +5,7 @@
 // colour x a tile of T right-hand sides; thread (off, t) owns one site of the block and
 // one right-hand side.  The workgroup
 //   1. forms the residual r = b - D x on its block: the full stencil on a first visit from a
-//      guess, afterwards the block's kept residual (even-odd: b - D_j x_j, formed again from the stored
+//      guess, afterwards the block's kept residual (even-odd: formed again from b and the stored
 //      x) minus the hops across its faces, which the neighbours left, spin-projected and multiplied by
 //      the link, in face buffers (read once and in order, a quarter of the loads of reading the
 //      neighbours' spinors across the faces; all of them in flight at once),
@@ -19,7 +19,7 @@
 // residual, 3-10 for the end).  32^3 x 64, 32 right-hand sides in FP32, 3 x 4, tile 4: 49.5 -> 46.5 ms per call
 // with the face buffers (of the 30 vector sets that a call must move at 4.4 TB/s, 22 ms), 42.2 with the reductions
 // by lane exchanges, 16-byte LDS vectors and the end of a visit without spills; the even-odd solver, which
-// formed the full residual at every visit from global memory, 3.34 -> 2.85 ms at 16^3 x 32 with 24, 3 x 3 (2.60
+// formed the full residual at every visit from global memory, 3.34 -> 2.70 ms at 16^3 x 32 with 24, 3 x 3 (2.60
 // with a kept Schur residual, which the roundings of x left: see sap_block_eo).
 // The links and clover of a site are loaded once per stencil for all T lanes of the site.
 // With the even-odd block solver (k_sap_batched_eo) step 2 runs on the block's Schur
@@ -595,12 +595,12 @@ __device__ __forceinline__ void face_store(const SapArgs<Ts, Tc> &a, int grp, in
     }
 }
 
-// The end of a visit on one site: x (+)= e, the faces of the change of the stored x (the correction
+// The end of a visit on one site: x = e or with add x + e, the faces of the change of the stored x (the correction
 // as rounded to the storage type; without inc of x) and, with inc, rho for later visits (keep():
 // stores it).  The links of two directions are loaded ahead.
 template <typename Ts, typename Tc, typename Keep>
 __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, int blk, int off, uint32_t bcp,
-                                            uint32_t lcp, int tt, Spinor<Tc> &e, Keep keep)
+                                            uint32_t lcp, int tt, Spinor<Tc> &e, bool add, Keep keep)
 {
     const KGeo &g = a.g;
     sched_fence();
@@ -616,7 +616,7 @@ __device__ __forceinline__ void finish_site(const SapArgs<Ts, Tc> &a, int grp, i
     if (on[0]) face_link<0>(a, blk, off, bcp, ff[0], l0);
     if (on[1]) face_link<1>(a, blk, off, bcp, ff[1], l1);
     Spinor<Tc> xn;
-    if (a.mode == 2) {
+    if (add) {
         Spinor<Tc> xo;
         load_spinor<Tc>(g, a.x, grp, blk, off, tt, xo);
 #pragma unroll
@@ -858,7 +858,7 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
 
     // 3. x|_j (+)= e, and with the incremental residual rho and the faces for later visits
     if (active)
-        finish_site(a, grp, blk, off, bcp, (uint32_t)opaque_index((int)lcp), tt, e, [&]() __attribute__((always_inline)) {
+        finish_site(a, grp, blk, off, bcp, (uint32_t)opaque_index((int)lcp), tt, e, a.mode == 2, [&]() __attribute__((always_inline)) {
             Spinor<Tc> rr;
             lds_load<Tc>(rho, str, me, rr);
             sig_store(g, a.sig, grp, blk, off, tt, rr);
@@ -904,6 +904,28 @@ __device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho,
     hop_fence(h);
 }
 
+// q = (ADD: +=) the clover term at one of the even sites, one chiral half at a time
+template <bool ADD, typename Ts, typename Tc>
+__device__ inline void eo_clover(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int str, int me, int ns, Spinor<Tc> &q)
+{
+    {
+        Spinor<Tc> own;
+        Tc A[36];
+        lds_load_half<0, Tc>(rho, str, me, own);
+        load_clover_half<0>(a.clover, a.g.V, ns, A);
+        clover_half<0, ADD>(A, own, q);
+    }
+    hop_fence(q);
+    {
+        Spinor<Tc> own;
+        Tc A[36];
+        lds_load_half<1, Tc>(rho, str, me, own);
+        load_clover_half<1>(a.clover, a.g.V, ns, A);
+        clover_half<1, ADD>(A, own, q);
+    }
+    hop_fence(q);
+}
+
 // The residual of one site at a first visit, to LDS: b (x = 0 everywhere), b minus the face hops (x = 0
 // on the block), or from a guess the full b - D x.
 template <typename Ts, typename Tc, int T>
@@ -938,48 +960,18 @@ __device__ inline void eo_residual(const SapArgs<Ts, Tc> &a, LdsPair<Tc> *rho, i
     lds_store<Tc>(rho, g.Vb * T, off * T + t, r);
 }
 
-// The residual of one site at a later visit: b - D_j x_j, the block's x as stored read from LDS, minus
-// the face hops of the neighbours' x.
-template <typename Ts, typename Tc, int T>
-__device__ inline void eo_residual_again(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int blk, int off, int grp,
-                                         int tt, int t, Spinor<Tc> &r)
+// c = b minus the face hops of the neighbours' x at one site: what a later visit solves D_j x_j = c for
+template <typename Ts, typename Tc>
+__device__ __forceinline__ void eo_rhs(const SapArgs<Ts, Tc> &a, int blk, int off, int grp, int tt, uint32_t lcp,
+                                       Spinor<Tc> &c)
 {
-    const KGeo &g = a.g;
-    const int str = g.Vb * T, ns = opaque_index(blk * g.Vb + off), me = off * T + t;
-    const uint32_t lcp = a.loc_coords[off];
-    {
-        Spinor<Tc> own;
-        Tc A[36];
-        lds_load_half<0, Tc>(rho, str, me, own);
-        load_clover_half<0>(a.clover, g.V, ns, A);
-        clover_half<0>(A, own, r);
-    }
-    hop_fence(r);
-    {
-        Spinor<Tc> own;
-        Tc A[36];
-        lds_load_half<1, Tc>(rho, str, me, own);
-        load_clover_half<1>(a.clover, g.V, ns, A);
-        clover_half<1>(A, own, r);
-    }
-    hop_fence(r);
-    eo_hops<Ts, Tc, T>(a, rho, ns, off, t, lcp, r);
-    {
-        Spinor<Tc> f;
-        face_sum(a, grp, blk, a.blk_coords[blk], lcp, tt, f);
+    Spinor<Tc> f;
+    load_spinor<Tc>(a.g, a.b, grp, blk, off, tt, c);
+    face_sum(a, grp, blk, a.blk_coords[blk], lcp, tt, f);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            r.re[c] += f.re[c];
-            r.im[c] += f.im[c];
-        }
-    }
-    hop_fence(r);
-    Spinor<Tc> bb;
-    load_spinor<Tc>(g, a.b, grp, blk, off, tt, bb);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        r.re[c] = bb.re[c] - r.re[c];
-        r.im[c] = bb.im[c] - r.im[c];
+    for (int k = 0; k < 12; ++k) {
+        c.re[k] -= f.re[k];
+        c.im[k] -= f.im[k];
     }
 }
 
@@ -989,7 +981,10 @@ __device__ inline void eo_update_x(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *
 {
     Spinor<Tc> e;
     lds_load<Tc>(rho, a.g.Vb * T, off * T + t, e);
-    finish_site(a, grp, blk, off, a.blk_coords[blk], a.loc_coords[off], tt, e, []() {});
+    const uint32_t lcp = a.loc_coords[off];
+    const int odd = (unpack_coord(lcp, 0) + unpack_coord(lcp, 1) + unpack_coord(lcp, 2) + unpack_coord(lcp, 3)) & 1;
+    // (a later visit leaves the odd sites' new x itself)
+    finish_site(a, grp, blk, off, a.blk_coords[blk], lcp, tt, e, a.mode == 2 && !(a.sig_in && odd), []() {});
 }
 
 // The even-odd block solver (DD-alpha-AMG's): with a block's sites split by the parity of
@@ -1019,57 +1014,81 @@ __device__ inline void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile,
     // local coordinates of the even and the odd site, 8 bits each
     const uint32_t lce = active ? a.loc_coords[se] : 0u, lco = active ? a.loc_coords[so] : 0u;
 
-    // 1. residual on the block (sites u and u + Ve in site order), to LDS.  A later visit forms it from the
-    // stored x, not from the Schur residual of the last one: what rounding x to its storage type took away
-    // is then part of the residual and is corrected, where it would add up from sweep to sweep (binary16
-    // storage, 8^4: relative error 2.2e-4 at any number of sweeps, against 3.0e-4 to 5.2e-4 at 2 to 6).
-    if (a.sig_in) {
-        if (active) {
-            Spinor<Tc> x;
-            load_spinor<Tc>(g, a.x, grp, blk, u, tt, x);
-            lds_store<Tc>(rho, str, u * T + t, x);
-            load_spinor<Tc>(g, a.x, grp, blk, u + Ve, tt, x);
-            lds_store<Tc>(rho, str, (u + Ve) * T + t, x);
-        }
-        __syncthreads();
-        Spinor<Tc> r0, r1;
-        if (active) {
-            eo_residual_again<Ts, Tc, T>(a, rho, blk, u, grp, tt, t, r0);
-            eo_residual_again<Ts, Tc, T>(a, rho, blk, u + Ve, grp, tt, t, r1);
-        }
-        __syncthreads();
-        if (active) {
-            lds_store<Tc>(rho, str, u * T + t, r0);
-            lds_store<Tc>(rho, str, (u + Ve) * T + t, r1);
-        }
-    } else if (active) {
-        eo_residual<Ts, Tc, T>(a, rho, blk, u, grp, tt, t);
-        eo_residual<Ts, Tc, T>(a, rho, blk, u + Ve, grp, tt, t);
-    }
-    __syncthreads();
-    // 2. odd: eo = A_oo^-1 r_o (kept), -eo to LDS; even: rhat_e = r_e + H_eo (-eo)
+    // 1., 2. the Schur residual rhat_e on the even sites, to LDS, and on the odd ones their solution for the
+    // even sites as they are, less their x: eo = A_oo^-1 r_o, of which the even sites' hops read -eo from LDS.
     Spinor<Tc> ee, eo;
     spinor_zero(ee);
     spinor_zero(eo);
-    if (active) {
-        const int ns = blk * g.Vb + so;
-        Spinor<Tc> r;
-        lds_load<Tc>(rho, str, mo, r);
-        clover_site(a.cloverinv, g.V, ns, r, eo);
+    if (a.sig_in) {
+        // A later visit, sites in parity order.  From the stored x, not from the Schur residual that the last
+        // visit ended with: what rounding x to its storage type took away is then part of the residual and is
+        // corrected, where it would add up from sweep to sweep (binary16 storage, 8^4: relative error 2.2e-4
+        // at any number of sweeps, against 3.0e-4 to 5.2e-4 at 2 to 6).  The odd sites' old x drops out: with
+        // c = b minus the face hops, eo is their new x for the even sites as they are, A_oo^-1 (c_o - H_oe x_e),
+        // and rhat_e = c_e - A_ee x_e - H_eo eo: a step's work, where b - D_j x_j and its reduction to the even
+        // sites take 1.6 times that (16^3 x 32, 24 right-hand sides in FP32, 3 x 3: 2.70 against 2.85 ms).
+        // (LDS holds -x_e, so that every term adds.)  c is loaded ahead of the barrier before its phase.
+        Spinor<Tc> co, ce;
+        spinor_zero(co);
+        spinor_zero(ce);
+        if (active) {
+            Spinor<Tc> x;
+            load_spinor<Tc>(g, a.x, grp, blk, se, tt, x);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            r.re[c] = -eo.re[c];
-            r.im[c] = -eo.im[c];
+            for (int k = 0; k < 12; ++k) {
+                x.re[k] = -x.re[k];
+                x.im[k] = -x.im[k];
+            }
+            lds_store<Tc>(rho, str, me, x);
+            eo_rhs(a, blk, so, grp, tt, lco, co);
         }
-        lds_store<Tc>(rho, str, mo, r);
-    }
-    __syncthreads();
-    if (active) {
-        const int ns = blk * g.Vb + se;
-        Spinor<Tc> r;
-        lds_load<Tc>(rho, str, me, r);
-        eo_hops<Ts, Tc, T>(a, rho, ns, se, t, lce, r);
-        lds_store<Tc>(rho, str, me, r);
+        __syncthreads();
+        if (active) {
+            const int ns = opaque_index(blk * g.Vb + so);
+            eo_hops<Ts, Tc, T>(a, rho, ns, so, t, lco, co);
+            clover_site(a.cloverinv, g.V, ns, co, eo);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                co.re[k] = -eo.re[k];
+                co.im[k] = -eo.im[k];
+            }
+            lds_store<Tc>(rho, str, mo, co);
+            eo_rhs(a, blk, se, grp, tt, lce, ce);
+        }
+        __syncthreads();
+        if (active) {
+            const int ns = opaque_index(blk * g.Vb + se);
+            eo_clover<true>(a, rho, str, me, ns, ce);
+            eo_hops<Ts, Tc, T>(a, rho, ns, se, t, lce, ce);
+            lds_store<Tc>(rho, str, me, ce);
+        }
+    } else {
+        // a first visit: the residual on the block (sites u and u + Ve in site order), then odd and even
+        if (active) {
+            eo_residual<Ts, Tc, T>(a, rho, blk, u, grp, tt, t);
+            eo_residual<Ts, Tc, T>(a, rho, blk, u + Ve, grp, tt, t);
+        }
+        __syncthreads();
+        if (active) {
+            const int ns = blk * g.Vb + so;
+            Spinor<Tc> r;
+            lds_load<Tc>(rho, str, mo, r);
+            clover_site(a.cloverinv, g.V, ns, r, eo);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                r.re[c] = -eo.re[c];
+                r.im[c] = -eo.im[c];
+            }
+            lds_store<Tc>(rho, str, mo, r);
+        }
+        __syncthreads();
+        if (active) {
+            const int ns = blk * g.Vb + se;
+            Spinor<Tc> r;
+            lds_load<Tc>(rho, str, me, r);
+            eo_hops<Ts, Tc, T>(a, rho, ns, se, t, lce, r);
+            lds_store<Tc>(rho, str, me, r);
+        }
     }
 
     // 3. minimal residual on S over the even sites
@@ -1094,22 +1113,7 @@ __device__ inline void sap_block_eo(const SapArgs<Ts, Tc> &a, int blk, int tile,
         Tc qq = 0, qrr = 0, qri = 0;
         if (active) {
             const int ns = opaque_index(blk * g.Vb + se);
-            {
-                Spinor<Tc> own;
-                Tc A[36];
-                lds_load_half<0, Tc>(rho, str, me, own);
-                load_clover_half<0>(a.clover, g.V, ns, A);
-                clover_half<0>(A, own, q);
-            }
-            hop_fence(q);
-            {
-                Spinor<Tc> own;
-                Tc A[36];
-                lds_load_half<1, Tc>(rho, str, me, own);
-                load_clover_half<1>(a.clover, g.V, ns, A);
-                clover_half<1>(A, own, q);
-            }
-            hop_fence(q);
+            eo_clover<false>(a, rho, str, me, ns, q);
             eo_hops<Ts, Tc, T>(a, rho, ns, se, t, lce, q);
             mr_products(rho, str, me, q, qq, qrr, qri);
         } else {
