@@ -263,8 +263,8 @@ __device__ inline void tile_products(const float2 *const (&qb)[2], const float2 
 }
 
 template <typename Tc, typename Tq>
-__global__ void __launch_bounds__(NTHR, sizeof(Tc) == 4 && sizeof(Tq) <= 4 ? 4 : 1) k_coarse(CoarseArgs<Tq> a, const Tc *__restrict__ links,
-                                                 const Tc *__restrict__ clover)
+__global__ void __launch_bounds__(NTHR, sizeof(Tc) == 4 && sizeof(Tq) <= 4 ? 4 : 1)
+    k_coarse(CoarseArgs<Tq> a, const Tc *__restrict__ links, const Tc *__restrict__ clover)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int N = a.N, N2 = 2 * N;

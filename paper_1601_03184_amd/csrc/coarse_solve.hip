@@ -594,10 +594,11 @@ int gmres_run(GmArgs &a, const float *b, float *u, int m, double *res_out, int32
         if (int rc = dots((const TV *)V, a.cvlen, j + 1, a.w, j, GM_PROJECT)) return rc;
         if (j < FV) {
             // up to FV basis vectors: each projection with the inner products that follow it
-            hipLaunchKernelGGL((k_gm_project<TV, false>), dim3((G2 + nv - 1) / nv), dim3(DTHR), 0, st, a, G2, j + 1, nv);
+            const dim3 grid((G2 + nv - 1) / nv);
+            hipLaunchKernelGGL((k_gm_project<TV, false>), grid, dim3(DTHR), 0, st, a, G2, j + 1, nv);
             GM_CHECK("k_gm_project launch");
             if (int rc = finish(G2, j + 1, j, GM_PROJECT)) return rc;
-            hipLaunchKernelGGL((k_gm_project<TV, true>), dim3((G2 + nv - 1) / nv), dim3(DTHR), 0, st, a, G2, j + 1, nv);
+            hipLaunchKernelGGL((k_gm_project<TV, true>), grid, dim3(DTHR), 0, st, a, G2, j + 1, nv);
             GM_CHECK("k_gm_project launch");
             if (int rc = finish(G2, 1, j, GM_NORM)) return rc;
         } else {

@@ -63,7 +63,8 @@ template <typename Tx> struct ChunkVec {
     typedef Tx type __attribute__((ext_vector_type(16 / sizeof(Tx))));
 };
 
-template <typename Tx> __device__ __forceinline__ void chunk_store(typename ChunkVec<Tx>::type *lds, int me, const Spinor<Tx> &s)
+template <typename Tx>
+__device__ __forceinline__ void chunk_store(typename ChunkVec<Tx>::type *lds, int me, const Spinor<Tx> &s)
 {
     constexpr int n = ChunkVec<Tx>::n;
 #pragma unroll
@@ -143,8 +144,8 @@ __device__ __forceinline__ void fields_store(Tf *dst, int ns, const FieldVec<Tf>
 }
 
 template <int MU, bool FWD, typename Tx, typename Ts>
-__device__ __forceinline__ void hop_fetch(const KGeo &g, const Ts *__restrict__ x, int grp, int tt, int blk, int off, int o0,
-                                          int ns, const int (&bc)[4], const int (&lc)[4], HopIn<Tx> &h)
+__device__ __forceinline__ void hop_fetch(const KGeo &g, const Ts *__restrict__ x, int grp, int tt, int blk, int off,
+                                          int o0, int ns, const int (&bc)[4], const int (&lc)[4], HopIn<Tx> &h)
 {
     const NbrSite n = FWD ? nbr_fwd(g, MU, blk, off, bc, lc) : nbr_bwd(g, MU, blk, off, bc, lc);
     const int l = n.off - o0;
@@ -154,8 +155,8 @@ __device__ __forceinline__ void hop_fetch(const KGeo &g, const Ts *__restrict__ 
 }
 
 template <int MU, bool FWD, int TL, bool STAGED, typename Tc, typename Tx, typename Tf>
-__device__ __forceinline__ void hop_apply(const Tf *__restrict__ links, const Tf *fl, const typename ChunkVec<Tx>::type *lds,
-                                          int t, int own, HopIn<Tx> &h, Spinor<Tc> &out)
+__device__ __forceinline__ void hop_apply(const Tf *__restrict__ links, const Tf *fl,
+                                          const typename ChunkVec<Tx>::type *lds, int t, int own, HopIn<Tx> &h, Spinor<Tc> &out)
 {
     Tc U[18];
     if constexpr (STAGED) {
@@ -298,8 +299,8 @@ __global__ void __launch_bounds__(DIRAC_THREADS, 4)
     const bool ok = (int)threadIdx.x / TL < ns && grp < ngrp;
     Spinor<Tc> out;
     using Tx = typename Elem<Ts>::type;
-    dirac_chunk<TL, (sizeof(Ts) > 2), false>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x), grp, tt, w.blk,
-                                 o0, ns, ok, smem, out);
+    dirac_chunk<TL, (sizeof(Ts) > 2), false>(g, links, clover, blk_coords, loc_coords, reinterpret_cast<const Tx *>(x),
+                                             grp, tt, w.blk, o0, ns, ok, smem, out);
     if (ok) store_spinor(g, y, grp, w.blk, o0 + (int)threadIdx.x / TL, tt, out);
 }
 
@@ -310,8 +311,8 @@ void dirac_chunk_launch(const mrhs_op *op, const Tc *links, const Tc *clover, co
     const KGeo &g = op->k;
     const Chunks ch = chunks_of(g, DIRAC_THREADS / TL);
     const int threads = round64(ch.sites * TL), ntiles = (ngrp * g.S + TL - 1) / TL;
-    hipLaunchKernelGGL((k_dirac_chunk<Ts, Tc, TL>), dim3(g.nblk * ntiles * ch.n), dim3(threads), 24 * sizeof(Ts) * threads,
-                       st, g, links, clover, op->blk_coords, op->loc_coords, (const Ts *)x, (Ts *)y, ntiles, ch, ngrp);
+    hipLaunchKernelGGL((k_dirac_chunk<Ts, Tc, TL>), dim3(g.nblk * ntiles * ch.n), dim3(threads),
+                       24 * sizeof(Ts) * threads, st, g, links, clover, op->blk_coords, op->loc_coords, (const Ts *)x, (Ts *)y, ntiles, ch, ngrp);
 }
 
 // Per (block, tile of T right-hand sides, slot): partial sums of |b - D x|^2 and |b|^2 per right-hand
@@ -503,7 +504,10 @@ Chunks residual_chunks(const KGeo &g, int T)
 {
     return chunks_of(g, T >= 4 ? res_sites<8>() : T == 2 ? res_sites<2>() : res_sites<1>());
 }
-int residual_slots(const KGeo &g, int ntiles, int T) { return (long)g.nblk * ntiles < 2048 ? residual_chunks(g, T).n : 1; }
+int residual_slots(const KGeo &g, int ntiles, int T)
+{
+    return (long)g.nblk * ntiles < 2048 ? residual_chunks(g, T).n : 1;
+}
 
 size_t residual_bytes(const KGeo &g, int n_rhs, int T, int slots)
 {
@@ -523,8 +527,8 @@ int residual_launch(const mrhs_op *op, const void *b, const void *x, int n_rhs, 
     const int threads = round64(ch.sites * T);
     const size_t lds = 24 * sizeof(Ts) * threads + (residual_staged<Ts, T>() ? field_bytes(ch.sites) : 0);
     hipLaunchKernelGGL((k_residual<Ts, T>), dim3(g.nblk * ntiles * slots), dim3(threads), lds, st, g,
-                       op->links64, op->clover64, op->blk_coords, op->loc_coords, (const Ts *)b, (const Ts *)x, ntiles, ch,
-                       slots, ngrp, part);
+                       op->links64, op->clover64, op->blk_coords, op->loc_coords, (const Ts *)b, (const Ts *)x, ntiles,
+                       ch, slots, ngrp, part);
     if (int rc = hip_check(hipGetLastError(), "k_residual launch")) return rc;
     hipLaunchKernelGGL((k_residual_finish<T>), dim3(n_rhs), dim3(256), 0, st, part, g.nblk, slots, out);
     return hip_check(hipGetLastError(), "k_residual_finish launch");

@@ -11,13 +11,13 @@
 //      neighbours' spinors across the faces; all of them in flight at once),
 //   2. runs n_mr minimal-residual steps on the block operator D_j = I_j^T D I_j with the
 //      block residual rho kept in LDS ([24][Vb][T], conflict-free for the thread order),
-//      the two inner products per step reduced across the block with wavefront shuffles
+//      the two inner products per step reduced across the block with lane exchanges
 //      and one LDS exchange, and the correction e kept in registers,
 //   3. writes x|_j (+)= e, its residual and its own faces.
 // Bound by the vector units: an MR step issues 8 us of instructions per workgroup (of 9), and at tile
 // 4 the one workgroup of a CU has nothing to run beside its loads and stores (of about 55 us 9 for the
 // residual, 3-10 for the end).  32^3 x 64, 32 right-hand sides in FP32, 3 x 4, tile 4: 49.5 -> 46.5 ms per call
-// with the face buffers (of the 30 vector sets that a call must move at 4.4 TB/s, 22 ms), 42.2 with the reductions
+// with the face buffers (the 15 vector sets that a call must move take 22 ms at 4.4 TB/s), 42.2 with the reductions
 // by lane exchanges, 16-byte LDS vectors and the end of a visit without spills; the even-odd solver, which
 // formed the full residual at every visit from global memory, 3.34 -> 2.70 ms at 16^3 x 32 with 24, 3 x 3 (2.60
 // with a kept Schur residual, which the roundings of x left: see sap_block_eo).
@@ -353,7 +353,8 @@ __device__ __forceinline__ void sig_load(const KGeo &g, Tc *sig, int grp, int bl
 }
 
 template <typename Tc>
-__device__ __forceinline__ void sig_store(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt, const Spinor<Tc> &s)
+__device__ __forceinline__ void sig_store(const KGeo &g, Tc *sig, int grp, int blk, int off, int tt,
+                                          const Spinor<Tc> &s)
 {
     constexpr int n = V16<Tc>::n;
     typename V16<Tc>::mem *p = sig_ptr(g, sig, grp, blk, off, tt);
@@ -377,7 +378,8 @@ template <typename Tc> struct HalfSpinor {
 
 // first component vector of a site's entry on face `minus` of direction MU of block blk
 template <int MU, typename Ts, typename Tc, typename Tp>
-__device__ __forceinline__ auto face_ptr(const SapArgs<Ts, Tc> &a, Tp *face, int grp, int blk, bool minus, int f, int tt)
+__device__ __forceinline__ auto face_ptr(const SapArgs<Ts, Tc> &a, Tp *face, int grp, int blk, bool minus, int f,
+                                         int tt)
 {
     using V = std::conditional_t<std::is_const<Tp>::value, const typename V16<Tc>::mem, typename V16<Tc>::mem>;
     const KGeo &g = a.g;
@@ -410,14 +412,15 @@ template <int MU> __device__ __forceinline__ bool own_colour(const KGeo &g, int 
 
 // What the neighbour across the +MU face (fwd) or the -MU face left for this site
 template <int MU, typename Ts, typename Tc>
-__device__ __forceinline__ void face_load(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp, int tt, bool fwd,
-                                 HalfSpinor<Tc> &w)
+__device__ __forceinline__ void face_load(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp,
+                                          int tt, bool fwd, HalfSpinor<Tc> &w)
 {
     constexpr int n = V16<Tc>::n;
     const int bc = unpack_coord(bcp, MU);
     // both neighbours are uniform over the workgroup, the choice is the lane's
     const int nf = face_nbr<MU>(a.g, blk, bc, false), nb = face_nbr<MU>(a.g, blk, bc, true);
-    const Tc *bf = own_colour<MU>(a.g, bc, true) ? a.face_s : a.face_o, *bb = own_colour<MU>(a.g, bc, false) ? a.face_s : a.face_o;
+    const Tc *bf = own_colour<MU>(a.g, bc, true) ? a.face_s : a.face_o;
+    const Tc *bb = own_colour<MU>(a.g, bc, false) ? a.face_s : a.face_o;
     const auto *p = face_ptr<MU>(a, fwd ? bf : bb, grp, fwd ? nf : nb, fwd, face_index<MU>(a, lcp), tt);
     const uint32_t str = (uint32_t)(a.fg.vf[MU] * a.g.S);
 #pragma unroll
@@ -456,8 +459,8 @@ template <int MU, typename Tc> __device__ __forceinline__ void face_add(const Ha
 // most one of the two faces of a direction unless its block is one site thick there (then the
 // backward face follows); the loads of ND directions are issued before their arithmetic.
 template <int MU0, int ND, typename Ts, typename Tc>
-__device__ __forceinline__ void face_round(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp, int tt,
-                                  Spinor<Tc> &r)
+__device__ __forceinline__ void face_round(const SapArgs<Ts, Tc> &a, int grp, int blk, uint32_t bcp, uint32_t lcp,
+                                           int tt, Spinor<Tc> &r)
 {
     const KGeo &g = a.g;
     HalfSpinor<Tc> w[ND];
@@ -824,13 +827,17 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
             };
             // (the LDS link indices are hidden like ns: the links are re-read in every step)
             auto hops = [&]() {
-                block_hops<0, Tc, (NL > 0)>(g, a.links, rho, T, ns, off, t, lcp, q, ul, NL > 0 ? opaque_index(cf[0]) : 0, sb[0]);
+                block_hops<0, Tc, (NL > 0)>(g, a.links, rho, T, ns, off, t, lcp, q, ul,
+                                            NL > 0 ? opaque_index(cf[0]) : 0, sb[0]);
                 hop_fence(q);
-                block_hops<1, Tc, (NL > 1)>(g, a.links, rho, T, ns, off, t, lcp, q, ul, NL > 1 ? opaque_index(cf[1]) : 0, sb[1]);
+                block_hops<1, Tc, (NL > 1)>(g, a.links, rho, T, ns, off, t, lcp, q, ul,
+                                            NL > 1 ? opaque_index(cf[1]) : 0, sb[1]);
                 hop_fence(q);
-                block_hops<2, Tc, (NL > 2)>(g, a.links, rho, T, ns, off, t, lcp, q, ul, NL > 2 ? opaque_index(cf[2]) : 0, sb[2]);
+                block_hops<2, Tc, (NL > 2)>(g, a.links, rho, T, ns, off, t, lcp, q, ul,
+                                            NL > 2 ? opaque_index(cf[2]) : 0, sb[2]);
                 hop_fence(q);
-                block_hops<3, Tc, (NL > 3)>(g, a.links, rho, T, ns, off, t, lcp, q, ul, NL > 3 ? opaque_index(cf[3]) : 0, sb[3]);
+                block_hops<3, Tc, (NL > 3)>(g, a.links, rho, T, ns, off, t, lcp, q, ul,
+                                            NL > 3 ? opaque_index(cf[3]) : 0, sb[3]);
                 hop_fence(q);
             };
             // Every wavefront starts the step together after the barrier; the clover term is read
@@ -858,11 +865,12 @@ __device__ __forceinline__ void sap_block(const SapArgs<Ts, Tc> &a, int blk, int
 
     // 3. x|_j (+)= e, and with the incremental residual rho and the faces for later visits
     if (active)
-        finish_site(a, grp, blk, off, bcp, (uint32_t)opaque_index((int)lcp), tt, e, a.mode == 2, [&]() __attribute__((always_inline)) {
-            Spinor<Tc> rr;
-            lds_load<Tc>(rho, str, me, rr);
-            sig_store(g, a.sig, grp, blk, off, tt, rr);
-        });
+        finish_site(a, grp, blk, off, bcp, (uint32_t)opaque_index((int)lcp), tt, e, a.mode == 2,
+                    [&]() __attribute__((always_inline)) {
+                        Spinor<Tc> rr;
+                        lds_load<Tc>(rho, str, me, rr);
+                        sig_store(g, a.sig, grp, blk, off, tt, rr);
+                    });
     // 4. sigma for the next visit: b - D_j x_j(new) = rho (the block residual after the MR
     //    steps, this lane's own LDS slot) + the face hops, which this half-sweep leaves unchanged
     //    (kept from step 1, or formed again after a full residual)
@@ -906,7 +914,8 @@ __device__ inline void eo_hops(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho,
 
 // q = (ADD: +=) the clover term at one of the even sites, one chiral half at a time
 template <bool ADD, typename Ts, typename Tc>
-__device__ inline void eo_clover(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int str, int me, int ns, Spinor<Tc> &q)
+__device__ inline void eo_clover(const SapArgs<Ts, Tc> &a, const LdsPair<Tc> *rho, int str, int me, int ns,
+                                 Spinor<Tc> &q)
 {
     {
         Spinor<Tc> own;
@@ -1422,10 +1431,12 @@ size_t ws_bytes_sap_batched(const mrhs_op *const *ops, int n, const int32_t *n_r
         const mrhs_op *op = ops[k];
         const bool f64 = op->prec == MRHS_PREC_F64;
         w += align256(native_elems(op, n_rhs[k]) * (f64 ? sizeof(double) : sizeof(float)));  // sigma / rho
-        w += align256(f64 ? face_elems<double>(op, n_rhs[k]) * sizeof(double) : face_elems<float>(op, n_rhs[k]) * sizeof(float));
+        w += align256(f64 ? face_elems<double>(op, n_rhs[k]) * sizeof(double)
+                          : face_elems<float>(op, n_rhs[k]) * sizeof(float));
         if (op->odd_blocks)
             w += f64 ? odd_bytes<double, double>(op, n_rhs[k])
-                     : op->dtype == MRHS_DTYPE_F16 ? odd_bytes<__half, float>(op, n_rhs[k]) : odd_bytes<float, float>(op, n_rhs[k]);
+                 : op->dtype == MRHS_DTYPE_F16 ? odd_bytes<__half, float>(op, n_rhs[k])
+                                               : odd_bytes<float, float>(op, n_rhs[k]);
     }
     return w;
 }

@@ -216,9 +216,9 @@ __global__ void __launch_bounds__(TTHR) k_restrict(TransArgs a)
 }
 
 // ---------------------------------------------------------------------------------------
-// prolongation: up to PSPLIT workgroups per (aggregate i, half h), as many as its 16-row blocks fill with
-// a block per wavefront, each taking every PSPLIT-th group of them (the output rows are independent).  (y_c)^h_i is staged in LDS;
-// each wavefront forms 16-row blocks of Q^h_i (y_c)^h_i, K = the test vectors.  Operand row
+// prolongation: up to PSPLIT workgroups per (aggregate i, half h), as many as its 16-row blocks fill
+// with a block per wavefront (16 sites: two; 16^4 in 2^4 aggregates, 8 vectors, 64 -> 41 us), which take the
+// groups of blocks in turn (the output rows are independent).  (y_c)^h_i is staged in LDS; each wavefront forms 16-row blocks of Q^h_i (y_c)^h_i, K = the test vectors.  Operand row
 // 4g + q of a block is site s0 + 4q + g, so that accumulator register q of the four lane
 // groups g = l/16 holds four neighbouring sites and a store covers their runs side by side.
 // ---------------------------------------------------------------------------------------
